@@ -8,7 +8,7 @@
 
 namespace gammax {
 
-// Output tile of one convolution workgroup: 16 nodes along x (one MFMA column block) by
+// Output tile of one bwd-weight step: 16 nodes along x (one MFMA column block) by
 // 8 rows along y by 4 planes along z.
 constexpr int CNN_TILE_X = 16, CNN_TILE_Y = 8, CNN_TILE_Z = 4;
 // Floats per workgroup partial of bwd-weight: 27 taps x 16 x 16, then 16 bias sums.
@@ -47,9 +47,11 @@ struct BwdWArgs {
     int64_t g_vstride;
     float* partial;          // CNN_PARTIAL_STRIDE floats per workgroup
     int tiles_x, tiles_y, tiles_z;
+    int ntiles;              // tiles over every volume
 };
 
-int64_t conv_blocks(const int o[3], int nvol);
+// Workgroups (= partials) of bwd-weight for output shape o.
+int bwdw_blocks(const int o[3], int nvol);
 // mode 0: relu -> bf16; 1: linear -> FP32 channel 0 (the last layer, fragments packed by
 // shifts: launch_pack bwd == 2); 2: bwd-data with ReLU mask -> bf16
 hipError_t launch_conv(int cin, int mode, const uint16_t* in, const int i[3], int64_t in_vstride,

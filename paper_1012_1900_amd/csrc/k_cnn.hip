@@ -23,7 +23,8 @@
 // Backward: bwd-data is the same kernel run on the output gradient with the flipped,
 // transposed kernel and an input offset of -2 (full correlation), times the ReLU mask of
 // the stored activation; bwd-weight contracts over nodes (D[co][ci] per tap, both
-// operands staged planar in LDS), one partial per workgroup, reduced deterministically.
+// operands staged node-major and read transposed from LDS), one partial per workgroup,
+// reduced deterministically.
 #include <type_traits>
 
 #include "internal.hpp"
@@ -170,11 +171,11 @@ __host__ __device__ constexpr int ftap_offset(int t) { return ((t / 9) * FLY + (
 // e = t % E of a box row of E slots and the rows t / E + RPR k, so its x coordinate and x
 // bounds test are fixed.  All loads of a thread are issued before the first store, so the
 // rounds share one memory latency (an outside node loads node 0 and stores 0).
-template <int CIN, int BX, int BY, int BZ>
+template <int CIN, int BX, int BY, int BZ, int THREADS = FTHREADS>
 __device__ __forceinline__ void stage_box(const uint16_t* __restrict__ in, int ix, int iy, int iz, int gx0, int gy0,
                                           int gz0, uint16_t* tile) {
     constexpr int PER_NODE = CIN == 16 ? 2 : 1;
-    constexpr int E = BX * PER_NODE, RPR = FTHREADS / E, NROW = BZ * BY;
+    constexpr int E = BX * PER_NODE, RPR = THREADS / E, NROW = BZ * BY;
     constexpr int ROUNDS = (NROW + RPR - 1) / RPR;
     constexpr int SLOT = CIN == 16 ? 8 : 2;   // bf16 per slot
     static_assert(ROUNDS <= 32, "one mask bit per round");
@@ -569,126 +570,180 @@ __global__ __launch_bounds__(FTHREADS) __attribute__((amdgpu_waves_per_eu(4))) v
 
 // ---- bwd-weight --------------------------------------------------------------------------
 //
-// Per workgroup: one TX x TY x TZ tile of output nodes of one volume.  For each tap,
-// D[co][ci] = sum over the tile's nodes of g[node][co] * x[node + tap][ci]  (k = nodes).
-// Both operands are staged planar in LDS (channel-major) so that 8 consecutive nodes of
-// one channel are contiguous.  Output: partial[block][tap][co][ci] and the bias partial
-// sum_node g[node][co] at partial[block][27 * 256 + co].
-template <int CIN>
-__global__ __launch_bounds__(NTHREADS) void k_conv_bwdw(BwdWArgs a) {
-    constexpr int NX = LZ * LY * LX, NG = TZ * TY * TX;
-    __shared__ __align__(16) uint16_t xs[CIN * NX];
-    __shared__ __align__(16) uint16_t gs[16 * NG];
-    __shared__ float bsum[NTHREADS];
+// For each tap, D[co][ci] = sum over nodes of g[node][co] * x[node + tap][ci] (k = nodes).
+// A workgroup takes TX x TY x TZ tiles of output nodes in turn (block b: tiles b, b + grid,
+// ...), keeps its sums in registers across them and writes one partial at the end:
+// partial[block][tap][co][ci], then the bias sums partial[block][27 * 256 + co].
+//
+// Operands.  Both tiles are staged as they lie in memory (node-major, 16 channels of a node
+// in 32 bytes) and read with the transposing LDS load (ds_read_b64_tr_b16): the 16 lanes of
+// a group supply four nodes' 32 bytes and lane c receives channel c of those four nodes.  A
+// chunk of k is two output rows (16 nodes along x each) of neighbouring z planes: lane group
+// g holds nodes x = 4 g .. 4 g + 3 of both, and the input operand of a tap is the same read
+// at the tap's offset, an immediate.  The form before this one staged channel-major with
+// 2-byte stores and gathered each operand with eight 2-byte reads: 75 us for a 16-channel
+// layer of 16 crops of 24 x 24 x 32 outputs, 15.7 us now.
+//
+// A wave owns the nine taps of one dz: the operand of an input row at shift dx serves the
+// three dy (output rows Y, Y - 1, Y - 2, kept in registers), so 8 LDS reads feed 9 products.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+constexpr int BW_THREADS = 192;   // one wave per dz
 
-    int b = blockIdx.x;
-    const int txi = b % a.tiles_x;
+__device__ __forceinline__ uint2 lds_read_tr(const uint16_t* p) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(p)));
+}
+__device__ __forceinline__ U4 pair_of(uint2 a, uint2 b) { return U4{a.x, a.y, b.x, b.y}; }
+
+struct BwTile {
+    int vol, x0, y0, z0;
+};
+__device__ __forceinline__ BwTile bw_tile(const BwdWArgs& a, int b) {
+    BwTile t;
+    t.x0 = (b % a.tiles_x) * TX;
     b /= a.tiles_x;
-    const int tyi = b % a.tiles_y;
+    t.y0 = (b % a.tiles_y) * TY;
     b /= a.tiles_y;
-    const int tzi = b % a.tiles_z;
-    const int vol = b / a.tiles_z;
-    const int x0 = txi * TX, y0 = tyi * TY, z0 = tzi * TZ;
-    const uint16_t* xin = a.x + (int64_t)vol * a.x_vstride;
-    const uint16_t* gin = a.g + (int64_t)vol * a.g_vstride;
-
-    for (int v = threadIdx.x; v < NX; v += NTHREADS) {
-        const int lx = v % LX, ly = (v / LX) % LY, lz = v / (LX * LY);
-        const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
-        const bool in = gx < a.ix && gy < a.iy && gz < a.iz;
-        const int64_t src = (((int64_t)gz * a.iy + gy) * a.ix + gx) * CIN;
-        if (CIN == 16) {
-            U4 q0 = {0u, 0u, 0u, 0u}, q1 = {0u, 0u, 0u, 0u};
-            if (in) {
-                q0 = *reinterpret_cast<const U4*>(xin + src);
-                q1 = *reinterpret_cast<const U4*>(xin + src + 8);
-            }
-            const uint32_t w8[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                xs[(2 * c) * NX + v] = (uint16_t)(w8[c] & 0xFFFFu);
-                xs[(2 * c + 1) * NX + v] = (uint16_t)(w8[c] >> 16);
-            }
-        } else {
-            uint32_t q = in ? *reinterpret_cast<const uint32_t*>(xin + src) : 0u;
-            xs[v] = (uint16_t)(q & 0xFFFFu);
-            xs[NX + v] = (uint16_t)(q >> 16);
-        }
-    }
-    for (int v = threadIdx.x; v < NG; v += NTHREADS) {
-        const int tx = v % TX, ty = (v / TX) % TY, tz = v / (TX * TY);
-        const int gx = x0 + tx, gy = y0 + ty, gz = z0 + tz;
-        U4 q0 = {0u, 0u, 0u, 0u}, q1 = {0u, 0u, 0u, 0u};
-        if (gx < a.ox && gy < a.oy && gz < a.oz) {
-            const int64_t src = (((int64_t)gz * a.oy + gy) * a.ox + gx) * 16;
-            q0 = *reinterpret_cast<const U4*>(gin + src);
-            q1 = *reinterpret_cast<const U4*>(gin + src + 8);
-        }
-        const uint32_t w8[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            gs[(2 * c) * NG + v] = (uint16_t)(w8[c] & 0xFFFFu);
-            gs[(2 * c + 1) * NG + v] = (uint16_t)(w8[c] >> 16);
-        }
-    }
-    __syncthreads();
-
-    float* part = a.partial + (int64_t)blockIdx.x * CNN_PARTIAL_STRIDE;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int j = lane & 15, g = lane >> 4;
-    for (int t = wv; t < 27; t += NTHREADS / 64) {
-        int dz, dy, dx;
-        tap_xyz(t, dz, dy, dx);
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int c = 0; c < NG / 32; ++c) {
-            const int row = 2 * c + (g >> 1);           // row = tz * TY + ty
-            const int ty = row % TY, tz = row / TY, xo = 8 * (g & 1);
-            const U4 aop = *reinterpret_cast<const U4*>(&gs[j * NG + row * TX + xo]);
-            U4 bop = {0u, 0u, 0u, 0u};
-            if (j < CIN) {
-                const uint16_t* p = &xs[j * NX + ((tz + dz) * LY + ty + dy) * LX + xo + dx];
-                bop.x = (uint32_t)p[0] | ((uint32_t)p[1] << 16);
-                bop.y = (uint32_t)p[2] | ((uint32_t)p[3] << 16);
-                bop.z = (uint32_t)p[4] | ((uint32_t)p[5] << 16);
-                bop.w = (uint32_t)p[6] | ((uint32_t)p[7] << 16);
-            }
-            acc = mfma_bf16(aop, bop, acc);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) part[t * 256 + (4 * g + r) * 16 + j] = acc[r];
-    }
-    // bias: sum over the tile of g[node][co]; 16 threads per channel
-    {
-        const int co = threadIdx.x & 15, q = threadIdx.x >> 4;
-        float s = 0.f;
-        for (int v = q; v < NG; v += NTHREADS / 16) s += bf2f(gs[co * NG + v]);
-        bsum[threadIdx.x] = s;
-        __syncthreads();
-        if (threadIdx.x < 16) {
-            float t = 0.f;
-            for (int k = 0; k < NTHREADS / 16; ++k) t += bsum[k * 16 + threadIdx.x];
-            part[27 * 256 + threadIdx.x] = t;
-        }
-    }
+    t.z0 = (b % a.tiles_z) * TZ;
+    t.vol = b / a.tiles_z;
+    return t;
 }
 
-// Sum of the per-workgroup partials into the flat gradient of one layer (FP32, the
-// parameter order W[co][ci][tap], b[co]).
-__global__ __launch_bounds__(256) void k_grad_reduce(const float* __restrict__ partial, int nblocks, int cin,
-                                                     int cout, float* __restrict__ grad) {
-    const int nw = cout * cin * 27;
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= nw + cout) return;
-    int src;
-    if (p < nw) {
-        const int co = p / (cin * 27), ci = (p / 27) % cin, t = p % 27;
-        src = t * 256 + co * 16 + ci;
-    } else {
-        src = 27 * 256 + (p - nw);
+// The gradient operand of output row (y, z) and (y, z + 1): channel lane & 15, nodes
+// 4 (lane / 16) .. + 3 of each.  at: this lane's element offset within a row (x, channel quad).
+__device__ __forceinline__ U4 bw_operand(const uint16_t* tile, int at, int row0, int row1, int row_nodes) {
+    return pair_of(lds_read_tr(tile + (row0 * row_nodes) * 16 + at), lds_read_tr(tile + (row1 * row_nodes) * 16 + at));
+}
+
+__global__ __launch_bounds__(BW_THREADS) void k_conv_bwdw16(BwdWArgs a) {
+    constexpr int NX = LZ * LY * LX, NG = TZ * TY * TX;
+    __shared__ __align__(16) uint16_t xs[NX * 16];
+    __shared__ __align__(16) uint16_t gs[NG * 16];
+    const int lane = threadIdx.x & 63, dz = threadIdx.x >> 6;
+    const int j = lane & 15, g = lane >> 4;
+    const int at = (4 * g + (j >> 2)) * 16 + (j & 3) * 4;
+    const U4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};   // bf16 1.0
+    f32x4 acc[9], bias = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 9; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int b = blockIdx.x; b < a.ntiles; b += gridDim.x) {
+        const BwTile t = bw_tile(a, b);
+        stage_box<16, LX, LY, LZ, BW_THREADS>(a.x + (int64_t)t.vol * a.x_vstride, a.ix, a.iy, a.iz, t.x0, t.y0, t.z0, xs);
+        stage_box<16, TX, TY, TZ, BW_THREADS>(a.g + (int64_t)t.vol * a.g_vstride, a.ox, a.oy, a.oz, t.x0, t.y0, t.z0, gs);
+        __syncthreads();
+#pragma unroll 1
+        for (int z = 0; z < TZ; z += 2) {
+            U4 ga[3];   // gradient rows Y, Y - 1, Y - 2 (slot y % 3)
+#pragma unroll
+            for (int Y = 0; Y < TY + 2; ++Y) {
+                if (Y < TY) {
+                    ga[Y % 3] = bw_operand(gs, at, z * TY + Y, (z + 1) * TY + Y, TX);
+                    if (dz == 0) bias = mfma_bf16(ga[Y % 3], ones, bias);
+                }
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx) {
+                    const U4 xb = bw_operand(xs + dx * 16, at, (z + dz) * LY + Y, (z + 1 + dz) * LY + Y, LX);
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy)
+                        if (Y - dy >= 0 && Y - dy < TY)
+                            acc[3 * dy + dx] = mfma_bf16(ga[(Y - dy + 3) % 3], xb, acc[3 * dy + dx]);
+                }
+            }
+        }
+        __syncthreads();   // the tiles are staged again
     }
+    float* part = a.partial + (int64_t)blockIdx.x * CNN_PARTIAL_STRIDE;
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[(9 * dz + k) * 256 + (4 * g + r) * 16 + j] = acc[k][r];
+    if (dz == 0 && j == 0)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[27 * 256 + 4 * g + r] = bias[r];
+}
+
+// Layer 1 (2 input channels): the 16 columns of a product hold 8 taps x 2 channels (column
+// 2 q + ci of wave w: tap 8 w + q), so four waves cover the 27 taps with one product per
+// chunk each, where one tap per product would leave 14 of 16 columns empty.  A lane's four
+// nodes of one channel are the halves of four consecutive words of the feature row.
+__global__ __launch_bounds__(NTHREADS) void k_conv_bwdw2(BwdWArgs a) {
+    constexpr int NX = LZ * LY * LX, NG = TZ * TY * TX;
+    __shared__ uint32_t xs[NX];
+    __shared__ __align__(16) uint16_t gs[NG * 16];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int j = lane & 15, g = lane >> 4;
+    const int at = (4 * g + (j >> 2)) * 16 + (j & 3) * 4;
+    const int tap = 8 * wv + (j >> 1), tr = tap < 27 ? tap : 26;   // a column past tap 26 is not stored
+    int dz, dy, dx;
+    tap_xyz(tr, dz, dy, dx);
+    const uint32_t* xl = xs + (dz * LY + dy) * LX + dx + 4 * g;
+    const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;      // high or low halves of two words
+    const U4 ones = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f}, bias = {0.f, 0.f, 0.f, 0.f};
+
+    for (int b = blockIdx.x; b < a.ntiles; b += gridDim.x) {
+        const BwTile t = bw_tile(a, b);
+        stage_box<2, LX, LY, LZ, NTHREADS>(a.x + (int64_t)t.vol * a.x_vstride, a.ix, a.iy, a.iz, t.x0, t.y0, t.z0,
+                                           reinterpret_cast<uint16_t*>(xs));
+        stage_box<16, TX, TY, TZ, NTHREADS>(a.g + (int64_t)t.vol * a.g_vstride, a.ox, a.oy, a.oz, t.x0, t.y0, t.z0, gs);
+        __syncthreads();
+#pragma unroll 1
+        for (int z = 0; z < TZ; z += 2)
+#pragma unroll
+            for (int y = 0; y < TY; ++y) {
+                const U4 ga = bw_operand(gs, at, z * TY + y, (z + 1) * TY + y, TX);
+                if (wv == 0) bias = mfma_bf16(ga, ones, bias);
+                const uint32_t* p = xl + (z * LY + y) * LX;
+                const uint32_t* q = p + LY * LX;
+                const U4 xb = {__builtin_amdgcn_perm(p[1], p[0], sel), __builtin_amdgcn_perm(p[3], p[2], sel),
+                               __builtin_amdgcn_perm(q[1], q[0], sel), __builtin_amdgcn_perm(q[3], q[2], sel)};
+                acc = mfma_bf16(ga, xb, acc);
+            }
+        __syncthreads();   // the tiles are staged again
+    }
+    float* part = a.partial + (int64_t)blockIdx.x * CNN_PARTIAL_STRIDE;
+    if (tap < 27)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[tap * 256 + (4 * g + r) * 16 + (j & 1)] = acc[r];
+    if (wv == 0 && j == 0)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[27 * 256 + 4 * g + r] = bias[r];
+}
+
+// Sum of the per-workgroup partials of one layer into its flat gradient (FP32, the parameter
+// order W[co][ci][tap], b[co]).  A block takes 64 consecutive partial words; its 16 waves sum
+// every 16th partial each, eight loads in flight, and the 16 sums are added in wave order (a
+// fixed order: training is deterministic).  One thread per parameter walking all partials
+// was a chain of one load latency per partial: 384 us for a layer of 1500 partials, 7.4 us now.
+constexpr int GR_WAVES = 16;
+__global__ __launch_bounds__(64 * GR_WAVES) void k_grad_reduce(const float* __restrict__ partial, int nblocks, int cin,
+                                                               int cout, float* __restrict__ grad) {
+    __shared__ float s_sum[GR_WAVES][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int src = blockIdx.x * 64 + lane;
+    const bool live = src < CNN_PARTIAL_STRIDE;
+    const float* p = partial + (live ? src : 0);
     float s = 0.f;
-    for (int b = 0; b < nblocks; ++b) s += partial[(int64_t)b * CNN_PARTIAL_STRIDE + src];
-    grad[p] = s;
+    int b = wv;
+    for (; b + 7 * GR_WAVES < nblocks; b += 8 * GR_WAVES) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = p[(int64_t)(b + k * GR_WAVES) * CNN_PARTIAL_STRIDE];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s += v[k];
+    }
+    for (; b < nblocks; b += GR_WAVES) s += p[(int64_t)b * CNN_PARTIAL_STRIDE];
+    s_sum[wv][lane] = s;
+    __syncthreads();
+    if (wv != 0 || !live) return;
+    s = 0.f;
+#pragma unroll
+    for (int k = 0; k < GR_WAVES; ++k) s += s_sum[k][lane];
+    const int t = src >> 8, co = t < 27 ? (src >> 4) & 15 : src & 15, ci = src & 15;
+    if (co >= cout) return;
+    if (t == 27) grad[cout * cin * 27 + co] = s;
+    else if (ci < cin) grad[(co * cin + ci) * 27 + t] = s;
 }
 
 // Loss: r = y - log(gamma + 0.01) at nodes with gamma >= 0; output gradient
@@ -1224,8 +1279,16 @@ int grid_for(int64_t n, int64_t cap) {
 
 }  // namespace
 
-int64_t conv_blocks(const int o[3], int nvol) {
+namespace {
+int64_t conv_tiles(const int o[3], int nvol) {
     return (int64_t)((o[2] + TX - 1) / TX) * ((o[1] + TY - 1) / TY) * ((o[0] + TZ - 1) / TZ) * nvol;
+}
+}  // namespace
+
+int bwdw_blocks(const int o[3], int nvol) {
+    // three workgroups of 51 KB of LDS fit a compute unit: 768 fill the card's 256
+    const int64_t t = conv_tiles(o, nvol);
+    return (int)(t < 768 ? t : 768);
 }
 
 hipError_t launch_conv(int cin, int mode, const uint16_t* in, const int i[3], int64_t in_vstride,
@@ -1313,17 +1376,20 @@ hipError_t launch_conv_bwdw(int cin, const uint16_t* x, const int i[3], int64_t 
     a.tiles_x = (o[2] + TX - 1) / TX;
     a.tiles_y = (o[1] + TY - 1) / TY;
     a.tiles_z = (o[0] + TZ - 1) / TZ;
-    const int64_t nb = conv_blocks(o, nvol);
-    if (nb <= 0) return hipSuccess;
-    if (cin == 2) hipLaunchKernelGGL((k_conv_bwdw<2>), dim3((unsigned)nb), dim3(NTHREADS), 0, s, a);
-    else if (cin == 16) hipLaunchKernelGGL((k_conv_bwdw<16>), dim3((unsigned)nb), dim3(NTHREADS), 0, s, a);
+    const int64_t nt = conv_tiles(o, nvol);
+    if (nt <= 0) return hipSuccess;
+    if (nt > 0x7fffffff) return hipErrorInvalidValue;
+    a.ntiles = (int)nt;
+    const unsigned nb = (unsigned)bwdw_blocks(o, nvol);
+    if (cin == 2) hipLaunchKernelGGL(k_conv_bwdw2, dim3(nb), dim3(NTHREADS), 0, s, a);
+    else if (cin == 16) hipLaunchKernelGGL(k_conv_bwdw16, dim3(nb), dim3(BW_THREADS), 0, s, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 hipError_t launch_grad_reduce(const float* partial, int nblocks, int cin, int cout, float* grad, hipStream_t s) {
-    const int n = cout * cin * 27 + cout;
-    hipLaunchKernelGGL(k_grad_reduce, dim3((n + 255) / 256), dim3(256), 0, s, partial, nblocks, cin, cout, grad);
+    hipLaunchKernelGGL(k_grad_reduce, dim3((CNN_PARTIAL_STRIDE + 63) / 64), dim3(64 * GR_WAVES), 0, s, partial, nblocks,
+                       cin, cout, grad);
     return hipGetLastError();
 }
 

@@ -119,7 +119,7 @@ TrainWs train_layout(unsigned char* base, int nvol, const int o[3]) {
     w.g3 = (uint16_t*)take(nvol * vol_of(s3) * 32);
     w.g2 = (uint16_t*)take(nvol * vol_of(s2) * 32);
     w.g1 = (uint16_t*)take(nvol * vol_of(s1) * 32);
-    w.nb_partial = (int)conv_blocks(s1, nvol);   // the largest bwd-weight grid (layer 0)
+    w.nb_partial = bwdw_blocks(s1, nvol);   // the largest bwd-weight grid (layer 0)
     w.partial = (float*)take((int64_t)w.nb_partial * CNN_PARTIAL_STRIDE * 4);
     w.nb_loss = loss_blocks(nvol * vol_of(o));
     w.loss_part = (float*)take((int64_t)w.nb_loss * 4);
@@ -344,7 +344,7 @@ gammax_status_t gammax_model_train_step(gammax_model_t* m, int32_t nvol, const i
         const int cin = CNN_CIN[l];
         const int64_t xs = vol_of(xshape[l]) * cin, gs = vol_of(gshape[l]) * 16;
         MCHK(m, launch_conv_bwdw(cin, xin[l], xshape[l], xs, gout[l], gshape[l], gs, nvol, w.partial, s));
-        const int nb = (int)conv_blocks(gshape[l], nvol);
+        const int nb = bwdw_blocks(gshape[l], nvol);
         MCHK(m, launch_grad_reduce(w.partial, nb, cin, CNN_COUT[l], m->grad + CNN_OFF[l], s));
         if (l > 0) {
             // gradient of the input, times the ReLU derivative of the stored activation
