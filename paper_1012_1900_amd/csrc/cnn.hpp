@@ -22,6 +22,20 @@ constexpr int CNN_OFF[CNN_LAYERS] = {0, 880, 7808, 14736};
 constexpr int CNN_NPARAM = 15169;
 // bf16 elements of one layer's fragment array (chunks x 64 lanes x 8)
 constexpr int CNN_FRAG_ELEMS = 14 * 64 * 8;
+// fragment arrays of the network: forward layers 0..3, then bwd-data layers 1..3
+constexpr int CNN_FRAG_ARRAYS = 7;
+struct PackOffsets {
+    int w[CNN_LAYERS];       // first weight of each layer
+};
+
+// The partials of every layer, the gradient they sum to, and the Adam state it updates.
+struct GradArgs {
+    const float* partial[CNN_LAYERS];
+    int nblocks[CNN_LAYERS];
+    int off[CNN_LAYERS];     // first parameter of each layer
+    float *grad, *theta, *m, *v;
+    float lr, beta1, beta2, eps, c1, c2;
+};
 
 struct ConvArgs {
     const uint16_t* in;      // channel-last bf16 (CIN channels)
@@ -65,14 +79,14 @@ hipError_t launch_conv12(const uint16_t* feat, const int f[3], int64_t feat_vstr
                          int64_t out_vstride, int nvol, hipStream_t s);
 hipError_t launch_conv_bwdw(int cin, const uint16_t* x, const int i[3], int64_t x_vstride, const uint16_t* g,
                             const int o[3], int64_t g_vstride, int nvol, float* partial, hipStream_t s);
-hipError_t launch_grad_reduce(const float* partial, int nblocks, int cin, int cout, float* grad, hipStream_t s);
+// Sums the partials of the four layers into the gradient and takes the Adam step.
+hipError_t launch_grad_reduce(const GradArgs& a, hipStream_t s);
 int loss_blocks(int64_t n);
-hipError_t launch_loss(const float* y, const float* gamma, int64_t n, float scale, uint16_t* gout, float* loss_part,
-                       int nblocks, hipStream_t s);
-hipError_t launch_adam(float* theta, float* m, float* v, const float* grad, int n, float lr, float beta1,
-                       float beta2, float eps, float c1, float c2, hipStream_t s);
-// Fragments of one layer: bwd 0 forward, 1 bwd-data, 2 the last layer by shifts.
-hipError_t launch_pack(const float* w, int cin, int cout, int bwd, uint16_t* frag, hipStream_t s);
+// count: labelled nodes of the batch (device); the output gradient is scaled by 2 / count.
+hipError_t launch_loss(const float* y, const float* gamma, int64_t n, const unsigned long long* count, uint16_t* gout,
+                       float* loss_part, int nblocks, hipStream_t s);
+// The fragment arrays of every layer from the parameters.
+hipError_t launch_pack(const float* theta, uint16_t* frags, hipStream_t s);
 // The network at the listed nodes only (their 9^3 patches): y[i] for node nodes[i], i < *count;
 // key (optional) receives the bits of gamma_hat.  n: grid shape, slowest first.
 hipError_t launch_cnn_tail(const float* ref, const float* ev, const int n[3], const Scalars* sc,

@@ -711,19 +711,25 @@ __global__ __launch_bounds__(NTHREADS) void k_conv_bwdw2(BwdWArgs a) {
         for (int r = 0; r < 4; ++r) part[27 * 256 + 4 * g + r] = bias[r];
 }
 
-// Sum of the per-workgroup partials of one layer into its flat gradient (FP32, the parameter
-// order W[co][ci][tap], b[co]).  A block takes 64 consecutive partial words; its 16 waves sum
+// Sum of the per-workgroup partials into the flat gradient (FP32, per layer W[co][ci][tap],
+// b[co]) and, by the thread that holds a parameter's sum, its Adam step with bias correction
+// (c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t)): one launch for the four layers
+// (blockIdx.y).  A block takes 64 consecutive partial words of a layer; its 16 waves sum
 // every 16th partial each, eight loads in flight, and the 16 sums are added in wave order (a
 // fixed order: training is deterministic).  One thread per parameter walking all partials
-// was a chain of one load latency per partial: 384 us for a layer of 1500 partials, 7.4 us now.
+// was a chain of one load latency per partial: 384 us for a layer of 1500 partials; 7.4 us
+// with the waves sharing them, and 16 us for the four layers with Adam in one launch
+// (four reductions and Adam took 34).
 constexpr int GR_WAVES = 16;
-__global__ __launch_bounds__(64 * GR_WAVES) void k_grad_reduce(const float* __restrict__ partial, int nblocks, int cin,
-                                                               int cout, float* __restrict__ grad) {
+__global__ __launch_bounds__(64 * GR_WAVES) void k_grad_reduce(GradArgs a) {
     __shared__ float s_sum[GR_WAVES][64];
+    const int l = blockIdx.y;
+    const int cin = l == 0 ? CNN_CIN[0] : CNN_CIN[1], cout = l == CNN_LAYERS - 1 ? CNN_COUT[3] : CNN_COUT[0];
+    const int nblocks = a.nblocks[l];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int src = blockIdx.x * 64 + lane;
     const bool live = src < CNN_PARTIAL_STRIDE;
-    const float* p = partial + (live ? src : 0);
+    const float* p = a.partial[l] + (live ? src : 0);
     float s = 0.f;
     int b = wv;
     for (; b + 7 * GR_WAVES < nblocks; b += 8 * GR_WAVES) {
@@ -741,18 +747,26 @@ __global__ __launch_bounds__(64 * GR_WAVES) void k_grad_reduce(const float* __re
 #pragma unroll
     for (int k = 0; k < GR_WAVES; ++k) s += s_sum[k][lane];
     const int t = src >> 8, co = t < 27 ? (src >> 4) & 15 : src & 15, ci = src & 15;
-    if (co >= cout) return;
-    if (t == 27) grad[cout * cin * 27 + co] = s;
-    else if (ci < cin) grad[(co * cin + ci) * 27 + t] = s;
+    if (co >= cout || (t < 27 && ci >= cin)) return;
+    const int i = a.off[l] + (t == 27 ? cout * cin * 27 + co : (co * cin + ci) * 27 + t);
+    a.grad[i] = s;
+    const float mi = a.beta1 * a.m[i] + (1.f - a.beta1) * s;
+    const float vi = a.beta2 * a.v[i] + (1.f - a.beta2) * s * s;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    a.theta[i] = a.theta[i] - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + a.eps);
 }
 
 // Loss: r = y - log(gamma + 0.01) at nodes with gamma >= 0; output gradient
-// bf16(scale * r) into channel 0 of a 16-channel tensor (other channels 0), and one
+// bf16(2 r / count), count the labelled nodes of the batch (a device count: no read-back
+// between the forward and the backward pass), into channel 0 of a 16-channel tensor (other channels 0), and one
 // partial sum of r^2 per workgroup.
 __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ y, const float* __restrict__ gamma,
-                                              int64_t n, float scale, uint16_t* __restrict__ gout,
-                                              float* __restrict__ loss_part) {
+                                              int64_t n, const unsigned long long* __restrict__ count,
+                                              uint16_t* __restrict__ gout, float* __restrict__ loss_part) {
     __shared__ float red[256];
+    const unsigned long long cnt = *count;
+    const float scale = (float)(2.0 / (double)(cnt > 0 ? cnt : 1));
     float s = 0.f;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
         const float gm = gamma[i];
@@ -772,20 +786,6 @@ __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ y, const
     if (threadIdx.x == 0) loss_part[blockIdx.x] = red[0];
 }
 
-// Adam with bias correction (c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t)).
-__global__ __launch_bounds__(256) void k_adam(float* __restrict__ theta, float* __restrict__ m,
-                                              float* __restrict__ v, const float* __restrict__ grad, int n, float lr,
-                                              float beta1, float beta2, float eps, float c1, float c2) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = grad[i];
-    const float mi = beta1 * m[i] + (1.f - beta1) * gi;
-    const float vi = beta2 * v[i] + (1.f - beta2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    theta[i] = theta[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-}
-
 // Fragments of one layer from the FP32 parameters.  Lane l of chunk c holds row l % 16
 // and k = 32 c + 8 (l / 16) + e, e = 0..7.
 //   forward, 2 channels : row = co; k = 32 c + 8 g + 2 q + ci, tap l1_tap(c, g, q)
@@ -794,10 +794,18 @@ __global__ __launch_bounds__(256) void k_adam(float* __restrict__ theta, float* 
 //             (tap 26 - tap', bwd-data)
 //   bwd == 2, the last layer (16 -> 1) by shifts: row = s = 3 dz + dy (rows 9..15 zero);
 //             chunk 0: k = 16 dx + ci, dx = 0, 1; chunk 1: k = ci, dx = 2 (k 16..31 zero)
-__global__ __launch_bounds__(64) void k_pack(const float* __restrict__ w, int cin, int cout, int bwd, int nch,
-                                             uint16_t* __restrict__ frag) {
-    const int c = blockIdx.x, lane = threadIdx.x;
+// One launch packs every array of the network (blockIdx.y = k: forward of layer k for k < 4,
+// else backward of layer k - 3), each CNN_FRAG_ELEMS apart.
+__global__ __launch_bounds__(64) void k_pack(const float* __restrict__ theta, PackOffsets off,
+                                             uint16_t* __restrict__ frags) {
+    const int c = blockIdx.x, lane = threadIdx.x, kind = blockIdx.y;
+    const int l = kind < CNN_LAYERS ? kind : kind - 3;
+    const int cin = l == 0 ? CNN_CIN[0] : CNN_CIN[1], cout = l == CNN_LAYERS - 1 ? CNN_COUT[3] : CNN_COUT[0];
+    const int bwd = kind >= CNN_LAYERS ? 1 : (l == CNN_LAYERS - 1 ? 2 : 0);
+    const int nch = bwd == 2 ? 2 : (bwd ? 14 : (cin == 16 ? 14 : 2));
     if (c >= nch) return;
+    const float* w = theta + off.w[l];
+    uint16_t* frag = frags + (int64_t)kind * CNN_FRAG_ELEMS;
     const int row = lane & 15, g = lane >> 4;
     uint16_t h[8];
 #pragma unroll
@@ -1387,30 +1395,23 @@ hipError_t launch_conv_bwdw(int cin, const uint16_t* x, const int i[3], int64_t 
     return hipGetLastError();
 }
 
-hipError_t launch_grad_reduce(const float* partial, int nblocks, int cin, int cout, float* grad, hipStream_t s) {
-    hipLaunchKernelGGL(k_grad_reduce, dim3((CNN_PARTIAL_STRIDE + 63) / 64), dim3(64 * GR_WAVES), 0, s, partial, nblocks,
-                       cin, cout, grad);
+hipError_t launch_grad_reduce(const GradArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_grad_reduce, dim3((CNN_PARTIAL_STRIDE + 63) / 64, CNN_LAYERS), dim3(64 * GR_WAVES), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_loss(const float* y, const float* gamma, int64_t n, float scale, uint16_t* gout, float* loss_part,
-                       int nblocks, hipStream_t s) {
-    hipLaunchKernelGGL(k_loss, dim3(nblocks), dim3(256), 0, s, y, gamma, n, scale, gout, loss_part);
+hipError_t launch_loss(const float* y, const float* gamma, int64_t n, const unsigned long long* count, uint16_t* gout,
+                       float* loss_part, int nblocks, hipStream_t s) {
+    hipLaunchKernelGGL(k_loss, dim3(nblocks), dim3(256), 0, s, y, gamma, n, count, gout, loss_part);
     return hipGetLastError();
 }
 
 int loss_blocks(int64_t n) { return grid_for(n, 1024); }
 
-hipError_t launch_adam(float* theta, float* m, float* v, const float* grad, int n, float lr, float beta1,
-                       float beta2, float eps, float c1, float c2, hipStream_t s) {
-    hipLaunchKernelGGL(k_adam, dim3((n + 255) / 256), dim3(256), 0, s, theta, m, v, grad, n, lr, beta1, beta2, eps,
-                       c1, c2);
-    return hipGetLastError();
-}
-
-hipError_t launch_pack(const float* w, int cin, int cout, int bwd, uint16_t* frag, hipStream_t s) {
-    const int nch = bwd == 2 ? 2 : (bwd ? 14 : (cin == 16 ? 14 : 2));
-    hipLaunchKernelGGL(k_pack, dim3(nch), dim3(64), 0, s, w, cin, cout, bwd, nch, frag);
+hipError_t launch_pack(const float* theta, uint16_t* frags, hipStream_t s) {
+    PackOffsets off;
+    for (int l = 0; l < CNN_LAYERS; ++l) off.w[l] = CNN_OFF[l];
+    hipLaunchKernelGGL(k_pack, dim3(14, CNN_FRAG_ARRAYS), dim3(64), 0, s, theta, off, frags);
     return hipGetLastError();
 }
 

@@ -27,17 +27,7 @@ gammax_status_t mfail(gammax_model* m, gammax_status_t st, const std::string& wh
                          std::string(#call) + ": " + hipGetErrorString(e_));                       \
     } while (0)
 
-hipError_t pack_all(gammax_model* m, hipStream_t s) {
-    hipError_t e;
-    for (int l = 0; l < CNN_LAYERS; ++l)
-        if ((e = launch_pack(m->theta + CNN_OFF[l], CNN_CIN[l], CNN_COUT[l], l == 3 ? 2 : 0, frag_fwd(m, l), s)) !=
-            hipSuccess)
-            return e;
-    for (int l = 1; l < CNN_LAYERS; ++l)
-        if ((e = launch_pack(m->theta + CNN_OFF[l], CNN_CIN[l], CNN_COUT[l], 1, frag_bwd(m, l), s)) != hipSuccess)
-            return e;
-    return hipSuccess;
-}
+hipError_t pack_all(gammax_model* m, hipStream_t s) { return launch_pack(m->theta, m->frag, s); }
 
 constexpr int64_t kAlign = 256;
 int64_t align_up(int64_t b) { return (b + kAlign - 1) / kAlign * kAlign; }
@@ -94,9 +84,9 @@ namespace {
 // Training workspace layout for nvol volumes of output shape o.
 struct TrainWs {
     uint16_t *a1, *a2, *a3, *g4, *g3, *g2, *g1;
-    float *y, *partial, *loss_part;
+    float *y, *partial[CNN_LAYERS], *loss_part;
     int64_t bytes;
-    int nb_partial, nb_loss;
+    int nb_partial[CNN_LAYERS], nb_loss;
 };
 
 TrainWs train_layout(unsigned char* base, int nvol, const int o[3]) {
@@ -119,8 +109,11 @@ TrainWs train_layout(unsigned char* base, int nvol, const int o[3]) {
     w.g3 = (uint16_t*)take(nvol * vol_of(s3) * 32);
     w.g2 = (uint16_t*)take(nvol * vol_of(s2) * 32);
     w.g1 = (uint16_t*)take(nvol * vol_of(s1) * 32);
-    w.nb_partial = bwdw_blocks(s1, nvol);   // the largest bwd-weight grid (layer 0)
-    w.partial = (float*)take((int64_t)w.nb_partial * CNN_PARTIAL_STRIDE * 4);
+    const int* gs[CNN_LAYERS] = {s1, s2, s3, o};   // output shape of each layer
+    for (int l = 0; l < CNN_LAYERS; ++l) {
+        w.nb_partial[l] = bwdw_blocks(gs[l], nvol);
+        w.partial[l] = (float*)take((int64_t)w.nb_partial[l] * CNN_PARTIAL_STRIDE * 4);
+    }
     w.nb_loss = loss_blocks(nvol * vol_of(o));
     w.loss_part = (float*)take((int64_t)w.nb_loss * 4);
     w.bytes = off;
@@ -146,7 +139,7 @@ gammax_status_t gammax_model_create(int device, const float* params, gammax_mode
     if (hipSetDevice(device) != hipSuccess || hipMalloc((void**)&m->theta, pb) != hipSuccess ||
         hipMalloc((void**)&m->adam_m, pb) != hipSuccess || hipMalloc((void**)&m->adam_v, pb) != hipSuccess ||
         hipMalloc((void**)&m->grad, pb) != hipSuccess ||
-        hipMalloc((void**)&m->frag, sizeof(uint16_t) * CNN_FRAG_ELEMS * 7) != hipSuccess ||
+        hipMalloc((void**)&m->frag, sizeof(uint16_t) * CNN_FRAG_ELEMS * CNN_FRAG_ARRAYS) != hipSuccess ||
         hipMalloc((void**)&m->d_cnt, 3 * sizeof(unsigned long long)) != hipSuccess ||
         hipHostMalloc((void**)&m->h_cnt, 3 * sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess) {
         gammax_model_destroy(m);
@@ -155,7 +148,7 @@ gammax_status_t gammax_model_create(int device, const float* params, gammax_mode
     if (hipMemcpy(m->theta, params, pb, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemset(m->adam_m, 0, pb) != hipSuccess || hipMemset(m->adam_v, 0, pb) != hipSuccess ||
         hipMemset(m->grad, 0, pb) != hipSuccess ||
-        hipMemset(m->frag, 0, sizeof(uint16_t) * CNN_FRAG_ELEMS * 7) != hipSuccess || pack_all(m, nullptr) != hipSuccess ||
+        hipMemset(m->frag, 0, sizeof(uint16_t) * CNN_FRAG_ELEMS * CNN_FRAG_ARRAYS) != hipSuccess || pack_all(m, nullptr) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess) {
         gammax_model_destroy(m);
         return GAMMAX_E_DEVICE;
@@ -325,14 +318,10 @@ gammax_status_t gammax_model_train_step(gammax_model_t* m, int32_t nvol, const i
     act_shape(o, 2, s3);
     const int64_t n_out = nvol * vol_of(o);
 
-    // forward; the count of labelled nodes (gamma >= 0) fixes the loss scale
-    MCHK(m, model_forward(m, feat_dev, nvol, o, w.a1, w.a2, w.a3, w.y, s));
+    // the count of labelled nodes (gamma >= 0) scales the loss; it stays on the device
     MCHK(m, launch_pass_count(gamma_dev, n_out, m->d_cnt, s));
-    MCHK(m, hipMemcpyAsync(m->h_cnt, m->d_cnt, 3 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    MCHK(m, hipStreamSynchronize(s));
-    const unsigned long long cnt = m->h_cnt[0] > 0 ? m->h_cnt[0] : 1;
-    const float scale = (float)(2.0 / (double)cnt);
-    MCHK(m, launch_loss(w.y, gamma_dev, n_out, scale, w.g4, w.loss_part, w.nb_loss, s));
+    MCHK(m, model_forward(m, feat_dev, nvol, o, w.a1, w.a2, w.a3, w.y, s));
+    MCHK(m, launch_loss(w.y, gamma_dev, n_out, m->d_cnt, w.g4, w.loss_part, w.nb_loss, s));
 
     // backward, layer 3 down to layer 0
     const uint16_t* xin[4] = {feat_dev, w.a1, w.a2, w.a3};
@@ -343,9 +332,7 @@ gammax_status_t gammax_model_train_step(gammax_model_t* m, int32_t nvol, const i
     for (int l = CNN_LAYERS - 1; l >= 0; --l) {
         const int cin = CNN_CIN[l];
         const int64_t xs = vol_of(xshape[l]) * cin, gs = vol_of(gshape[l]) * 16;
-        MCHK(m, launch_conv_bwdw(cin, xin[l], xshape[l], xs, gout[l], gshape[l], gs, nvol, w.partial, s));
-        const int nb = bwdw_blocks(gshape[l], nvol);
-        MCHK(m, launch_grad_reduce(w.partial, nb, cin, CNN_COUT[l], m->grad + CNN_OFF[l], s));
+        MCHK(m, launch_conv_bwdw(cin, xin[l], xshape[l], xs, gout[l], gshape[l], gs, nvol, w.partial[l], s));
         if (l > 0) {
             // gradient of the input, times the ReLU derivative of the stored activation
             MCHK(m, launch_conv(16, 2, gout[l], gshape[l], gs, frag_bwd(m, l), nullptr, 16, xin[l], gin[l],
@@ -353,15 +340,30 @@ gammax_status_t gammax_model_train_step(gammax_model_t* m, int32_t nvol, const i
         }
     }
 
-    // Adam on the FP32 master copy, then new bf16 fragments
+    // the gradient and Adam on the FP32 master copy, then new bf16 fragments
     m->step += 1;
-    const double c1 = 1.0 / (1.0 - std::pow((double)hp->beta1, (double)m->step));
-    const double c2 = 1.0 / (1.0 - std::pow((double)hp->beta2, (double)m->step));
-    MCHK(m, launch_adam(m->theta, m->adam_m, m->adam_v, m->grad, CNN_NPARAM, hp->lr, hp->beta1, hp->beta2, hp->eps,
-                        (float)c1, (float)c2, s));
+    GradArgs ga{};
+    for (int l = 0; l < CNN_LAYERS; ++l) {
+        ga.partial[l] = w.partial[l];
+        ga.nblocks[l] = w.nb_partial[l];
+        ga.off[l] = CNN_OFF[l];
+    }
+    ga.grad = m->grad;
+    ga.theta = m->theta;
+    ga.m = m->adam_m;
+    ga.v = m->adam_v;
+    ga.lr = hp->lr;
+    ga.beta1 = hp->beta1;
+    ga.beta2 = hp->beta2;
+    ga.eps = hp->eps;
+    ga.c1 = (float)(1.0 / (1.0 - std::pow((double)hp->beta1, (double)m->step)));
+    ga.c2 = (float)(1.0 / (1.0 - std::pow((double)hp->beta2, (double)m->step)));
+    MCHK(m, launch_grad_reduce(ga, s));
     MCHK(m, pack_all(m, s));
+    MCHK(m, hipMemcpyAsync(m->h_cnt, m->d_cnt, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
     MCHK(m, hipMemcpyAsync(m->h_loss, w.loss_part, sizeof(float) * w.nb_loss, hipMemcpyDeviceToHost, s));
     MCHK(m, hipStreamSynchronize(s));
+    const unsigned long long cnt = m->h_cnt[0] > 0 ? m->h_cnt[0] : 1;
     if (loss) {
         double acc = 0.0;
         for (int b = 0; b < w.nb_loss; ++b) acc += m->h_loss[b];
