@@ -110,6 +110,8 @@ struct gammax_ctx {
     int64_t cnn_ws_cap = 0;
     float* yhat = nullptr;          // log(gamma_hat + 0.01) per grid node
     int64_t yhat_cap = 0;
+    float2* range = nullptr;        // range of every cell's corner doses (long tails)
+    int64_t range_cap = 0;
     float* ycoarse = nullptr;       // the network's output on the pooled coarse grid (cnn_pool 2)
     int64_t ycoarse_cap = 0;
     // gammax_map_grids: listed nodes, their first bounds, the guard list (each n_ref words)
@@ -127,6 +129,7 @@ struct gammax_ctx {
     struct ManyState* many = nullptr;     // gammax_map_many state (created on first use)
     uint64_t tail_hint = 0;         // tail length of the last map (picks the tail sort variant)
     uint32_t long_rows = 0;         // longest tail walk of the last map, if long (widens the tail groups)
+    uint64_t tail_cells = 0;        // cells its tail visited (whether cell ranges pay)
     // maps queued by gammax_map_async and not yet collected
     AsyncSlot* slots = nullptr;     // GAMMAX_ASYNC_SLOTS entries, created on first use
     uint64_t next_ticket = 1;
@@ -484,6 +487,17 @@ bool short_tail(const gammax_ctx* c, const gammax_options_t& opt) {
     return opt.tail_lanes == 0 && c->tail_hint <= (uint64_t)SMALL_SORT_CAP;
 }
 
+// Whether the tail walk of an n-node map should write every cell's dose range first.  That
+// costs about 12 bytes of traffic per node of the grid (36 us at 192x256x256) and saves eight
+// gathers per visited cell, so it pays once the tail visits more than about twice as many
+// cells as the grid has, judged by the context's last map (1.2 visits per node: 227 us with,
+// 226 us without; 1.8: 356 against 387 us; 43 at a 5 % dose error:
+// 2.8 -> 2.2 ms for the map of a 160x200x200 pair).  The result does
+// not depend on it.  The walk forms the ranges' byte offsets in 32 bits.
+bool want_ranges(const gammax_ctx* c, int64_t n) {
+    return n < ((int64_t)1 << 29) && c->tail_cells >= 2 * (uint64_t)n;
+}
+
 // Least lanes per node of the automatic tail layout: wide enough that the longest walk of
 // the context's last map (if it was long) takes about 32 dependent steps.
 int tail_min_lanes(const gammax_ctx* c) {
@@ -614,6 +628,8 @@ SearchArgs make_search_args(const gammax_problem_t* p, const gammax_options_t& o
         sa.ny = (int)p->shape[0];
         sa.nx = (int)p->shape[1];
     }
+    sa.div_nx = make_fast_div((uint32_t)sa.nx);
+    sa.div_ny = make_fast_div((uint32_t)sa.ny);
     sa.dd = (float)p->dd;
     sa.dd64 = p->dd;
     sa.local = p->norm == GAMMAX_LOCAL ? 1 : 0;
@@ -683,9 +699,11 @@ gammax_status_t enqueue_search(gammax_ctx* c, const CallSetup& cs, uint32_t m_bo
                                hipStream_t s, bool timing, bool skip_zero = false) {
     const gammax_problem_t* p = cs.p;
     const gammax_options_t& opt = *cs.opt;
-    const SearchArgs sa = make_search_args(p, opt, cs.ref, cs.ev, cs.gamma, c->d_sc, c->tab,
-                                           c->tab_valid ? (int)c->tab_len : 0, c->tab_valid ? c->tab_k1 : INFINITY,
+    SearchArgs sa = make_search_args(p, opt, cs.ref, cs.ev, cs.gamma, c->d_sc, c->tab,
+                                     c->tab_valid ? (int)c->tab_len : 0, c->tab_valid ? c->tab_k1 : INFINITY,
                                            r2_cap, c->work, c->work_cap, c->sums, c->yhat);
+    sa.range = want_ranges(c, cs.n) && c->range_cap >= cs.n ? c->range : nullptr;
+    sa.range_min = (uint32_t)(cs.n / 64);
     const bool learned = uses_model(p, &opt);
     SearchPlan plan{};
     plan.ndim = p->ndim;
@@ -777,7 +795,7 @@ GraphKey key_of(gammax_ctx* c, const CallSetup& cs) {
     return k;
 }
 
-void fill_result_from(gammax_ctx* c, const Scalars& h, gammax_result_t* res, bool timing, float ms_table,
+void fill_result_from(gammax_ctx* c, int ndim, const Scalars& h, gammax_result_t* res, bool timing, float ms_table,
                       bool cnn) {
     const float r2 = u2f(h.r2_bits);
     res->n_evaluated = h.n_masked;
@@ -809,10 +827,13 @@ void fill_result_from(gammax_ctx* c, const Scalars& h, gammax_result_t* res, boo
     // widens its tail groups if this one had long walks
     c->tail_hint = h.sort_overflow ? (uint64_t)SMALL_SORT_CAP + 1 : h.n_tail;
     c->long_rows = h.long_rows;
+    // cells visited past the key-0 cells (2^d per node, fewer at the grid's faces), at least
+    const uint64_t key0 = (uint64_t)h.n_masked << ndim;
+    c->tail_cells = h.n_cells > key0 ? h.n_cells - key0 : 0;
 }
 
-void fill_result(gammax_ctx* c, gammax_result_t* res, bool timing, float ms_table, bool cnn) {
-    fill_result_from(c, *c->h_sc, res, timing, ms_table, cnn);
+void fill_result(gammax_ctx* c, int ndim, gammax_result_t* res, bool timing, float ms_table, bool cnn) {
+    fill_result_from(c, ndim, *c->h_sc, res, timing, ms_table, cnn);
 }
 
 gammax_status_t scalar_errors(gammax_ctx* c, const Scalars& h, bool local) {
@@ -872,6 +893,7 @@ gammax_status_t map_setup(gammax_ctx* c, const gammax_problem_t* p, const gammax
     if ((st = grow(c, &c->hist, &c->hist_cap, sort_hist_words(*n))) != GAMMAX_OK) return st;
     if ((st = grow(c, &c->sums, &c->sums_cap, search_sums_needed((uint32_t)*n))) != GAMMAX_OK) return st;
     if (opt->timing && (st = ensure_events(c)) != GAMMAX_OK) return st;
+    if (want_ranges(c, *n) && (st = grow(c, &c->range, &c->range_cap, *n)) != GAMMAX_OK) return st;
     *learned = uses_model(p, opt);
     if (*learned && (st = grow(c, &c->yhat, &c->yhat_cap, *n)) != GAMMAX_OK) return st;
     if (*learned && opt->cnn_pool == 2 && (st = grow_pooled(c, p)) != GAMMAX_OK) return st;
@@ -951,7 +973,7 @@ gammax_status_t gammax_ctx_destroy(gammax_ctx_t* c) {
     (void)hipDeviceSynchronize();
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     void* dev[] = {c->d_sc, c->d_cnt, c->d_count, c->d_seq, c->work, c->blockcnt, c->part, c->hist,
-                   c->sums, c->tab, c->tb, c->tb_hist, c->cnn_ws, c->yhat, c->ycoarse, c->g_work, c->g_tab,
+                   c->sums, c->tab, c->tb, c->tb_hist, c->cnn_ws, c->yhat, c->range, c->ycoarse, c->g_work, c->g_tab,
                    c->g_2d};
     for (void* p : dev)
         if (p) (void)hipFree(p);
@@ -996,7 +1018,7 @@ gammax_status_t gammax_map(gammax_ctx_t* c, const gammax_problem_t* p, const gam
         *c->h_sc = c->h_ring[r];
         if ((st = device_errors(c, local)) != GAMMAX_OK) return st;
         if (!(c->h_sc->flags & FLAG_TABLE_SHORT)) {
-            fill_result(c, res, timing, 0.0f, learned);
+            fill_result(c, p->ndim, res, timing, 0.0f, learned);
             return GAMMAX_OK;
         }
         // the radius outgrew the cached table: build a larger one below and run again
@@ -1039,7 +1061,7 @@ gammax_status_t gammax_map(gammax_ctx_t* c, const gammax_problem_t* p, const gam
         HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
     }
-    fill_result(c, res, timing, ms_table, learned);
+    fill_result(c, p->ndim, res, timing, ms_table, learned);
     return GAMMAX_OK;
 }
 
@@ -1119,7 +1141,7 @@ gammax_status_t gammax_map_wait(gammax_ctx_t* c, uint64_t ticket, gammax_result_
         return gammax_map(c, &sl.p, &sl.o, sl.ref, sl.eval, sl.gamma, res, sl.stream);
     }
     std::memset(res, 0, sizeof(*res));
-    fill_result_from(c, h, res, false, 0.0f, sl.learned);
+    fill_result_from(c, sl.p.ndim, h, res, false, 0.0f, sl.learned);
     return GAMMAX_OK;
 }
 
@@ -2049,7 +2071,7 @@ gammax_status_t gammax_batch(gammax_ctx_t* c, int32_t n, const gammax_problem_t*
             if ((st = gammax_map(sub, &probs[i], &P.opt[i], refs[i], evals[i], gammas[i], &r, s)) != GAMMAX_OK)
                 return fail(c, st, "pair " + std::to_string(i) + ": " + sub->err);
         } else {
-            fill_result_from(sub, h, &r, false, 0.0f, learned[i] != 0);
+            fill_result_from(sub, probs[i].ndim, h, &r, false, 0.0f, learned[i] != 0);
         }
         const unsigned long long t = b->h_done[i];
         r.ms_done = (t > t0 && b->clock_khz > 0) ? (float)((double)(t - t0) / b->clock_khz) : 0.0f;

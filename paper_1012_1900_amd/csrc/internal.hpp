@@ -175,6 +175,18 @@ void table_row_host(int ndim, const double s[3], int az, int ay, int ax, TabEntr
 
 // ---- search ------------------------------------------------------------------------------
 
+// Division of n < 2^31 by a fixed d >= 2 as a multiply and a shift: mul = floor(2^(31 + s) / d)
+// + 1 with s = ceil(log2 d), quotient = high word of n mul, shifted right by s - 1.  The excess
+// e = mul d - 2^(31 + s) is at most d <= 2^s, so n e < 2^(31 + s) and the quotient is exact.
+struct FastDiv {
+    uint32_t mul, shift;
+};
+inline FastDiv make_fast_div(uint32_t d) {
+    uint32_t s = 1;
+    while (((uint64_t)1 << s) < d) ++s;
+    return FastDiv{(uint32_t)(((uint64_t)1 << (31 + s)) / d + 1), s - 1};
+}
+
 struct SearchArgs {
     const float* ref;
     const float* ev;
@@ -183,6 +195,7 @@ struct SearchArgs {
     const TabEntry* tab;
     int tab_len;
     int nx, ny, nz;          // nz = 1 in 2D
+    FastDiv div_nx, div_ny;
     float dd;                // fl32(DD); local: dD = DD * D_r
     double dd64;             // DD in double for the FP64 paths
     int local;
@@ -195,6 +208,8 @@ struct SearchArgs {
     float r2_cap;            // the table holds every cell with key^2 < r2_cap
     int tail_key;            // key of the tail sort: 0 = gamma0^2 (DD sort), 1 = bound after the
                              // key-0 cells, 2 = predicted gamma (learned ordering)
+    float2* range;           // range of every cell's corner doses (workspace), or null
+    uint32_t range_min;      // tails of at least this many nodes fill and use it
     const float* yhat;       // learned radius: log(gamma_hat + 0.01) per tail item, or null
     float spec_factor;       // the speculative walk stops at key >= spec_factor * gamma_hat
     // work lists

@@ -636,6 +636,9 @@ __device__ __forceinline__ uint32_t block_append(bool want, uint32_t* counter) {
     return off + (uint32_t)__popcll(bal & lt);
 }
 
+// n / d for n < 2^31 (the host prepares the multiplier; see make_fast_div).
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv& d) { return __umulhi(n, d.mul) >> d.shift; }
+
 // Finished node: write gamma, update the per-lane counts.
 __device__ __forceinline__ void finish_node(const SearchArgs& a, int node, float F, uint32_t& npass,
                                             uint32_t& nborder, uint32_t& gm) {
@@ -1322,6 +1325,484 @@ __global__ __launch_bounds__(SEARCH_THREADS) __attribute__((amdgpu_waves_per_eu(
     tail_group_body<DIM, MODE>(a, tab, order, count, first, g_req, spec, sums, blockIdx.x, gridDim.x);
 }
 
+// Pass B for long tails (plain radius, automatic layout).  The walk of a node is split into a
+// cheap scan and the projections:
+//   scan  a group of 8 lanes tests 32 rows of its node per step (4 per lane, their loads in
+//         flight together); a row whose cell can still lower F, by the dose bound, goes to
+//         the wave's queue in LDS;
+//   eval  when 64 cells are queued, whichever nodes they belong to, the wave projects them, one
+//         per lane, and each takes its node's F down with an LDS minimum.  A queued cell whose
+//         bound F has passed meanwhile is dropped.
+// A group that finishes a node takes its next one without waiting for the other groups, and
+// past TQ_LONG rows a node is scanned by the whole wave (its walk would outlast the others').
+//
+// Why: a projection costs about ten times a test.  A tail node visits about 30 cells (158 at a
+// 5 % dose error) of which 11 (23) can lower F, and walking 8 rows of a node at a time
+// projected all 64 of the wave's whenever one could.  Measured, walking 8 rows at a time against
+// this: 482535 nodes at 192x256x256 410 -> 227 us; 349353 nodes under local normalisation
+// (walks up to 1440 rows) 407 -> 190 us; 1.25 M nodes at 160x200x200 with a 5 % dose error
+// 4.3 -> 2.0 ms.  Bound by VALU issue (80 % of it: 191 instructions of a wave per node, of
+// which the 11 projections are 74).
+//
+// A projection's or test's arithmetic is that of tail_group_body, the minimum does not depend
+// on its order and a dropped or untested cell cannot lower F, so F has the same bits.  The
+// sequential walk visits exactly the rows whose key is below the final F (every row up to the
+// one that gives F has a smaller key), so the visited cells and the ill-conditioned
+// tetrahedra are judged by the final F: which nodes share a wave changes no count.
+//
+// The test needs the range of a cell's corner doses.  For a tail worth it (range_min nodes),
+// k_cell_range has written every cell's range beforehand: one 8-byte load per row instead of
+// eight gathers.
+constexpr int TQ_LANES = 8, TQ_ROWS = 4, TQ_STEP = TQ_LANES * TQ_ROWS;
+constexpr int TQ_GROUPS = SEARCH_THREADS / TQ_LANES;   // of a workgroup
+constexpr int TQ_LONG = 256;   // rows after which a walk goes on in steps of the whole wave
+constexpr int TQ_FEW = 2;      // groups with rows left at which a partial batch is projected
+constexpr int TQ_TAB = 192;    // table rows staged in LDS
+constexpr int TQ_RING = 512;   // queue slots of a wave: 63 left over and a step of 8 groups fit
+static_assert(WAVE - 1 + WAVE * TQ_ROWS <= TQ_RING && (TQ_RING & (TQ_RING - 1)) == 0, "queue ring");
+
+// Sum over the 8 lanes of a group by data-parallel primitives (no LDS round trip): lanes 1
+// and 2 apart within a quad, then the mirrored lane of the group's other quad.
+template <int CTRL>
+__device__ __forceinline__ int dpp8(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false); }
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141;
+__device__ __forceinline__ uint32_t sum8(uint32_t v) {
+    v += (uint32_t)dpp8<DPP_XOR1>((int)v);
+    v += (uint32_t)dpp8<DPP_XOR2>((int)v);
+    return v + (uint32_t)dpp8<DPP_HALF_MIRROR>((int)v);
+}
+
+// Smallest and largest corner dose of a cell.
+template <int DIM>
+__device__ __forceinline__ void corner_range(const float* __restrict__ ev, int b0, int ox, int oy, int oz, float& lo,
+                                             float& hi) {
+    const float v0 = ev[b0], v1 = ev[b0 + ox], v2 = ev[b0 + oy], v3 = ev[b0 + oy + ox];
+    lo = vmin<float>(vmin<float>(v0, v1), vmin<float>(v2, v3));
+    hi = __builtin_fmaxf(__builtin_fmaxf(v0, v1), __builtin_fmaxf(v2, v3));
+    if constexpr (DIM == 3) {
+        const float v4 = ev[b0 + oz], v5 = ev[b0 + oz + ox], v6 = ev[b0 + oz + oy], v7 = ev[b0 + oz + oy + ox];
+        lo = vmin<float>(lo, vmin<float>(vmin<float>(v4, v5), vmin<float>(v6, v7)));
+        hi = __builtin_fmaxf(hi, __builtin_fmaxf(__builtin_fmaxf(v4, v5), __builtin_fmaxf(v6, v7)));
+    }
+}
+
+// Range of the corner doses of every cell (index of its lower corner; corners past the grid
+// count as the last node, as in the walk).  A thread takes one column of RANGE_Z planes and
+// carries the range of a plane's four corners to the next cell.
+constexpr int RANGE_Z = 8;
+__global__ __launch_bounds__(SEARCH_THREADS) void k_cell_range(const float* __restrict__ ev, int nx, int ny, int nz,
+                                                               const uint32_t* __restrict__ count, uint32_t least,
+                                                               float2* __restrict__ range) {
+    if (*count < least) return;
+    const int64_t sxy = (int64_t)nx * ny;
+    const int64_t c = (int64_t)blockIdx.x * SEARCH_THREADS + threadIdx.x;
+    if (c >= sxy) return;
+    const int x = (int)(c % nx), y = (int)(c / nx);
+    const int ox = x + 1 < nx ? 1 : 0, oy = y + 1 < ny ? nx : 0;
+    const int z0 = blockIdx.y * RANGE_Z;
+    float v[RANGE_Z + 1][4];
+#pragma unroll
+    for (int k = 0; k <= RANGE_Z; ++k) {
+        const int zz = z0 + k < nz ? z0 + k : nz - 1;
+        const float* p = ev + zz * sxy + c;
+        v[k][0] = p[0];
+        v[k][1] = p[ox];
+        v[k][2] = p[oy];
+        v[k][3] = p[oy + ox];
+    }
+    float lo[RANGE_Z + 1], hi[RANGE_Z + 1];
+#pragma unroll
+    for (int k = 0; k <= RANGE_Z; ++k) {
+        lo[k] = vmin<float>(vmin<float>(v[k][0], v[k][1]), vmin<float>(v[k][2], v[k][3]));
+        hi[k] = __builtin_fmaxf(__builtin_fmaxf(v[k][0], v[k][1]), __builtin_fmaxf(v[k][2], v[k][3]));
+    }
+#pragma unroll
+    for (int k = 0; k < RANGE_Z; ++k)
+        if (z0 + k < nz)
+            range[(z0 + k) * sxy + c] = make_float2(vmin<float>(lo[k], lo[k + 1]), __builtin_fmaxf(hi[k], hi[k + 1]));
+}
+
+// The node of a group, read by the group's scan and by the lanes that project its cells.
+struct alignas(16) TqNode {
+    int x, y, z, node;
+    float dr, inv_dd;
+    uint32_t f;      // F (non-negative float bits: an unsigned minimum is the float minimum)
+    uint32_t inner;  // every cell with key below F lies inside the grid, whole
+};
+
+template <int DIM, int MODE>
+__device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEntry* __restrict__ tab,
+                                                const uint32_t* __restrict__ order, uint32_t M, int first,
+                                                BlockSums* sums, uint32_t vb, uint32_t vgrid) {
+    constexpr int NV = DIM == 3 ? 8 : 4;
+    __shared__ TqNode s_node[TQ_GROUPS];
+    __shared__ uint2 s_queue[SEARCH_THREADS / WAVE][TQ_RING];   // row | group of the wave << 28, bound
+    __shared__ TabEntry s_tab[TQ_TAB];
+    __shared__ uint2 s_head[TQ_TAB];                            // key^2, offset in nodes
+    const int lane = threadIdx.x & (WAVE - 1), gl = lane & (TQ_LANES - 1), gsh = lane & ~(TQ_LANES - 1);
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    uint2* queue = s_queue[threadIdx.x / WAVE];
+    TqNode* wnode = s_node + (threadIdx.x / WAVE) * (WAVE / TQ_LANES);
+    TqNode& self = wnode[lane / TQ_LANES];
+    const int nx = a.nx, ny = a.ny, nz = a.nz, sxy = nx * ny;
+    const float inv_dd_g = a.sc->inv_dd;
+    const InvS2<float> is = inv_s2_of(a);
+    const bool ranges = a.range != nullptr && M >= a.range_min;   // (N < 2^29: byte offsets fit 32 bits)
+    // a cell whose corner differences span less than this holds no ill-conditioned
+    // tetrahedron: Den <= 1 + span^2 (1/sx^2 + 1/sy^2 + 1/sz^2), with a margin for rounding
+    const float ill_span2 = (a.den_guard * 0.999f - 1.0f) / ((is.x + is.y) + is.z);
+    uint32_t cells = 0, gm = 0, npass = 0, nborder = 0, long_rows = 0;
+    GuardCtx gc{};
+    uint32_t dummy_fp64 = 0;
+    bool dummy_ill = false;
+
+    // the first rows of the walk, which every node visits, in LDS
+    const int tab_len = a.tab_len - first, tab_lds = min(tab_len, TQ_TAB);
+    tab += first;
+    for (int u = threadIdx.x; u < tab_lds * 4; u += SEARCH_THREADS)
+        reinterpret_cast<uint4*>(s_tab)[u] = reinterpret_cast<const uint4*>(tab)[u];
+    // (a group that never gets a node still reads one in the steps of the others: node 0)
+    if (gl == 0) self = TqNode{};
+    for (int u = threadIdx.x; u < tab_lds; u += SEARCH_THREADS) {
+        const TabEntry& e = tab[u];
+        s_head[u] = make_uint2(f2u(e.key2), (uint32_t)((e.az * ny + e.ay) * nx + e.ax));
+    }
+    __syncthreads();
+    // key^2 (infinite past the table) and offset of row n
+    auto row_head = [&](int n) -> int4 {
+        int4 e = make_int4(0x7F800000, 0, 0, 0);
+        if (n < tab_lds) e = *reinterpret_cast<const int4*>(&s_tab[n]);
+        else if (n < tab_len) e = *reinterpret_cast<const int4*>(&tab[n]);
+        return e;
+    };
+
+    uint32_t i = vb * TQ_GROUPS + threadIdx.x / TQ_LANES;
+    const uint32_t stride = vgrid * TQ_GROUPS;
+    bool have = false, done = false;
+    int n0 = 0;                           // the node's next row
+    uint32_t q_head = 0, q_tail = 0;      // of the wave's queue (uniform)
+    uint32_t q_last = 0;                  // the node's last queued cell lies before this position
+    uint32_t lane_cells = 0, whole = 0;   // whole cells of this lane's rows; of the last step only
+    float key[TQ_ROWS];                   // the last step's keys
+    float ill_key = Num<float>::inf();    // smallest key of a cell with an ill-conditioned tetrahedron
+#pragma unroll
+    for (int k = 0; k < TQ_ROWS; ++k) key[k] = 0.0f;
+    // the group's next node, loaded while the current one is walked: its dose one iteration
+    // after its index, so that no load waits for another
+    int p_node = 0;
+    float p_f = 0.0f, p_dr = 0.0f;
+    bool p_have = i < M, p_fresh = true;
+    if (p_have) {
+        const uint32_t item = order ? order[i] : i;
+        p_node = (int)a.tail_node[item];
+        p_f = u2f(a.tail_f[item]);
+    }
+
+    // One scan step.  KIND 0: each group its own node's rows, all in LDS and every cell inside
+    // the grid; 1: the same without those conditions; 2: the whole wave the rows of group wg's
+    // node (KIND 0, 1: wg is the lane's own group).  row0: this lane's first row.
+    auto scan_step = [&](auto kind, int wg, int row0) {
+        constexpr int KIND = decltype(kind)::value;
+        constexpr int RSTEP = KIND == 2 ? WAVE : TQ_LANES;
+        const bool scan = KIND == 2 || (have && !done), mine = KIND == 2 ? lane / TQ_LANES == wg : scan;
+        const TqNode nd = wnode[wg];
+        const float F = u2f(nd.f), Fm = F + F * 0x1p-8f;
+        bool past = false;   // a row of the step at or past F (or past the table): the rows end here
+        if (mine) {
+            lane_cells += __popc(whole);   // the step before held no row past F
+            whole = 0u;
+        }
+        float kk[TQ_ROWS], lo[TQ_ROWS], hi[TQ_ROWS];   // keys, range of each row's corner doses
+        int b0[TQ_ROWS];
+        uint32_t work = 0u, full = 0u;
+#pragma unroll
+        for (int k = 0; k < TQ_ROWS; ++k) {
+            kk[k] = lo[k] = hi[k] = 0.0f;
+            b0[k] = nd.node;
+            if constexpr (KIND == 0) {
+                // (a lane that does not scan reads row 0, whose cell exists for its node)
+                const uint2 e = s_head[scan ? row0 + k * RSTEP : 0];
+                kk[k] = u2f(e.x);
+                const bool in = scan && kk[k] < F;
+                past = past || !in;
+                work |= in ? 1u << k : 0u;
+                b0[k] += in ? (int)e.y : 0;
+            } else if (scan) {
+                const int4 e = row_head(row0 + k * RSTEP);
+                kk[k] = __builtin_bit_cast(float, e.x);
+                const int qx = nd.x + e.y, qy = nd.y + e.z, qz = nd.z + e.w;
+                const bool in = (unsigned)qx < (unsigned)nx && (unsigned)qy < (unsigned)ny &&
+                                (DIM == 2 || (unsigned)qz < (unsigned)nz) && kk[k] < F;
+                const bool okx = qx + 1 < nx, oky = qy + 1 < ny, okz = DIM == 2 || qz + 1 < nz;
+                past = past || !(kk[k] < F);
+                if (in) {
+                    work |= 1u << k;
+                    full |= okx && oky && okz ? (1u << k) : 0u;
+                    b0[k] = (DIM == 3 ? qz * sxy : 0) + qy * nx + qx;
+                    if (!ranges)
+                        corner_range<DIM>(a.ev, b0[k], okx ? 1 : 0, oky ? nx : 0, (DIM == 3 && okz) ? sxy : 0, lo[k], hi[k]);
+                }
+            }
+        }
+        if constexpr (KIND == 0) full = work;
+        if (ranges) {
+#pragma unroll
+            for (int k = 0; k < TQ_ROWS; ++k) {
+                // (a row without work reads its node's own cell; byte offsets fit 32 bits)
+                const float2 r = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(a.range) + (uint32_t)b0[k] * 8u);
+                lo[k] = r.x;
+                hi[k] = r.y;
+            }
+        } else if constexpr (KIND == 0) {
+#pragma unroll
+            for (int k = 0; k < TQ_ROWS; ++k)
+                if ((work >> k) & 1u) corner_range<DIM>(a.ev, b0[k], 1, nx, DIM == 3 ? sxy : 0, lo[k], hi[k]);
+        }
+        const uint32_t before = q_tail;
+        float bad_key = Num<float>::inf();
+        uint32_t wide_cells = 0u;
+        bool suspect = false;   // a whole cell whose corners span enough for an ill-conditioned tetrahedron
+#pragma unroll
+        for (int k = 0; k < TQ_ROWS; ++k) {
+            // the normalisation is monotone, so the range of the normalised corners is the
+            // normalised range, bit for bit
+            const float glo = dose_norm<float>(lo[k], nd.dr, nd.inv_dd), ghi = dose_norm<float>(hi[k], nd.dr, nd.inv_dd);
+            const float m = __builtin_fmaxf(__builtin_fmaxf(glo, -ghi), 0.0f);
+            const float lb = fmadd(m, m, kk[k]);
+            const bool need = ((work >> k) & 1u) && lb < Fm;
+            if constexpr (DIM == 3 && MODE == 1) suspect = suspect || !((ghi - glo) * (ghi - glo) < ill_span2);
+            const unsigned long long mask = __ballot(need);
+            if (need)
+                queue[(q_tail + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))) &
+                      (TQ_RING - 1)] = make_uint2((uint32_t)(row0 + k * RSTEP) | ((uint32_t)wg << 28), f2u(lb));
+            q_tail += (uint32_t)__popcll(mask);
+            if constexpr (KIND == 2) wide_cells += (uint32_t)__popcll(__ballot((full >> k) & 1u));
+        }
+        if constexpr (DIM == 3 && MODE == 1) {
+            if (__ballot(suspect && full != 0u) != 0ull) {   // rare
+#pragma nounroll
+                for (int k = 0; k < TQ_ROWS; ++k) {
+                    if (!((full >> k) & 1u)) continue;
+                    const int4 e = row_head(row0 + k * RSTEP);
+                    const int c0 = ((nd.z + e.w) * ny + nd.y + e.z) * nx + nd.x + e.y;
+                    float g[8];
+#pragma unroll
+                    for (int b = 0; b < 8; ++b)
+                        g[b] = dose_norm<float>(a.ev[c0 + (b & 1) + ((b >> 1) & 1) * nx + ((b >> 2) & 1) * sxy], nd.dr,
+                                                nd.inv_dd);
+                    if (tets_ill(g, is, a.den_guard)) bad_key = vmin<float>(bad_key, __builtin_bit_cast(float, e.x));
+                }
+                if (KIND == 2)
+                    for (int o = WAVE / 2; o > 0; o >>= 1) bad_key = vmin<float>(bad_key, __shfl_xor(bad_key, o));
+                if (mine) ill_key = vmin<float>(ill_key, bad_key);
+            }
+        }
+        const unsigned long long pb = __ballot(past);
+        if (mine) {
+            if constexpr (KIND == 2) {
+                lane_cells += gl == 0 ? wide_cells : 0u;
+                n0 += WAVE * TQ_ROWS;
+            } else {
+                whole = full;
+#pragma unroll
+                for (int k = 0; k < TQ_ROWS; ++k) key[k] = kk[k];
+                n0 += TQ_STEP;
+                done = ((pb >> gsh) & ((1ull << TQ_LANES) - 1ull)) != 0ull;
+            }
+            if (q_tail != before) q_last = q_tail;
+        }
+    };
+
+    for (;;) {
+        if (p_fresh) {
+            p_dr = a.ref[p_node];
+            p_fresh = false;
+        }
+        if (!have && p_have) {
+            const uint32_t row = fast_div((uint32_t)p_node, a.div_nx);
+            const int z = DIM == 3 ? (int)fast_div(row, a.div_ny) : 0;
+            if (gl == 0) {
+                const int x = p_node - (int)row * nx, y = (int)row - z * ny;
+                // a cell of key below F starts at most sqrt(F) / s past the node's own cells:
+                // all are whole while sqrt(F) stays below s times the cells left on either side
+                const int cx = min(nx - 2 - x, x - 1), cy = min(ny - 2 - y, y - 1);
+                const int cz = DIM == 3 ? min(nz - 2 - z, z - 1) : cx;
+                const float fx = (float)cx, fy = (float)cy, fz = (float)cz;
+                const float lim = vmin<float>(a.s2x * (fx * fx), vmin<float>(a.s2y * (fy * fy), DIM == 3 ? a.s2z * (fz * fz) : Num<float>::inf()));
+                const bool inner = cx > 0 && cy > 0 && cz > 0 && p_f < lim * 0.999f;
+                self = TqNode{x, y, z, p_node, p_dr, node_inv_dd(p_dr, inv_dd_g, a.dd, a.local), f2u(p_f), inner ? 1u : 0u};
+            }
+            n0 = 0;
+            q_last = q_head;
+            lane_cells = whole = 0u;
+            ill_key = Num<float>::inf();
+            have = true;
+            done = false;
+            i += stride;
+            p_have = i < M;
+            if (p_have) {
+                const uint32_t item = order ? order[i] : i;
+                p_node = (int)a.tail_node[item];
+                p_f = u2f(a.tail_f[item]);
+                p_fresh = true;
+            }
+        }
+        if (__ballot(have) == 0ull) break;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+
+        // scan
+        bool flush = false;
+        if (q_tail - q_head < WAVE && __ballot(have && !done) != 0ull) {
+            // a long walk goes on in steps of 256 rows by the whole wave, while all of them lie
+            // below F with its queued cells projected (the rest of its rows, and its end, again
+            // by the group)
+            bool far = have && !done && n0 >= TQ_LONG;
+            unsigned long long fb = __ballot(far);
+            if (fb != 0ull) {
+                if (far) far = __builtin_bit_cast(float, row_head(n0 + WAVE * TQ_ROWS - 1).x) < u2f(self.f);
+                fb = __ballot(far);
+            }
+            if (fb != 0ull) {
+                const int wg = (__ffsll(fb) - 1) / TQ_LANES, wl = __builtin_amdgcn_readfirstlane(wg * TQ_LANES);
+                flush = (int32_t)(q_head - (uint32_t)__builtin_amdgcn_readlane((int)q_last, wl)) < 0;
+                if (!flush) scan_step(std::integral_constant<int, 2>{}, wg, __builtin_amdgcn_readlane(n0, wl) + lane);
+            } else if (__ballot(have && !done && (self.inner == 0u || n0 + TQ_STEP > tab_lds)) == 0ull) {
+                scan_step(std::integral_constant<int, 0>{}, lane / TQ_LANES, n0 + gl);
+            } else {
+                scan_step(std::integral_constant<int, 1>{}, lane / TQ_LANES, n0 + gl);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+
+        // project: 64 cells, or what is queued once few groups have rows left to scan
+        const uint32_t queued = q_tail - q_head;
+        if (queued >= WAVE || flush || (queued > 0u && __popcll(__ballot(have && !done)) <= TQ_FEW * TQ_LANES)) {
+            const uint32_t take = queued < WAVE ? queued : WAVE;
+            const uint2 it = queue[(q_head + lane) & (TQ_RING - 1)];
+            TqNode* owner = &wnode[(it.x >> 28) & 7u];
+            const TqNode nd = *owner;
+            const float F = u2f(nd.f);
+            const bool proj = (uint32_t)lane < take && u2f(it.y) < F + F * 0x1p-8f;
+            TabEntry e{};
+            if (proj) {
+                const int n = (int)(it.x & 0x0FFFFFFFu);
+                if (n < tab_lds) e = s_tab[n];
+                else e = tab[n];
+            }
+            const int qx = nd.x + e.ax, qy = nd.y + e.ay, qz = nd.z + e.az;
+            const bool okx = qx + 1 < nx, oky = qy + 1 < ny, okz = DIM == 2 || qz + 1 < nz;
+            const bool wave_masked = __ballot(proj && !(okx && oky && okz)) != 0ull;
+            if (proj) {
+                const int b0 = (DIM == 3 ? qz * sxy : 0) + qy * nx + qx;
+                const int ox = okx ? 1 : 0, oy = oky ? nx : 0, oz = (DIM == 3 && okz) ? sxy : 0;
+                float g[NV];
+                g[0] = a.ev[b0];
+                g[1] = a.ev[b0 + ox];
+                g[2] = a.ev[b0 + oy];
+                g[3] = a.ev[b0 + oy + ox];
+                if constexpr (DIM == 3) {
+                    g[4] = a.ev[b0 + oz];
+                    g[5] = a.ev[b0 + oz + ox];
+                    g[6] = a.ev[b0 + oz + oy];
+                    g[7] = a.ev[b0 + oz + oy + ox];
+                }
+#pragma unroll
+                for (int b = 0; b < NV; ++b) g[b] = dose_norm<float>(g[b], nd.dr, nd.inv_dd);
+                const Geo<float> Gm = geo_from_row(e);
+                float c;
+                if constexpr (DIM == 3) {
+                    if (wave_masked)
+                        c = cell3<float, true, 0>(g, Gm, is, okx, oky, okz, a.den_guard, gc, dummy_fp64, dummy_ill);
+                    else
+                        c = cell3<float, false, 0>(g, Gm, is, true, true, true, a.den_guard, gc, dummy_fp64, dummy_ill);
+                } else {
+                    if (wave_masked)
+                        c = cell2<float, true>(g, Gm, is, okx, oky);
+                    else
+                        c = cell2<float, false>(g, Gm, is, true, true);
+                }
+                if (c < F) atomicMin(&owner->f, f2u(c));
+            }
+            q_head += take;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+
+        // finish the nodes whose rows are scanned and whose queued cells are projected
+        const bool fin = have && done && (int32_t)(q_head - q_last) >= 0;
+        if (__ballot(fin) != 0ull) {
+            const TqNode nd = self;
+            const float F = u2f(nd.f);
+            if (fin) {
+#pragma unroll
+                for (int k = 0; k < TQ_ROWS; ++k) lane_cells += ((whole >> k) & 1u) && key[k] < F ? 1u : 0u;
+                // steps before the last whose rows the projections have since put past F (rare)
+                for (int s0 = n0 - TQ_STEP;
+                     s0 > 0 && !(__builtin_bit_cast(float, row_head(s0 - 1).x) < F); s0 -= TQ_STEP) {
+#pragma unroll
+                    for (int k = 0; k < TQ_ROWS; ++k) {
+                        const int4 e = row_head(s0 - TQ_STEP + k * TQ_LANES + gl);
+                        const int qx = nd.x + e.y, qy = nd.y + e.z, qz = nd.z + e.w;
+                        const bool w = qx >= 0 && qx + 1 < nx && qy >= 0 && qy + 1 < ny &&
+                                       (DIM == 2 || (qz >= 0 && qz + 1 < nz));
+                        lane_cells -= w && !(__builtin_bit_cast(float, e.x) < F) ? 1u : 0u;
+                    }
+                }
+            }
+            const uint32_t sum = sum8(lane_cells);
+            bool to_guard = false;
+            if constexpr (MODE == 1)
+                to_guard = ((__ballot(fin && ill_key < F) >> gsh) & ((1ull << TQ_LANES) - 1ull)) != 0ull;
+            if (fin) {
+                if (n0 > (int)LONG_WALK_ROWS && (uint32_t)n0 > long_rows)   // (it has at most n0 rows)
+                    long_rows = max(long_rows, (uint32_t)resume_row(tab, tab_len, 0, F));
+                if (gl == 0 && !to_guard) {
+                    finish_node(a, nd.node, F, npass, nborder, gm);
+                    cells += sum + zero_cells(DIM, nd.x, nd.y, nd.z, nx, ny, nz);
+                }
+                have = false;
+            }
+            if constexpr (MODE == 1) {
+                const bool put = fin && to_guard && gl == 0;
+                const unsigned long long gb = __ballot(put);
+                if (gb != 0ull) {   // rare: one atomic per wave
+                    uint32_t base = 0u;
+                    if (lane == 0) base = atomicAdd(&a.sc->n_guard, (uint32_t)__popcll(gb));
+                    base = (uint32_t)__shfl((int)base, 0);
+                    if (put) a.guard_list[base + (uint32_t)__popcll(gb & lt)] = (uint32_t)nd.node;
+                }
+            }
+        }
+    }
+    if (__ballot(long_rows > LONG_WALK_ROWS) != 0ull) {
+        for (int o = WAVE / 2; o > 0; o >>= 1) long_rows = max(long_rows, (uint32_t)__shfl_xor((int)long_rows, o));
+        if (lane == 0) atomicMax(&a.sc->long_rows, long_rows);
+    }
+    block_sums(sums, vb, npass, nborder, 0u, cells, gm);
+}
+
+// Tails of at least this many nodes take the queued walk: at 13 thousand nodes (24 us against
+// 27) the wide groups of tail_group_body still win, which keep a short tail's latency low; at
+// 23 thousand (60 us against 43-58) they no longer do.
+constexpr uint32_t TQ_MIN_TAIL = 16384;
+
+// The walk of the automatic layout (vb / vgrid: this block and the number of blocks).
+template <int DIM, int MODE>
+__device__ __forceinline__ void tail_auto_body(const SearchArgs& a, const uint32_t* __restrict__ order, bool sorted,
+                                               const uint32_t* __restrict__ count, int first, int g_req, BlockSums* sums,
+                                               uint32_t vb, uint32_t vgrid) {
+    if (*count >= TQ_MIN_TAIL)
+        tail_queue_body<DIM, MODE>(a, a.tab, sorted ? order : nullptr, *count, first, sums, vb, vgrid);
+    else
+        tail_group_body<DIM, MODE>(a, a.tab, order, count, first, g_req, 0, sums, vb, vgrid);
+}
+
+template <int DIM, int MODE>
+__global__ __launch_bounds__(SEARCH_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_tail_auto(
+    SearchArgs a, const uint32_t* __restrict__ order, int sorted, const uint32_t* __restrict__ count, int first, int g_req,
+    BlockSums* sums) {
+    tail_auto_body<DIM, MODE>(a, order, sorted != 0, count, first, g_req, sums, blockIdx.x, gridDim.x);
+}
+
 // One block: sum the per-block partial counts into the scalars, and flag a cell table
 // that does not reach the search radius (the host then rebuilds it and runs again).
 // ADD: add the sums into the scalars (which the prep zeroed) instead of storing them, so
@@ -1433,6 +1914,21 @@ unsigned tail_pass(const SearchArgs& a, const SearchPlan& p, const uint32_t* ord
     const unsigned groups = SEARCH_THREADS / (unsigned)(G > 0 ? G : -G);
     unsigned gb = (p.M + groups - 1) / groups;
     if (gb > kTailBlocks) gb = kTailBlocks;
+    if (G < 0 && spec == 0) {
+        if (a.range) {
+            const unsigned cols = (unsigned)(((int64_t)a.nx * a.ny + SEARCH_THREADS - 1) / SEARCH_THREADS);
+            hipLaunchKernelGGL(k_cell_range, dim3(cols, (unsigned)((a.nz + RANGE_Z - 1) / RANGE_Z)), dim3(SEARCH_THREADS), 0,
+                               s, a.ev, a.nx, a.ny, a.nz, count, a.range_min, a.range);
+        }
+        const int sorted = p.hist != nullptr;
+        if (p.ndim == 3) {
+            if (guarded) hipLaunchKernelGGL((k_tail_auto<3, 1>), dim3(gb), dim3(SEARCH_THREADS), 0, s, a, order, sorted, count, first, G, sums);
+            else hipLaunchKernelGGL((k_tail_auto<3, 0>), dim3(gb), dim3(SEARCH_THREADS), 0, s, a, order, sorted, count, first, G, sums);
+        } else {
+            hipLaunchKernelGGL((k_tail_auto<2, 0>), dim3(gb), dim3(SEARCH_THREADS), 0, s, a, order, sorted, count, first, G, sums);
+        }
+        return gb;
+    }
     tail_group(a, order, count, p.ndim, guarded ? 1 : 0, G, first, gb, spec, sums, s);
     return gb;
 }
@@ -1459,16 +1955,21 @@ __global__ __launch_bounds__(SEARCH_THREADS) __attribute__((amdgpu_waves_per_eu(
     const BatchPair* __restrict__ pairs, const uint2* __restrict__ items) {
     const uint2 w = items[blockIdx.x];
     const BatchPair& P = pairs[w.x];
-    if (P.ndim == 3) {
-        if (P.guarded)
-            tail_group_body<3, 1>(P.sa, P.sa.tab, P.sa.tail_pos, &P.sa.sc->n_tail, P.first, P.g_req, 0, P.sa.sums,
-                                  w.y, (uint32_t)P.tail_blocks);
-        else
-            tail_group_body<3, 0>(P.sa, P.sa.tab, P.sa.tail_pos, &P.sa.sc->n_tail, P.first, P.g_req, 0, P.sa.sums,
-                                  w.y, (uint32_t)P.tail_blocks);
+    const SearchArgs& sa = P.sa;
+    const uint32_t* n = &sa.sc->n_tail;
+    const uint32_t nb = (uint32_t)P.tail_blocks;
+    if (P.g_req < 0) {
+        if (P.ndim == 3) {
+            if (P.guarded) tail_auto_body<3, 1>(sa, sa.tail_pos, false, n, P.first, P.g_req, sa.sums, w.y, nb);
+            else tail_auto_body<3, 0>(sa, sa.tail_pos, false, n, P.first, P.g_req, sa.sums, w.y, nb);
+        } else {
+            tail_auto_body<2, 0>(sa, sa.tail_pos, false, n, P.first, P.g_req, sa.sums, w.y, nb);
+        }
+    } else if (P.ndim == 3) {
+        if (P.guarded) tail_group_body<3, 1>(sa, sa.tab, sa.tail_pos, n, P.first, P.g_req, 0, sa.sums, w.y, nb);
+        else tail_group_body<3, 0>(sa, sa.tab, sa.tail_pos, n, P.first, P.g_req, 0, sa.sums, w.y, nb);
     } else {
-        tail_group_body<2, 0>(P.sa, P.sa.tab, P.sa.tail_pos, &P.sa.sc->n_tail, P.first, P.g_req, 0, P.sa.sums, w.y,
-                              (uint32_t)P.tail_blocks);
+        tail_group_body<2, 0>(sa, sa.tab, sa.tail_pos, n, P.first, P.g_req, 0, sa.sums, w.y, nb);
     }
 }
 
