@@ -489,13 +489,13 @@ bool short_tail(const gammax_ctx* c, const gammax_options_t& opt) {
 
 // Whether the tail walk of an n-node map should write every cell's dose range first.  That
 // costs about 12 bytes of traffic per node of the grid (36 us at 192x256x256) and saves eight
-// gathers per visited cell, so it pays once the tail visits more than about twice as many
+// gathers per cell that the queued walk visits, so it pays once such a tail visits more than about twice as many
 // cells as the grid has, judged by the context's last map (1.2 visits per node: 227 us with,
 // 226 us without; 1.8: 356 against 387 us; 43 at a 5 % dose error:
 // 2.8 -> 2.2 ms for the map of a 160x200x200 pair).  The result does
 // not depend on it.  The walk forms the ranges' byte offsets in 32 bits.
 bool want_ranges(const gammax_ctx* c, int64_t n) {
-    return n < ((int64_t)1 << 29) && c->tail_cells >= 2 * (uint64_t)n;
+    return n < ((int64_t)1 << 29) && c->tail_hint >= QUEUED_TAIL && c->tail_cells >= 2 * (uint64_t)n;
 }
 
 // Least lanes per node of the automatic tail layout: wide enough that the longest walk of
@@ -662,6 +662,7 @@ SearchArgs make_search_args(const gammax_problem_t* p, const gammax_options_t& o
     double guard = opt.cond_threshold * (smin * smin) / (smax * smax);
     if (opt.precision != GAMMAX_PREC_GUARDED) guard = INFINITY;
     sa.den_guard = (float)guard;
+    sa.ill_span2 = (sa.den_guard * 0.999f - 1.0f) / ((sa.inv_s2[0] + sa.inv_s2[1]) + sa.inv_s2[2]);
     sa.k1 = k1;
     sa.r2_cap = r2_cap;
     const bool learned = uses_model(p, &opt);
@@ -690,6 +691,25 @@ ZeroGeo make_zero_geo(const gammax_problem_t* p) {
     for (int k = 0; k < (nd == 3 ? 8 : 4); ++k) {
         if (nd == 3) table_row_host(3, s3, (k >> 2) - 1, ((k >> 1) & 1) - 1, (k & 1) - 1, &z.row[k]);
         else table_row_host(2, s3, 0, (k >> 1) - 1, (k & 1) - 1, &z.row[k]);
+    }
+    if (nd == 3) {
+        // a face of cell k that misses the node's corner v lies past a plane t_i = t_j, i in v
+        // and j outside (v = 7: past a plane t_i = 0); cell 7 (v = 0) owns none
+        const double s2[3] = {s3[2] * s3[2], s3[1] * s3[1], s3[0] * s3[0]};   // x, y, z
+        double least = INFINITY;
+        for (int k = 0; k < 8; ++k) {
+            const int v = 7 ^ k;
+            double d2 = INFINITY;
+            for (int i = 0; i < 3; ++i) {
+                if (!((v >> i) & 1)) continue;
+                if (v == 7) d2 = std::fmin(d2, s2[i]);
+                for (int j = 0; j < 3; ++j)
+                    if (!((v >> j) & 1)) d2 = std::fmin(d2, s2[i] * s2[j] / (s2[i] + s2[j]));
+            }
+            z.far2[k] = round_down_float(d2 * (1.0 - 1e-6));
+            least = std::fmin(least, d2);
+        }
+        z.far2_min = round_down_float(least * (1.0 - 1e-6));
     }
     return z;
 }

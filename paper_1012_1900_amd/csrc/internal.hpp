@@ -187,6 +187,11 @@ inline FastDiv make_fast_div(uint32_t d) {
     return FastDiv{(uint32_t)(((uint64_t)1 << (31 + s)) / d + 1), s - 1};
 }
 
+// Tails of at least this many nodes take the queued walk in the automatic layout: at 13 thousand
+// nodes (24 us against 27) the wide groups of the plain one still win, which keep a short
+// tail's latency low; at 23 thousand (60 us against 43-58) they no longer do.
+constexpr uint32_t QUEUED_TAIL = 16384;
+
 struct SearchArgs {
     const float* ref;
     const float* ev;
@@ -203,6 +208,8 @@ struct SearchArgs {
     float inv_s2[7];         // FP32 1 / sigma^2 of the chain blocks x, y, z, xy, xz, yz, xyz
                              // (sigma_B^2 = sum over B of s_i^2; the z terms are 0 in 2D)
     float den_guard;         // FP64 re-projection when a tetrahedron's Den exceeds this
+    float ill_span2;         // corners within this squared dose span hold no such tetrahedron:
+                             // Den <= 1 + span^2 (1/sx^2 + 1/sy^2 + 1/sz^2), with a margin for rounding
     double sx, sy, sz;       // s_i in double for the FP64 paths
     float k1;                // key^2 of the first table row after the zero-key cells (+inf: none)
     float r2_cap;            // the table holds every cell with key^2 < r2_cap
@@ -225,6 +232,8 @@ struct SearchArgs {
 
 struct ZeroGeo {
     TabEntry row[8];         // the 2^d zero-key cells in table order
+    float far2[8];           // 3D: least squared distance of a cell's faces that miss the node
+    float far2_min;          // the smallest over the cells that own such faces
 };
 
 // The whole search on `s`: zero-key pass over all M nodes (grid order), sort of the tail,

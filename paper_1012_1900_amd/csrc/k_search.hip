@@ -678,10 +678,393 @@ __device__ __forceinline__ int resume_row(const TabEntry* tab, int n, int first,
     return lo;
 }
 
-// Pass A in 3D.  MODE 0: FP32; MODE 1: FP32 and flag ill-conditioned tetrahedra.
+// Full cells among the zero-key cells of a node (every one is evaluated for a tail node).
+__device__ __forceinline__ uint32_t zero_cells(int DIM, int x, int y, int z, int nx, int ny, int nz) {
+    const uint32_t cx = (x > 0) + (x + 1 < nx), cy = (y > 0) + (y + 1 < ny);
+    const uint32_t cz = DIM == 3 ? (uint32_t)((z > 0) + (z + 1 < nz)) : 1u;
+    return cx * cy * cz;
+}
+
+// End of a key-0 pass block (all its threads): a finished node's gamma, the block's counts,
+// and the appends of its tail and guard nodes.  The counts of a wave come from ballots (a node
+// visits at most 8 cells), the waves' from one barrier, and only a block with tail or guard
+// nodes waits for the atomics that give it its slots.  (Two appends and a reduction of five
+// counts by shuffles, with eight barriers between them, took 34.0 and 191 us where this takes
+// 32.3 and 180: 391 thousand nodes at 2.5 mm, 3.1 million at 1.25 mm.)
+__device__ __forceinline__ void zero_epilogue(const SearchArgs& a, BlockSums* bins, uint32_t vb, bool live, int node,
+                                              float F, uint32_t key, uint32_t cells, bool to_tail, bool to_guard) {
+    constexpr int WAVES = SEARCH_THREADS / WAVE;
+    __shared__ uint32_t s_n[6][WAVES];   // tail, guard, pass, border, cells, max gamma^2
+    __shared__ uint32_t s_base[2];
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    const bool done = live && !to_tail && !to_guard;
+    const float gam = sqrtf(F);
+    if (done) a.gamma[node] = gam;
+    const unsigned long long tb = __ballot(to_tail), gb = __ballot(to_guard);
+    const uint32_t npass = (uint32_t)__popcll(__ballot(done && gam <= 1.0f));
+    const uint32_t nborder = (uint32_t)__popcll(__ballot(done && fabsf(gam - 1.0f) <= 1e-5f));
+    cells = done ? cells : 0u;
+    uint32_t ncells = 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ncells += (uint32_t)__popcll(__ballot((cells >> k) & 1u)) << k;
+    uint32_t gm = done ? f2u(gam * gam) : 0u;
+    for (int o = WAVE / 2; o > 0; o >>= 1) gm = max(gm, (uint32_t)__shfl_xor((int)gm, o));
+    if (lane == 0) {
+        s_n[0][w] = (uint32_t)__popcll(tb);
+        s_n[1][w] = (uint32_t)__popcll(gb);
+        s_n[2][w] = npass;
+        s_n[3][w] = nborder;
+        s_n[4][w] = ncells;
+        s_n[5][w] = gm;
+    }
+    __syncthreads();
+    uint32_t tot[2] = {0u, 0u}, off[2] = {0u, 0u};
+#pragma unroll
+    for (int j = 0; j < WAVES; ++j)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const uint32_t n = s_n[k][j];
+            off[k] += j < w ? n : 0u;
+            tot[k] += n;
+        }
+    if (threadIdx.x == 0) {
+        if (tot[0]) s_base[0] = atomicAdd(&a.sc->n_tail, tot[0]);
+        if (tot[1]) s_base[1] = atomicAdd(&a.sc->n_guard, tot[1]);
+    }
+    if (threadIdx.x == WAVE) {
+        uint32_t t[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int j = 0; j < WAVES; ++j) {
+            t[0] += s_n[2][j];
+            t[1] += s_n[3][j];
+            t[2] += s_n[4][j];
+            t[3] = max(t[3], s_n[5][j]);
+        }
+        BlockSums* out = &bins[vb & (SUM_BINS - 1)];
+        if (t[0]) atomicAdd(&out->pass, (unsigned long long)t[0]);
+        if (t[1]) atomicAdd(&out->border, (unsigned long long)t[1]);
+        if (t[2]) atomicAdd(&out->cells, (unsigned long long)t[2]);
+        if (t[3]) atomicMax(&out->maxg2, t[3]);
+    }
+    if (tot[0] + tot[1] == 0u) return;
+    __syncthreads();
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    if (to_tail) {
+        const uint32_t pos = s_base[0] + off[0] + (uint32_t)__popcll(tb & lt);
+        a.tail_node[pos] = (uint32_t)node;
+        a.tail_f[pos] = f2u(F);
+        a.tail_key_arr[pos] = key;
+        a.tail_pos[pos] = pos;
+    }
+    if (to_guard) a.guard_list[s_base[1] + off[1] + (uint32_t)__popcll(gb & lt)] = (uint32_t)node;
+}
+
+// ---- pass A in 3D ------------------------------------------------------------------------
+//
+// A key-0 cell holds the node at one of its corners (bit i of V: the corner's side along axis
+// i, x = 1, y = 2, z = 4), and of the 26 faces it owns only those whose chain steps onto that
+// corner hold the node: 75 of the 208 of the eight cells.  For these the spatial constants are
+// exact zeros and ones (mu = -1 for the blocks stepped before the node, 0 after it, no
+// perpendicular part), so the near faces below are cell3's with the same roundings and
+// without its constant terms.
+//
+// The other 133 faces ("far") keep a distance from the node.  A face that misses corner V has,
+// at every point, t_j >= t_i for some axis i in V and j outside it (or, V = 7, some t_i = 0),
+// so it lies at least at the distance from the node to the plane t_i = t_j,
+// 1 / sqrt(1 / s_i^2 + 1 / s_j^2), or to t_i = 0 (ZeroGeo::far2), and its doses lie in the
+// range of the cell's corners.  After the near faces a cell is needed only if that bound is
+// below F, with the tail walk's margin of 2^-8 F; the needed cells of a wave (0.3 of 7 per
+// node at 2.5 mm 3%/3mm, 0.7-1.9 at 1.25 mm) are queued in LDS and projected 64 at a time as
+// in the walk of long tails.  Nodes at the grid's faces queue all of their cells instead.  The
+// minimum has the same bits as over all 208 faces.
+//
+// Bound by VALU issue (1870 instructions of a wave against 3270 over all faces at 2.5 mm) and,
+// at 391 thousand nodes, by the two rounds its 1528 blocks take: 40.0 -> 32.3 us there,
+// 3.1 million nodes at 1.25 mm 259 -> 180 us (guarded).  Capped at 128 VGPRs for four waves per
+// SIMD (140 uncapped: 34.7 and 204 us).
+
+// Chain sums at a block stepped before the node (M = 1: mu = -1) or after it (M = 0: mu = 0).
+template <int M>
+__device__ __forceinline__ float near_n(float n, const Step<float>& s) {
+#pragma clang fp contract(off)
+    return M ? n + s.d : n;
+}
+template <int M>
+__device__ __forceinline__ float near_t(const Step<float>& s, float L) {
+#pragma clang fp contract(off)
+    return M ? fmadd(-s.w, L, 1.0f) : -(s.w * L);
+}
+template <int M1>
+__device__ __forceinline__ float near1(float g0, const Step<float>& a) {
+#pragma clang fp contract(off)
+    const float N = near_n<M1>(g0, a);
+    const float L = N * Num<float>::rcp(den_step(1.0f, a));
+    const float t1 = near_t<M1>(a, L);
+    return (t1 >= 0.0f && t1 <= 1.0f) ? N * L : Num<float>::inf();
+}
+template <int M1, int M2>
+__device__ __forceinline__ float near2(float g0, const Step<float>& a, const Step<float>& b) {
+#pragma clang fp contract(off)
+    const float N = near_n<M2>(near_n<M1>(g0, a), b);
+    const float L = N * Num<float>::rcp(den_step(den_step(1.0f, a), b));
+    const float t1 = near_t<M1>(a, L), t2 = near_t<M2>(b, L);
+    return (t1 <= 1.0f && t1 >= t2 && t2 >= 0.0f) ? N * L : Num<float>::inf();
+}
+template <int M1, int M2, int M3>
+__device__ __forceinline__ float near3(float g0, const Step<float>& a, const Step<float>& b, const Step<float>& c) {
+#pragma clang fp contract(off)
+    const float N = near_n<M3>(near_n<M2>(near_n<M1>(g0, a), b), c);
+    const float L = N * Num<float>::rcp(den3(a, b, c));
+    const float t1 = near_t<M1>(a, L), t2 = near_t<M2>(b, L), t3 = near_t<M3>(c, L);
+    return (t1 <= 1.0f && t1 >= t2 && t2 >= t3 && t3 >= 0.0f) ? N * L : Num<float>::inf();
+}
+template <int S>
+__device__ __forceinline__ float inv_of(const InvS2<float>& is) {
+    if constexpr (S == 1) return is.x;
+    else if constexpr (S == 2) return is.y;
+    else if constexpr (S == 4) return is.z;
+    else if constexpr (S == 3) return is.xy;
+    else if constexpr (S == 5) return is.xz;
+    else if constexpr (S == 6) return is.yz;
+    else return is.xyz;
+}
+// Step from vertex U of the cell along block S.
+template <int U, int S>
+__device__ __forceinline__ Step<float> near_step(const float* g, const InvS2<float>& is) {
+    static_assert((U & S) == 0, "a chain steps away from its start");
+    return mk_step(g[U | S], g[U], inv_of<S>(is));
+}
+// Smallest dist^2 over the near faces of the cell that holds the node at corner V (V = 0: but
+// the node itself).  A, B, C: the axes, V = A, A | B, 7 or 0.
+template <int V, int A, int B, int C>
+__device__ __forceinline__ float near_faces(const float* g, const InvS2<float>& is) {
+    const float g0 = g[0];
+    if constexpr (V == A) {
+        const Step<float> a = near_step<0, A>(g, is), ab = near_step<A, B>(g, is), ac = near_step<A, C>(g, is);
+        float r = vmin<float>(near1<1>(g0, a), near2<1, 0>(g0, a, near_step<A, (B | C)>(g, is)));
+        r = vmin<float>(r, vmin<float>(near2<1, 0>(g0, a, ab), near2<1, 0>(g0, a, ac)));
+        return vmin<float>(r, vmin<float>(near3<1, 0, 0>(g0, a, ab, near_step<(A | B), C>(g, is)),
+                                          near3<1, 0, 0>(g0, a, ac, near_step<(A | C), B>(g, is))));
+    } else if constexpr (V == (A | B)) {
+        const Step<float> a = near_step<0, A>(g, is), b = near_step<0, B>(g, is), e = near_step<0, (A | B)>(g, is);
+        const Step<float> ab = near_step<A, B>(g, is), ba = near_step<B, A>(g, is), c = near_step<(A | B), C>(g, is);
+        float r = vmin<float>(near1<1>(g0, e), near2<1, 0>(g0, e, c));
+        r = vmin<float>(r, vmin<float>(near2<1, 1>(g0, a, ab), near2<1, 1>(g0, b, ba)));
+        return vmin<float>(r, vmin<float>(near3<1, 1, 0>(g0, a, ab, c), near3<1, 1, 0>(g0, b, ba, c)));
+    } else {
+        constexpr int M = V == 7 ? 1 : 0;
+        const Step<float> x = near_step<0, 1>(g, is), y = near_step<0, 2>(g, is), z = near_step<0, 4>(g, is);
+        const Step<float> xy = near_step<0, 3>(g, is), xz = near_step<0, 5>(g, is), yz = near_step<0, 6>(g, is);
+        const Step<float> x_y = near_step<1, 2>(g, is), x_z = near_step<1, 4>(g, is), y_x = near_step<2, 1>(g, is);
+        const Step<float> y_z = near_step<2, 4>(g, is), z_x = near_step<4, 1>(g, is), z_y = near_step<4, 2>(g, is);
+        const Step<float> xy_z = near_step<3, 4>(g, is), xz_y = near_step<5, 2>(g, is), yz_x = near_step<6, 1>(g, is);
+        float r = near1<M>(g0, near_step<0, 7>(g, is));
+        r = vmin<float>(r, vmin<float>(near2<M, M>(g0, x, near_step<1, 6>(g, is)), near2<M, M>(g0, yz, yz_x)));
+        r = vmin<float>(r, vmin<float>(near2<M, M>(g0, y, near_step<2, 5>(g, is)), near2<M, M>(g0, xz, xz_y)));
+        r = vmin<float>(r, vmin<float>(near2<M, M>(g0, z, near_step<4, 3>(g, is)), near2<M, M>(g0, xy, xy_z)));
+        r = vmin<float>(r, vmin<float>(near3<M, M, M>(g0, x, x_y, xy_z), near3<M, M, M>(g0, x, x_z, xz_y)));
+        r = vmin<float>(r, vmin<float>(near3<M, M, M>(g0, y, y_x, xy_z), near3<M, M, M>(g0, y, y_z, yz_x)));
+        r = vmin<float>(r, vmin<float>(near3<M, M, M>(g0, z, z_x, xz_y), near3<M, M, M>(g0, z, z_y, yz_x)));
+        if constexpr (V == 0) {
+            r = vmin<float>(r, vmin<float>(near1<0>(g0, x), vmin<float>(near1<0>(g0, y), near1<0>(g0, z))));
+            r = vmin<float>(r, vmin<float>(near1<0>(g0, xy), vmin<float>(near1<0>(g0, xz), near1<0>(g0, yz))));
+            r = vmin<float>(r, vmin<float>(near2<0, 0>(g0, x, x_y), near2<0, 0>(g0, y, y_x)));
+            r = vmin<float>(r, vmin<float>(near2<0, 0>(g0, x, x_z), near2<0, 0>(g0, z, z_x)));
+            r = vmin<float>(r, vmin<float>(near2<0, 0>(g0, y, y_z), near2<0, 0>(g0, z, z_y)));
+        }
+        return r;
+    }
+}
+// Corners of key-0 cell c = 4 (az + 1) + 2 (ay + 1) + (ax + 1) from the 3 x 3 x 3 neighbourhood.
+template <int C>
+__device__ __forceinline__ void zero_corners(const float* g27, float* g) {
+#pragma unroll
+    for (int b = 0; b < 8; ++b)
+        g[b] = g27[((C >> 2) + (b >> 2)) * 9 + (((C >> 1) & 1) + ((b >> 1) & 1)) * 3 + (C & 1) + (b & 1)];
+}
+template <int C, int V, int A, int B, int CC>
+__device__ __forceinline__ float zero_near(const float* g27, const InvS2<float>& is) {
+    static_assert((C ^ 7) == V, "the node's corner");
+    float g[8];
+    zero_corners<C>(g27, g);
+    return near_faces<V, A, B, CC>(g, is);
+}
+
+// MODE 0: FP32; MODE 1: FP32 and flag ill-conditioned tetrahedra.
 // vb: the block's index in the node list (256 nodes each).
-template <int MODE, bool JU = false>
+template <int MODE>
 __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& zg, BlockSums* sums, uint32_t vb) {
+    constexpr int GMODE = MODE == 1 ? 1 : 0;
+    constexpr int WAVES = SEARCH_THREADS / WAVE;
+    __shared__ float s_g[WAVES][27][WAVE];          // normalised neighbourhoods of the wave's nodes
+    __shared__ uint32_t s_f[WAVES][WAVE];           // their F (non-negative float bits)
+    __shared__ uint16_t s_item[WAVES][8 * WAVE];    // queued cells: node's lane | cell << 6
+    __shared__ uint8_t s_up[WAVES][WAVE];           // bit i: the grid goes on past the node along axis i
+    __shared__ TabEntry s_zero[8];
+    const uint32_t M = a.sc->n_masked;
+    if (vb * SEARCH_THREADS >= M) {   // grids are sized for every grid node; M is on the device
+        return;
+    }
+    if (threadIdx.x < 8) s_zero[threadIdx.x] = zg.row[threadIdx.x];
+    __syncthreads();
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    const uint32_t i = vb * SEARCH_THREADS + threadIdx.x;
+    const bool live = i < M;
+    const int nx = a.nx, ny = a.ny, nz = a.nz, sxy = nx * ny;
+    const int node = live ? (int)a.nodes[i] : 0;
+    const uint32_t yz = fast_div((uint32_t)node, a.div_nx);
+    const int z = (int)fast_div(yz, a.div_ny), y = (int)yz - z * ny, x = node - (int)yz * nx;
+    const float dr = a.ref[node];
+    const float inv_dd = node_inv_dd(dr, a.sc->inv_dd, a.dd, a.local);
+    // neighbourhood offsets, clamped at the grid faces (clamped values feed only cells
+    // that do not exist or faces that are masked out)
+    const int oxm = x > 0 ? -1 : 0, oxp = x + 1 < nx ? 1 : 0;
+    const int oym = y > 0 ? -nx : 0, oyp = y + 1 < ny ? nx : 0;
+    const int ozm = z > 0 ? -sxy : 0, ozp = z + 1 < nz ? sxy : 0;
+    const int ox[3] = {oxm, 0, oxp}, oy[3] = {oym, 0, oyp}, oz[3] = {ozm, 0, ozp};
+    float g27[27];
+#pragma unroll
+    for (int k = 0; k < 27; ++k) g27[k] = a.ev[node + oz[k / 9] + oy[(k / 3) % 3] + ox[k % 3]];
+#pragma unroll
+    for (int k = 0; k < 27; ++k) g27[k] = dose_norm<float>(g27[k], dr, inv_dd);
+    const float F0 = live ? g27[13] * g27[13] : 0.0f;   // gamma0^2
+
+    const InvS2<float> is = inv_s2_of(a);
+    const bool bnd = oxm == 0 || oxp == 0 || oym == 0 || oyp == 0 || ozm == 0 || ozp == 0;
+    const bool open = live && F0 > 0.0f;   // a node of dose difference 0 visits no cell
+    float F = F0;
+    {
+        float r = zero_near<7, 0, 1, 2, 4>(g27, is);
+        r = vmin<float>(r, zero_near<6, 1, 1, 2, 4>(g27, is));
+        r = vmin<float>(r, zero_near<5, 2, 2, 1, 4>(g27, is));
+        r = vmin<float>(r, zero_near<3, 4, 4, 1, 2>(g27, is));
+        r = vmin<float>(r, zero_near<4, 3, 1, 2, 4>(g27, is));
+        r = vmin<float>(r, zero_near<2, 5, 1, 4, 2>(g27, is));
+        r = vmin<float>(r, zero_near<1, 6, 2, 4, 1>(g27, is));
+        r = vmin<float>(r, zero_near<0, 7, 1, 2, 4>(g27, is));
+        F = open && !bnd ? vmin<float>(F, r) : F;
+    }
+    // a neighbourhood whose doses span less than this holds no ill-conditioned tetrahedron
+    bool suspect = false;
+    if constexpr (MODE == 1) {
+        float lo = g27[0], hi = g27[0];
+#pragma unroll
+        for (int k = 1; k < 27; ++k) {
+            lo = vmin<float>(lo, g27[k]);
+            hi = __builtin_fmaxf(hi, g27[k]);
+        }
+        suspect = open && !((hi - lo) * (hi - lo) < a.ill_span2);
+    }
+
+    // the cells with far faces that can lower F, or (at the grid's faces) every cell there is
+    uint32_t q = 0;
+    uint16_t* item = s_item[wv];
+    auto push = [&](bool want, int c) {
+        const unsigned long long mask = __ballot(want);
+        if (want)
+            item[q + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] =
+                (uint16_t)(lane | (c << 6));
+        q += (uint32_t)__popcll(mask);
+    };
+    const float Fm = F + F * 0x1p-8f;
+    const bool edge = open && bnd, inner = open && !bnd;
+    if (__ballot(edge || (inner && zg.far2_min < Fm)) != 0ull) {
+        // corner ranges of the eight cells, pairs along x, then y, then z
+        float lo[18], hi[18];
+#pragma unroll
+        for (int k = 0; k < 18; ++k) {
+            const int r = k >> 1, p = 3 * r + (k & 1);
+            lo[k] = vmin<float>(g27[p], g27[p + 1]);
+            hi[k] = __builtin_fmaxf(g27[p], g27[p + 1]);
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int k = ((c >> 2) * 3 + ((c >> 1) & 1)) * 2 + (c & 1);   // pair (z, y, x) of the cell
+            const float l = vmin<float>(vmin<float>(lo[k], lo[k + 2]), vmin<float>(lo[k + 6], lo[k + 8]));
+            const float h = __builtin_fmaxf(__builtin_fmaxf(hi[k], hi[k + 2]), __builtin_fmaxf(hi[k + 6], hi[k + 8]));
+            const float m = __builtin_fmaxf(__builtin_fmaxf(l, -h), 0.0f);
+            const bool there = ((c & 1) || oxm != 0) && ((c & 2) || oym != 0) && ((c & 4) || ozm != 0);
+            push((inner && c != 7 && fmadd(m, m, zg.far2[c]) < Fm) || (edge && there), c);
+        }
+    }
+    bool redo = suspect;
+    if (q != 0u || __ballot(redo) != 0ull) {
+#pragma unroll
+        for (int k = 0; k < 27; ++k) s_g[wv][k][lane] = g27[k];
+        s_f[wv][lane] = f2u(F);
+        s_up[wv][lane] = (uint8_t)((oxp ? 1 : 0) | (oyp ? 2 : 0) | (ozp ? 4 : 0));
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    uint32_t n_fp64 = 0;
+    GuardCtx gc{};
+    // cell c of the node of lane nl, all faces it owns
+    auto cell_of = [&](int nl, int c, bool mask, auto gmode, bool& ill) -> float {
+        const float(*gn)[WAVE] = s_g[wv] + (((c >> 2) * 3 + ((c >> 1) & 1)) * 3 + (c & 1));
+        float g[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) g[b] = gn[(b >> 2) * 9 + ((b >> 1) & 1) * 3 + (b & 1)][nl];
+        const Geo<float> G = geo_from_row(s_zero[c]);
+        const uint32_t up = s_up[wv][nl] | ~(uint32_t)c;   // a cell at -1 reaches back to the node
+        if (mask)
+            return cell3<float, true, decltype(gmode)::value>(g, G, is, up & 1u, up & 2u, up & 4u, a.den_guard, gc, n_fp64,
+                                                               ill);
+        return cell3<float, false, decltype(gmode)::value>(g, G, is, true, true, true, a.den_guard, gc, n_fp64, ill);
+    };
+    bool ill = false;
+    if (q != 0u) {
+#pragma unroll 1
+        for (uint32_t h = 0; h < q; h += WAVE) {
+            const bool on = h + lane < q;
+            const uint32_t it = on ? item[h + lane] : 0u;
+            const int nl = (int)(it & 63u), c = (int)(it >> 6);
+            const bool whole = ((s_up[wv][nl] | ~(uint32_t)c) & 7u) == 7u;
+            const bool mask = __ballot(on && !whole) != 0ull;
+            if (on) {
+                const float v = cell_of(nl, c, mask, std::integral_constant<int, 0>{}, ill);
+                atomicMin(&s_f[wv][nl], f2u(v));
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        F = u2f(s_f[wv][lane]);
+    }
+    uint32_t cells = open ? zero_cells(3, x, y, z, nx, ny, nz) : 0u;
+    // rare: the tetrahedra of a steep neighbourhood are judged, and a node whose F fell to 0
+    // counts the cells up to there, cell by cell in table order
+    const bool zero = open && F == 0.0f;
+    if (__ballot(redo || zero) != 0ull) {
+        if (q == 0u && __ballot(redo) == 0ull) {
+#pragma unroll
+            for (int k = 0; k < 27; ++k) s_g[wv][k][lane] = g27[k];
+            s_up[wv][lane] = (uint8_t)((oxp ? 1 : 0) | (oyp ? 2 : 0) | (ozp ? 4 : 0));
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        if (redo || zero) {
+            F = F0;
+            cells = 0u;
+#pragma unroll 1
+            for (int c = 0; c < 8; ++c) {
+                const bool there = ((c & 1) || oxm != 0) && ((c & 2) || oym != 0) && ((c & 4) || ozm != 0);
+                if (!there) continue;
+                const bool whole = (!(c & 1) || oxp != 0) && (!(c & 2) || oyp != 0) && (!(c & 4) || ozp != 0);
+                cells += F > 0.0f && whole ? 1u : 0u;
+                F = vmin<float>(F, cell_of(lane, c, true, std::integral_constant<int, GMODE>{}, ill));
+            }
+        }
+    }
+    const bool to_guard = MODE == 1 && ill && open;
+    const bool to_tail = live && !to_guard && F > a.k1;
+    zero_epilogue(a, sums, vb, live, node, F, tail_sort_key(a, node, F0, F), cells, to_tail, to_guard);
+}
+
+template <int MODE>
+__global__ __launch_bounds__(SEARCH_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_zero3(SearchArgs a, ZeroGeo zg, BlockSums* sums) {
+    zero3_body<MODE>(a, zg, sums, blockIdx.x);
+}
+
+// Pass A in 3D with Ju et al.'s recursion (projection = 1): one lane per node, the recursion
+// in interior cells, every owned face in the cells of a wave that meets a grid face.
+template <int MODE>
+__device__ __forceinline__ void zero3_ju_body(const SearchArgs& a, const ZeroGeo& zg, BlockSums* sums, uint32_t vb) {
     constexpr int GMODE = MODE == 1 ? 1 : 0;
     const uint32_t M = a.sc->n_masked;
     if (vb * SEARCH_THREADS >= M) {   // grids are sized for every grid node; M is on the device
@@ -731,10 +1114,7 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
             v = exists ? v : Num<float>::inf();
             cells += (F > 0.0f && exists && okx && oky && okz) ? 1u : 0u;
         } else {
-            if constexpr (JU)
-                v = cell3_ju<GMODE>(g, G, is, a.s2x, a.s2y, a.s2z, a.den_guard, ill);
-            else
-                v = cell3<float, false, GMODE>(g, G, is, true, true, true, a.den_guard, gc, n_fp64, ill);
+            v = cell3_ju<GMODE>(g, G, is, a.s2x, a.s2y, a.s2z, a.den_guard, ill);
             cells += F > 0.0f ? 1u : 0u;
         }
         F = F0 > 0.0f ? vmin<float>(F, v) : F;
@@ -762,9 +1142,9 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
     block_sums(sums, vb, npass, nborder, 0u, ncells, gm);
 }
 
-template <int MODE, bool JU = false>
-__global__ __launch_bounds__(SEARCH_THREADS) void k_zero3(SearchArgs a, ZeroGeo zg, BlockSums* sums) {
-    zero3_body<MODE, JU>(a, zg, sums, blockIdx.x);
+template <int MODE>
+__global__ __launch_bounds__(SEARCH_THREADS) void k_zero3_ju(SearchArgs a, ZeroGeo zg, BlockSums* sums) {
+    zero3_ju_body<MODE>(a, zg, sums, blockIdx.x);
 }
 
 // Pass A in 2D (4 zero-key cells, 3x3 neighbourhood).
@@ -833,13 +1213,6 @@ template <int MODE>
 __global__ __launch_bounds__(SEARCH_THREADS) void k_zero2(SearchArgs a, ZeroGeo zg, BlockSums* sums) {
     zero2_body(a, zg, sums, blockIdx.x);
     (void)MODE;
-}
-
-// Full cells among the zero-key cells of a node (every one is evaluated for a tail node).
-__device__ __forceinline__ uint32_t zero_cells(int DIM, int x, int y, int z, int nx, int ny, int nz) {
-    const uint32_t cx = (x > 0) + (x + 1 < nx), cy = (y > 0) + (y + 1 < ny);
-    const uint32_t cz = DIM == 3 ? (uint32_t)((z > 0) + (z + 1 < nz)) : 1u;
-    return cx * cy * cz;
 }
 
 // Pass A with one lane per cell: the 2^d lanes of a group share one node (grid order) and
@@ -1448,9 +1821,6 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
     const float inv_dd_g = a.sc->inv_dd;
     const InvS2<float> is = inv_s2_of(a);
     const bool ranges = a.range != nullptr && M >= a.range_min;   // (N < 2^29: byte offsets fit 32 bits)
-    // a cell whose corner differences span less than this holds no ill-conditioned
-    // tetrahedron: Den <= 1 + span^2 (1/sx^2 + 1/sy^2 + 1/sz^2), with a margin for rounding
-    const float ill_span2 = (a.den_guard * 0.999f - 1.0f) / ((is.x + is.y) + is.z);
     uint32_t cells = 0, gm = 0, npass = 0, nborder = 0, long_rows = 0;
     GuardCtx gc{};
     uint32_t dummy_fp64 = 0;
@@ -1570,7 +1940,7 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
             const float m = __builtin_fmaxf(__builtin_fmaxf(glo, -ghi), 0.0f);
             const float lb = fmadd(m, m, kk[k]);
             const bool need = ((work >> k) & 1u) && lb < Fm;
-            if constexpr (DIM == 3 && MODE == 1) suspect = suspect || !((ghi - glo) * (ghi - glo) < ill_span2);
+            if constexpr (DIM == 3 && MODE == 1) suspect = suspect || !((ghi - glo) * (ghi - glo) < a.ill_span2);
             const unsigned long long mask = __ballot(need);
             if (need)
                 queue[(q_tail + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))) &
@@ -1780,17 +2150,12 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
     block_sums(sums, vb, npass, nborder, 0u, cells, gm);
 }
 
-// Tails of at least this many nodes take the queued walk: at 13 thousand nodes (24 us against
-// 27) the wide groups of tail_group_body still win, which keep a short tail's latency low; at
-// 23 thousand (60 us against 43-58) they no longer do.
-constexpr uint32_t TQ_MIN_TAIL = 16384;
-
 // The walk of the automatic layout (vb / vgrid: this block and the number of blocks).
 template <int DIM, int MODE>
 __device__ __forceinline__ void tail_auto_body(const SearchArgs& a, const uint32_t* __restrict__ order, bool sorted,
                                                const uint32_t* __restrict__ count, int first, int g_req, BlockSums* sums,
                                                uint32_t vb, uint32_t vgrid) {
-    if (*count >= TQ_MIN_TAIL)
+    if (*count >= QUEUED_TAIL)
         tail_queue_body<DIM, MODE>(a, a.tab, sorted ? order : nullptr, *count, first, sums, vb, vgrid);
     else
         tail_group_body<DIM, MODE>(a, a.tab, order, count, first, g_req, 0, sums, vb, vgrid);
@@ -2540,8 +2905,8 @@ hipError_t launch_search(const SearchArgs& a, const SearchPlan& p, hipStream_t s
             }
         } else if (p.ndim == 3 && p.projection == 1) {
             // Ju's recursion in the key-0 pass (interior cells)
-            if (guarded) hipLaunchKernelGGL((k_zero3<1, true>), dim3(nb), dim3(SEARCH_THREADS), 0, s, a, p.zero, sums);
-            else hipLaunchKernelGGL((k_zero3<0, true>), dim3(nb), dim3(SEARCH_THREADS), 0, s, a, p.zero, sums);
+            if (guarded) hipLaunchKernelGGL(k_zero3_ju<1>, dim3(nb), dim3(SEARCH_THREADS), 0, s, a, p.zero, sums);
+            else hipLaunchKernelGGL(k_zero3_ju<0>, dim3(nb), dim3(SEARCH_THREADS), 0, s, a, p.zero, sums);
         } else if (p.ndim == 3) {
             if (guarded) hipLaunchKernelGGL(k_zero3<1>, dim3(nb), dim3(SEARCH_THREADS), 0, s, a, p.zero, sums);
             else hipLaunchKernelGGL(k_zero3<0>, dim3(nb), dim3(SEARCH_THREADS), 0, s, a, p.zero, sums);
