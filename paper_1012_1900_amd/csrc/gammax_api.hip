@@ -303,13 +303,9 @@ __global__ void k_zero_u32(uint32_t* p) {
     if (threadIdx.x == 0) *p = 0u;
 }
 
-// The map's scalars into the pinned ring at the slot of the device map counter, made
-// visible at system scope before the kernel ends; then the counter moves on.  One wave:
-// every lane reads the same counter value.  (A runtime device-to-host copy queued after the
-// map's last kernel starts several microseconds after it; a kernel follows at once.)
+// A pair's scalars into its pinned ring (as a single map's last kernel does), one wave.
 __device__ __forceinline__ void publish_body(const Scalars* __restrict__ src, uint32_t* seq, Scalars* ring) {
     constexpr int W = (int)(sizeof(Scalars) / sizeof(uint32_t));
-    static_assert(sizeof(Scalars) % sizeof(uint32_t) == 0, "Scalars is a whole number of words");
     const uint32_t k = *seq;
     Scalars* dst = ring + (k % GAMMAX_ASYNC_SLOTS);
     const int t = threadIdx.x;
@@ -317,9 +313,7 @@ __device__ __forceinline__ void publish_body(const Scalars* __restrict__ src, ui
     if (t == 0) *seq = k + 1u;
     __threadfence_system();
 }
-__global__ void k_publish_scalars(const Scalars* __restrict__ src, uint32_t* seq, Scalars* ring) {
-    publish_body(src, seq, ring);
-}
+static_assert(SCALAR_RING == GAMMAX_ASYNC_SLOTS, "the kernels and the host count the same ring");
 // Every pair of a batch publishes its scalars (block i: pair i).
 __global__ void k_batch_publish(const BatchPair* __restrict__ pairs) {
     const BatchPair& P = pairs[blockIdx.x];
@@ -774,10 +768,12 @@ gammax_status_t enqueue_search(gammax_ctx* c, const CallSetup& cs, uint32_t m_bo
         plan.ev_sort_end = c->ev[6];
         plan.ev_tail_end = c->ev[7];
     }
+    // (its last kernel publishes: a runtime device-to-host copy queued behind it would start
+    // several microseconds after it)
+    plan.seq = c->d_seq;
+    plan.ring = c->h_ring;
     HIPCHK(c, launch_search(sa, plan, s));
     if (timing) HIPCHK(c, hipEventRecord(c->ev[8], s));
-    hipLaunchKernelGGL(k_publish_scalars, dim3(1), dim3(64), 0, s, (const Scalars*)c->d_sc, c->d_seq, c->h_ring);
-    HIPCHK(c, hipGetLastError());
     return GAMMAX_OK;
 }
 

@@ -22,13 +22,14 @@ struct Scalars {
     uint32_t sort_overflow; // the one-workgroup tail sort met a longer tail (left unsorted)
     uint32_t long_rows;     // longest tail walk in table rows, when above LONG_WALK_ROWS (else 0)
     uint32_t n_fallback_inline;   // learned radius, short tail: nodes the prediction would not certify
-    uint32_t reserved;
+    uint32_t ticket;        // blocks that have finished the guard pass
     unsigned long long n_pass;
     unsigned long long n_border;
     unsigned long long n_fp64;
     unsigned long long n_cells;
 };
 
+constexpr int SCALAR_RING = 64;   // slots of the pinned ring the maps publish to
 enum : uint32_t { FLAG_NONFINITE = 1u, FLAG_TABLE_SHORT = 2u };
 // A tail walk longer than this many table rows is recorded in Scalars::long_rows.
 constexpr uint32_t LONG_WALK_ROWS = 256;
@@ -259,6 +260,8 @@ struct SearchPlan {
     uint32_t* tmp_keys;      // sort scratch, M entries each
     uint32_t* tmp_vals;
     uint32_t* hist;          // sort_hist_words(M)
+    uint32_t* seq;           // device map counter and pinned ring the scalars are published to
+    Scalars* ring;           // (null: not published)
     int small_sort;          // sort the tail with the rank sort (expected to hold <= SMALL_SORT_CAP)
     hipEvent_t ev_shell_end; // optional: recorded after the zero-key pass
     hipEvent_t ev_sort_end;  // optional: recorded after the tail sort

@@ -2217,20 +2217,95 @@ __device__ __forceinline__ void finalize_body(const BlockSums* __restrict__ sums
     }
 }
 
-__global__ __launch_bounds__(SEARCH_THREADS) void k_finalize(const BlockSums* __restrict__ sums, int n,
-                                                             Scalars* sc, float r2_cap) {
-    finalize_body(sums, n, sc, r2_cap);
+// The map's scalars into the pinned ring at the slot of the device map counter, made visible
+// at system scope before the kernel ends; then the counter moves on.  src: global memory
+// (read at device scope: other blocks' atomics put the counts there) or LDS.
+template <bool LDS>
+__device__ __forceinline__ void publish_scalars(const uint32_t* src, uint32_t* seq, Scalars* ring) {
+    constexpr int W = (int)(sizeof(Scalars) / sizeof(uint32_t));
+    static_assert(sizeof(Scalars) % sizeof(uint32_t) == 0 && W <= WAVE, "Scalars fits one wave's words");
+    if (threadIdx.x >= WAVE) return;
+    const uint32_t k = *seq;   // (every lane reads the counter before lane 0 moves it on)
+    Scalars* dst = ring + (k % SCALAR_RING);
+    const int t = threadIdx.x;
+    if (t < W)
+        reinterpret_cast<volatile uint32_t*>(dst)[t] =
+            LDS ? src[t] : __hip_atomic_load(src + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (t == 0) *seq = k + 1u;
+    __threadfence_system();
 }
 
-// The guard pass and the count reduction in one launch (guarded precision, 3D): block 0
-// first adds the partial slots of the earlier passes into the scalars, then every block
-// redoes its share of the guard list in FP64-guarded precision and adds its own counts
-// straight into the scalars (a block with no guard nodes adds nothing).
-__global__ __launch_bounds__(SEARCH_THREADS) void k_guard_finalize(SearchArgs a, const TabEntry* __restrict__ tab,
-                                                                   const BlockSums* __restrict__ sums) {
-    if (blockIdx.x == 0) finalize_body<true>(sums, SUM_BINS, a.sc, a.r2_cap);
-    walk_body<3, 2, false>(a, tab, a.guard_list, &a.sc->n_guard, 0, 0, nullptr, blockIdx.x, gridDim.x);
+// End of a map in one launch: the partial slots of the passes are added to the scalars, the
+// nodes with an ill-conditioned tetrahedron are redone in FP64-guarded precision (GUARD: 3D,
+// guarded), and the scalars are published (ring: null where the caller reads them itself).
+// With no node to redo, block 0 does it all and the others return; else every block takes a
+// ticket after its share, and the last one publishes.  (A count reduction with the guard and
+// a publishing kernel behind it were two launches of 4.5 and 3.9 us at the end of every map;
+// this one takes 4.4.)
+template <bool GUARD>
+__global__ __launch_bounds__(SEARCH_THREADS) void k_finish(SearchArgs a, const BlockSums* __restrict__ sums,
+                                                           uint32_t* seq, Scalars* ring) {
+    constexpr int W = (int)(sizeof(Scalars) / sizeof(uint32_t));
+    __shared__ uint32_t s_last;
+    __shared__ __align__(8) uint32_t s_sc[W];
+    Scalars* sc = a.sc;
+    if (GUARD && sc->n_guard != 0u) {
+        if (blockIdx.x == 0) finalize_body<true>(sums, SUM_BINS, sc, a.r2_cap);
+        walk_body<3, 2, false>(a, a.tab, a.guard_list, &sc->n_guard, 0, 0, nullptr, blockIdx.x, gridDim.x);
+        if (!ring) return;
+        __threadfence();
+        __syncthreads();
+        if (threadIdx.x == 0) s_last = atomicAdd(&sc->ticket, 1u) == gridDim.x - 1u ? 1u : 0u;
+        __syncthreads();
+        if (s_last != 0u) publish_scalars<false>(reinterpret_cast<const uint32_t*>(sc), seq, ring);
+        return;
+    }
+    if (blockIdx.x != 0) return;
+    unsigned long long p = 0, b = 0, f = 0, c = 0;
+    uint32_t m = 0;
+    if (threadIdx.x < SUM_BINS) {
+        const BlockSums v = sums[threadIdx.x];
+        p = v.pass;
+        b = v.border;
+        f = v.fp64;
+        c = v.cells;
+        m = v.maxg2;
+    }
+    if (threadIdx.x < W) s_sc[threadIdx.x] = reinterpret_cast<const uint32_t*>(sc)[threadIdx.x];
+    __shared__ unsigned long long s[4][SEARCH_THREADS / WAVE];
+    __shared__ uint32_t sm[SEARCH_THREADS / WAVE];
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        p += (unsigned long long)__shfl_xor((long long)p, o);
+        b += (unsigned long long)__shfl_xor((long long)b, o);
+        f += (unsigned long long)__shfl_xor((long long)f, o);
+        c += (unsigned long long)__shfl_xor((long long)c, o);
+        m = max(m, (uint32_t)__shfl_xor((int)m, o));
+    }
+    if ((threadIdx.x & (WAVE - 1)) == 0) {
+        const int w = threadIdx.x / WAVE;
+        s[0][w] = p;
+        s[1][w] = b;
+        s[2][w] = f;
+        s[3][w] = c;
+        sm[w] = m;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        Scalars* l = reinterpret_cast<Scalars*>(s_sc);
+        if (u2f(l->r2_bits) > a.r2_cap && l->n_masked > 0) l->flags |= FLAG_TABLE_SHORT;
+        for (int w = 0; w < SEARCH_THREADS / WAVE; ++w) {
+            l->n_pass += s[0][w];
+            l->n_border += s[1][w];
+            l->n_fp64 += s[2][w];
+            l->n_cells += s[3][w];
+            l->maxg2_bits = max(l->maxg2_bits, sm[w]);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < W) reinterpret_cast<uint32_t*>(sc)[threadIdx.x] = s_sc[threadIdx.x];
+    if (ring) publish_scalars<true>(s_sc, seq, ring);
 }
+static_assert(SUM_BINS <= SEARCH_THREADS, "one partial slot per thread");
 
 constexpr unsigned kTailBlocks = 1024;   // grid-stride blocks of the tail walk
 constexpr unsigned kGuardBlocks = 64;    // grid-stride blocks of the guard pass
@@ -2338,8 +2413,8 @@ __global__ __launch_bounds__(SEARCH_THREADS) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
-// Every pair's guard pass with its count reduction (as k_guard_finalize), or the count
-// reduction alone (as k_finalize); block 0 of each pair then stamps its completion.
+// Every pair's guard pass with its count reduction, or the count reduction alone; block 0 of
+// each pair then stamps its completion.
 __global__ __launch_bounds__(SEARCH_THREADS) void k_batch_finish(const BatchPair* __restrict__ pairs,
                                                                  const uint2* __restrict__ items) {
     const uint2 w = items[blockIdx.x];
@@ -2939,13 +3014,13 @@ hipError_t launch_search(const SearchArgs& a, const SearchPlan& p, hipStream_t s
                 used += (int)tail_pass(a, p, a.fb_list, &a.sc->n_fallback, first, guarded, 2, tb, sums, s);
         }
         if (p.ev_tail_end) (void)hipEventRecord(p.ev_tail_end, s);
-        // guard pass, with the count reduction in the same launch
+        // guard pass, count reduction and publication in one launch
         if (guarded) {
-            hipLaunchKernelGGL(k_guard_finalize, dim3(kGuardBlocks), dim3(SEARCH_THREADS), 0, s, a, a.tab, sums);
+            hipLaunchKernelGGL(k_finish<true>, dim3(kGuardBlocks), dim3(SEARCH_THREADS), 0, s, a, sums, p.seq, p.ring);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(SEARCH_THREADS), 0, s, sums, SUM_BINS, a.sc, a.r2_cap);
+    hipLaunchKernelGGL(k_finish<false>, dim3(1), dim3(SEARCH_THREADS), 0, s, a, sums, p.seq, p.ring);
     return hipGetLastError();
 }
 
