@@ -647,6 +647,16 @@ SearchArgs make_search_args(const gammax_problem_t* p, const gammax_options_t& o
         sa.inv_s2[5] = z2 > 0.0f ? 1.0f / (y2 + z2) : 0.0f;
         sa.inv_s2[6] = 1.0f / ((x2 + y2) + z2);
     }
+    {
+        const double x2 = sx * sx, y2 = sy * sy, z2 = sz * sz;
+        sa.inv_s2d[0] = 1.0 / x2;
+        sa.inv_s2d[1] = 1.0 / y2;
+        sa.inv_s2d[2] = z2 > 0.0 ? 1.0 / z2 : 0.0;
+        sa.inv_s2d[3] = 1.0 / (x2 + y2);
+        sa.inv_s2d[4] = z2 > 0.0 ? 1.0 / (x2 + z2) : 0.0;
+        sa.inv_s2d[5] = z2 > 0.0 ? 1.0 / (y2 + z2) : 0.0;
+        sa.inv_s2d[6] = 1.0 / ((x2 + y2) + z2);
+    }
     double smin = std::fmin(sx, sy), smax = std::fmax(sx, sy);
     if (nd == 3) {
         smin = std::fmin(smin, sz);

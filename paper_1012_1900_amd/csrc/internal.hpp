@@ -212,6 +212,7 @@ struct SearchArgs {
     float ill_span2;         // corners within this squared dose span hold no such tetrahedron:
                              // Den <= 1 + span^2 (1/sx^2 + 1/sy^2 + 1/sz^2), with a margin for rounding
     double sx, sy, sz;       // s_i in double for the FP64 paths
+    double inv_s2d[7];       // and 1 / sigma^2, as inv_s2
     float k1;                // key^2 of the first table row after the zero-key cells (+inf: none)
     float r2_cap;            // the table holds every cell with key^2 < r2_cap
     int tail_key;            // key of the tail sort: 0 = gamma0^2 (DD sort), 1 = bound after the
@@ -239,7 +240,7 @@ struct ZeroGeo {
 
 // The whole search on `s`: zero-key pass over all M nodes (grid order), sort of the tail,
 // tail walk from the first non-zero key, FP64-guarded pass (precision 1), count reduction.
-// precision: 0 FP32, 1 guarded FP32, 2 FP64 (one walk over all nodes).
+// precision: 0 FP32, 1 guarded FP32, 2 FP64.
 struct SearchPlan {
     int ndim, precision;
     int tail_lanes;          // lanes per node in the tail walk: 1 (one lane per node) or 8..64

@@ -46,16 +46,20 @@ struct Num<float> {
     static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
     static __device__ __forceinline__ float inf() { return __builtin_huge_valf(); }
     static __device__ __forceinline__ float min(float a, float b) { return __builtin_fminf(a, b); }
+    static __device__ __forceinline__ float max(float a, float b) { return __builtin_fmaxf(a, b); }
 };
 template <>
 struct Num<double> {
     static __device__ __forceinline__ double rcp(double x) { return 1.0 / x; }
     static __device__ __forceinline__ double inf() { return __builtin_huge_val(); }
     static __device__ __forceinline__ double min(double a, double b) { return __builtin_fmin(a, b); }
+    static __device__ __forceinline__ double max(double a, double b) { return __builtin_fmax(a, b); }
 };
 
 template <typename T>
 __device__ __forceinline__ T vmin(T a, T b) { return Num<T>::min(a, b); }
+template <typename T>
+__device__ __forceinline__ T vmax(T a, T b) { return Num<T>::max(a, b); }
 
 // Fused multiply-add, written out: the projections below form every product-sum they fuse
 // explicitly and the compiler contracts nothing else in them (contraction off), so each
@@ -191,6 +195,29 @@ __device__ __forceinline__ InvS2<float> inv_s2_of(const SearchArgs& a) {
     r.yz = a.inv_s2[5];
     r.xyz = a.inv_s2[6];
     return r;
+}
+
+// The reciprocals in T (FP64: formed by the host too).
+template <typename T>
+__device__ __forceinline__ InvS2<T> inv_s2_for(const SearchArgs& a) {
+    if constexpr (sizeof(T) == 8) {
+        InvS2<double> r;
+        r.x = a.inv_s2d[0];
+        r.y = a.inv_s2d[1];
+        r.z = a.inv_s2d[2];
+        r.xy = a.inv_s2d[3];
+        r.xz = a.inv_s2d[4];
+        r.yz = a.inv_s2d[5];
+        r.xyz = a.inv_s2d[6];
+        return r;
+    } else {
+        return inv_s2_of(a);
+    }
+}
+
+// 1 / dD of a node in the FP64 paths.
+__device__ __forceinline__ double fp64_inv_dd(const SearchArgs& a, float dr) {
+    return a.local ? 1.0 / (a.dd64 * (double)dr) : 1.0 / (a.dd64 * (double)ord_to_float(a.sc->dmax_ord));
 }
 
 // Tetrahedron of a 3D cell redone in FP64 (the precision guard).  The four corner doses
@@ -686,13 +713,14 @@ __device__ __forceinline__ uint32_t zero_cells(int DIM, int x, int y, int z, int
 }
 
 // End of a key-0 pass block (all its threads): a finished node's gamma, the block's counts,
-// and the appends of its tail and guard nodes.  The counts of a wave come from ballots (a node
+// and the appends of its tail (with the words bound and key) and guard nodes.  The counts of a wave come from ballots (a node
 // visits at most 8 cells), the waves' from one barrier, and only a block with tail or guard
 // nodes waits for the atomics that give it its slots.  (Two appends and a reduction of five
 // counts by shuffles, with eight barriers between them, took 34.0 and 191 us where this takes
 // 32.3 and 180: 391 thousand nodes at 2.5 mm, 3.1 million at 1.25 mm.)
 __device__ __forceinline__ void zero_epilogue(const SearchArgs& a, BlockSums* bins, uint32_t vb, bool live, int node,
-                                              float F, uint32_t key, uint32_t cells, bool to_tail, bool to_guard) {
+                                              float F, uint32_t bound, uint32_t key, uint32_t cells, bool to_tail,
+                                              bool to_guard) {
     constexpr int WAVES = SEARCH_THREADS / WAVE;
     __shared__ uint32_t s_n[6][WAVES];   // tail, guard, pass, border, cells, max gamma^2
     __shared__ uint32_t s_base[2];
@@ -752,7 +780,7 @@ __device__ __forceinline__ void zero_epilogue(const SearchArgs& a, BlockSums* bi
     if (to_tail) {
         const uint32_t pos = s_base[0] + off[0] + (uint32_t)__popcll(tb & lt);
         a.tail_node[pos] = (uint32_t)node;
-        a.tail_f[pos] = f2u(F);
+        a.tail_f[pos] = bound;
         a.tail_key_arr[pos] = key;
         a.tail_pos[pos] = pos;
     }
@@ -784,42 +812,42 @@ __device__ __forceinline__ void zero_epilogue(const SearchArgs& a, BlockSums* bi
 // SIMD (140 uncapped: 34.7 and 204 us).
 
 // Chain sums at a block stepped before the node (M = 1: mu = -1) or after it (M = 0: mu = 0).
-template <int M>
-__device__ __forceinline__ float near_n(float n, const Step<float>& s) {
+template <int M, typename T>
+__device__ __forceinline__ T near_n(T n, const Step<T>& s) {
 #pragma clang fp contract(off)
     return M ? n + s.d : n;
 }
-template <int M>
-__device__ __forceinline__ float near_t(const Step<float>& s, float L) {
+template <int M, typename T>
+__device__ __forceinline__ T near_t(const Step<T>& s, T L) {
 #pragma clang fp contract(off)
-    return M ? fmadd(-s.w, L, 1.0f) : -(s.w * L);
+    return M ? fmadd(-s.w, L, T(1)) : -(s.w * L);
 }
-template <int M1>
-__device__ __forceinline__ float near1(float g0, const Step<float>& a) {
+template <int M1, typename T>
+__device__ __forceinline__ T near1(T g0, const Step<T>& a) {
 #pragma clang fp contract(off)
-    const float N = near_n<M1>(g0, a);
-    const float L = N * Num<float>::rcp(den_step(1.0f, a));
-    const float t1 = near_t<M1>(a, L);
-    return (t1 >= 0.0f && t1 <= 1.0f) ? N * L : Num<float>::inf();
+    const T N = near_n<M1>(g0, a);
+    const T L = N * Num<T>::rcp(den_step(T(1), a));
+    const T t1 = near_t<M1>(a, L);
+    return (t1 >= T(0) && t1 <= T(1)) ? N * L : Num<T>::inf();
 }
-template <int M1, int M2>
-__device__ __forceinline__ float near2(float g0, const Step<float>& a, const Step<float>& b) {
+template <int M1, int M2, typename T>
+__device__ __forceinline__ T near2(T g0, const Step<T>& a, const Step<T>& b) {
 #pragma clang fp contract(off)
-    const float N = near_n<M2>(near_n<M1>(g0, a), b);
-    const float L = N * Num<float>::rcp(den_step(den_step(1.0f, a), b));
-    const float t1 = near_t<M1>(a, L), t2 = near_t<M2>(b, L);
-    return (t1 <= 1.0f && t1 >= t2 && t2 >= 0.0f) ? N * L : Num<float>::inf();
+    const T N = near_n<M2>(near_n<M1>(g0, a), b);
+    const T L = N * Num<T>::rcp(den_step(den_step(T(1), a), b));
+    const T t1 = near_t<M1>(a, L), t2 = near_t<M2>(b, L);
+    return (t1 <= T(1) && t1 >= t2 && t2 >= T(0)) ? N * L : Num<T>::inf();
 }
-template <int M1, int M2, int M3>
-__device__ __forceinline__ float near3(float g0, const Step<float>& a, const Step<float>& b, const Step<float>& c) {
+template <int M1, int M2, int M3, typename T>
+__device__ __forceinline__ T near3(T g0, const Step<T>& a, const Step<T>& b, const Step<T>& c) {
 #pragma clang fp contract(off)
-    const float N = near_n<M3>(near_n<M2>(near_n<M1>(g0, a), b), c);
-    const float L = N * Num<float>::rcp(den3(a, b, c));
-    const float t1 = near_t<M1>(a, L), t2 = near_t<M2>(b, L), t3 = near_t<M3>(c, L);
-    return (t1 <= 1.0f && t1 >= t2 && t2 >= t3 && t3 >= 0.0f) ? N * L : Num<float>::inf();
+    const T N = near_n<M3>(near_n<M2>(near_n<M1>(g0, a), b), c);
+    const T L = N * Num<T>::rcp(den3(a, b, c));
+    const T t1 = near_t<M1>(a, L), t2 = near_t<M2>(b, L), t3 = near_t<M3>(c, L);
+    return (t1 <= T(1) && t1 >= t2 && t2 >= t3 && t3 >= T(0)) ? N * L : Num<T>::inf();
 }
-template <int S>
-__device__ __forceinline__ float inv_of(const InvS2<float>& is) {
+template <int S, typename T>
+__device__ __forceinline__ T inv_of(const InvS2<T>& is) {
     if constexpr (S == 1) return is.x;
     else if constexpr (S == 2) return is.y;
     else if constexpr (S == 4) return is.z;
@@ -829,75 +857,79 @@ __device__ __forceinline__ float inv_of(const InvS2<float>& is) {
     else return is.xyz;
 }
 // Step from vertex U of the cell along block S.
-template <int U, int S>
-__device__ __forceinline__ Step<float> near_step(const float* g, const InvS2<float>& is) {
+template <int U, int S, typename T>
+__device__ __forceinline__ Step<T> near_step(const T* g, const InvS2<T>& is) {
     static_assert((U & S) == 0, "a chain steps away from its start");
     return mk_step(g[U | S], g[U], inv_of<S>(is));
 }
 // Smallest dist^2 over the near faces of the cell that holds the node at corner V (V = 0: but
 // the node itself).  A, B, C: the axes, V = A, A | B, 7 or 0.
-template <int V, int A, int B, int C>
-__device__ __forceinline__ float near_faces(const float* g, const InvS2<float>& is) {
-    const float g0 = g[0];
+template <int V, int A, int B, int C, typename T>
+__device__ __forceinline__ T near_faces(const T* g, const InvS2<T>& is) {
+    const T g0 = g[0];
     if constexpr (V == A) {
-        const Step<float> a = near_step<0, A>(g, is), ab = near_step<A, B>(g, is), ac = near_step<A, C>(g, is);
-        float r = vmin<float>(near1<1>(g0, a), near2<1, 0>(g0, a, near_step<A, (B | C)>(g, is)));
-        r = vmin<float>(r, vmin<float>(near2<1, 0>(g0, a, ab), near2<1, 0>(g0, a, ac)));
-        return vmin<float>(r, vmin<float>(near3<1, 0, 0>(g0, a, ab, near_step<(A | B), C>(g, is)),
+        const Step<T> a = near_step<0, A>(g, is), ab = near_step<A, B>(g, is), ac = near_step<A, C>(g, is);
+        T r = vmin<T>(near1<1>(g0, a), near2<1, 0>(g0, a, near_step<A, (B | C)>(g, is)));
+        r = vmin<T>(r, vmin<T>(near2<1, 0>(g0, a, ab), near2<1, 0>(g0, a, ac)));
+        return vmin<T>(r, vmin<T>(near3<1, 0, 0>(g0, a, ab, near_step<(A | B), C>(g, is)),
                                           near3<1, 0, 0>(g0, a, ac, near_step<(A | C), B>(g, is))));
     } else if constexpr (V == (A | B)) {
-        const Step<float> a = near_step<0, A>(g, is), b = near_step<0, B>(g, is), e = near_step<0, (A | B)>(g, is);
-        const Step<float> ab = near_step<A, B>(g, is), ba = near_step<B, A>(g, is), c = near_step<(A | B), C>(g, is);
-        float r = vmin<float>(near1<1>(g0, e), near2<1, 0>(g0, e, c));
-        r = vmin<float>(r, vmin<float>(near2<1, 1>(g0, a, ab), near2<1, 1>(g0, b, ba)));
-        return vmin<float>(r, vmin<float>(near3<1, 1, 0>(g0, a, ab, c), near3<1, 1, 0>(g0, b, ba, c)));
+        const Step<T> a = near_step<0, A>(g, is), b = near_step<0, B>(g, is), e = near_step<0, (A | B)>(g, is);
+        const Step<T> ab = near_step<A, B>(g, is), ba = near_step<B, A>(g, is), c = near_step<(A | B), C>(g, is);
+        T r = vmin<T>(near1<1>(g0, e), near2<1, 0>(g0, e, c));
+        r = vmin<T>(r, vmin<T>(near2<1, 1>(g0, a, ab), near2<1, 1>(g0, b, ba)));
+        return vmin<T>(r, vmin<T>(near3<1, 1, 0>(g0, a, ab, c), near3<1, 1, 0>(g0, b, ba, c)));
     } else {
         constexpr int M = V == 7 ? 1 : 0;
-        const Step<float> x = near_step<0, 1>(g, is), y = near_step<0, 2>(g, is), z = near_step<0, 4>(g, is);
-        const Step<float> xy = near_step<0, 3>(g, is), xz = near_step<0, 5>(g, is), yz = near_step<0, 6>(g, is);
-        const Step<float> x_y = near_step<1, 2>(g, is), x_z = near_step<1, 4>(g, is), y_x = near_step<2, 1>(g, is);
-        const Step<float> y_z = near_step<2, 4>(g, is), z_x = near_step<4, 1>(g, is), z_y = near_step<4, 2>(g, is);
-        const Step<float> xy_z = near_step<3, 4>(g, is), xz_y = near_step<5, 2>(g, is), yz_x = near_step<6, 1>(g, is);
-        float r = near1<M>(g0, near_step<0, 7>(g, is));
-        r = vmin<float>(r, vmin<float>(near2<M, M>(g0, x, near_step<1, 6>(g, is)), near2<M, M>(g0, yz, yz_x)));
-        r = vmin<float>(r, vmin<float>(near2<M, M>(g0, y, near_step<2, 5>(g, is)), near2<M, M>(g0, xz, xz_y)));
-        r = vmin<float>(r, vmin<float>(near2<M, M>(g0, z, near_step<4, 3>(g, is)), near2<M, M>(g0, xy, xy_z)));
-        r = vmin<float>(r, vmin<float>(near3<M, M, M>(g0, x, x_y, xy_z), near3<M, M, M>(g0, x, x_z, xz_y)));
-        r = vmin<float>(r, vmin<float>(near3<M, M, M>(g0, y, y_x, xy_z), near3<M, M, M>(g0, y, y_z, yz_x)));
-        r = vmin<float>(r, vmin<float>(near3<M, M, M>(g0, z, z_x, xz_y), near3<M, M, M>(g0, z, z_y, yz_x)));
+        const Step<T> x = near_step<0, 1>(g, is), y = near_step<0, 2>(g, is), z = near_step<0, 4>(g, is);
+        const Step<T> xy = near_step<0, 3>(g, is), xz = near_step<0, 5>(g, is), yz = near_step<0, 6>(g, is);
+        const Step<T> x_y = near_step<1, 2>(g, is), x_z = near_step<1, 4>(g, is), y_x = near_step<2, 1>(g, is);
+        const Step<T> y_z = near_step<2, 4>(g, is), z_x = near_step<4, 1>(g, is), z_y = near_step<4, 2>(g, is);
+        const Step<T> xy_z = near_step<3, 4>(g, is), xz_y = near_step<5, 2>(g, is), yz_x = near_step<6, 1>(g, is);
+        T r = near1<M>(g0, near_step<0, 7>(g, is));
+        r = vmin<T>(r, vmin<T>(near2<M, M>(g0, x, near_step<1, 6>(g, is)), near2<M, M>(g0, yz, yz_x)));
+        r = vmin<T>(r, vmin<T>(near2<M, M>(g0, y, near_step<2, 5>(g, is)), near2<M, M>(g0, xz, xz_y)));
+        r = vmin<T>(r, vmin<T>(near2<M, M>(g0, z, near_step<4, 3>(g, is)), near2<M, M>(g0, xy, xy_z)));
+        r = vmin<T>(r, vmin<T>(near3<M, M, M>(g0, x, x_y, xy_z), near3<M, M, M>(g0, x, x_z, xz_y)));
+        r = vmin<T>(r, vmin<T>(near3<M, M, M>(g0, y, y_x, xy_z), near3<M, M, M>(g0, y, y_z, yz_x)));
+        r = vmin<T>(r, vmin<T>(near3<M, M, M>(g0, z, z_x, xz_y), near3<M, M, M>(g0, z, z_y, yz_x)));
         if constexpr (V == 0) {
-            r = vmin<float>(r, vmin<float>(near1<0>(g0, x), vmin<float>(near1<0>(g0, y), near1<0>(g0, z))));
-            r = vmin<float>(r, vmin<float>(near1<0>(g0, xy), vmin<float>(near1<0>(g0, xz), near1<0>(g0, yz))));
-            r = vmin<float>(r, vmin<float>(near2<0, 0>(g0, x, x_y), near2<0, 0>(g0, y, y_x)));
-            r = vmin<float>(r, vmin<float>(near2<0, 0>(g0, x, x_z), near2<0, 0>(g0, z, z_x)));
-            r = vmin<float>(r, vmin<float>(near2<0, 0>(g0, y, y_z), near2<0, 0>(g0, z, z_y)));
+            r = vmin<T>(r, vmin<T>(near1<0>(g0, x), vmin<T>(near1<0>(g0, y), near1<0>(g0, z))));
+            r = vmin<T>(r, vmin<T>(near1<0>(g0, xy), vmin<T>(near1<0>(g0, xz), near1<0>(g0, yz))));
+            r = vmin<T>(r, vmin<T>(near2<0, 0>(g0, x, x_y), near2<0, 0>(g0, y, y_x)));
+            r = vmin<T>(r, vmin<T>(near2<0, 0>(g0, x, x_z), near2<0, 0>(g0, z, z_x)));
+            r = vmin<T>(r, vmin<T>(near2<0, 0>(g0, y, y_z), near2<0, 0>(g0, z, z_y)));
         }
         return r;
     }
 }
 // Corners of key-0 cell c = 4 (az + 1) + 2 (ay + 1) + (ax + 1) from the 3 x 3 x 3 neighbourhood.
-template <int C>
-__device__ __forceinline__ void zero_corners(const float* g27, float* g) {
+template <int C, typename T>
+__device__ __forceinline__ void zero_corners(const T* g27, T* g) {
 #pragma unroll
     for (int b = 0; b < 8; ++b)
         g[b] = g27[((C >> 2) + (b >> 2)) * 9 + (((C >> 1) & 1) + ((b >> 1) & 1)) * 3 + (C & 1) + (b & 1)];
 }
-template <int C, int V, int A, int B, int CC>
-__device__ __forceinline__ float zero_near(const float* g27, const InvS2<float>& is) {
+template <int C, int V, int A, int B, int CC, typename T>
+__device__ __forceinline__ T zero_near(const T* g27, const InvS2<T>& is) {
     static_assert((C ^ 7) == V, "the node's corner");
-    float g[8];
+    T g[8];
     zero_corners<C>(g27, g);
     return near_faces<V, A, B, CC>(g, is);
 }
 
-// MODE 0: FP32; MODE 1: FP32 and flag ill-conditioned tetrahedra.
-// vb: the block's index in the node list (256 nodes each).
+// MODE 0: FP32; MODE 1: FP32 and flag ill-conditioned tetrahedra; MODE 3: FP64 (a tail node's
+// bound is left as a double in tail_f and tail_key_arr).  vb: the block's index in the node list (256 nodes each).
 template <int MODE>
 __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& zg, BlockSums* sums, uint32_t vb) {
     constexpr int GMODE = MODE == 1 ? 1 : 0;
+    using T = typename std::conditional<MODE == 3, double, float>::type;
+    using U = typename std::conditional<MODE == 3, unsigned long long, uint32_t>::type;
     constexpr int WAVES = SEARCH_THREADS / WAVE;
-    __shared__ float s_g[WAVES][27][WAVE];          // normalised neighbourhoods of the wave's nodes
-    __shared__ uint32_t s_f[WAVES][WAVE];           // their F (non-negative float bits)
+    __shared__ float s_g[WAVES][27][WAVE];          // neighbourhoods of the wave's nodes, normalised (FP64: doses)
+    __shared__ U s_f[WAVES][WAVE];                  // their F (non-negative bits)
+    __shared__ float s_dr[MODE == 3 ? WAVES : 1][WAVE];
+    __shared__ double s_inv[MODE == 3 ? WAVES : 1][WAVE];
     __shared__ uint16_t s_item[WAVES][8 * WAVE];    // queued cells: node's lane | cell << 6
     __shared__ uint8_t s_up[WAVES][WAVE];           // bit i: the grid goes on past the node along axis i
     __shared__ TabEntry s_zero[8];
@@ -915,43 +947,54 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
     const uint32_t yz = fast_div((uint32_t)node, a.div_nx);
     const int z = (int)fast_div(yz, a.div_ny), y = (int)yz - z * ny, x = node - (int)yz * nx;
     const float dr = a.ref[node];
-    const float inv_dd = node_inv_dd(dr, a.sc->inv_dd, a.dd, a.local);
+    T inv_dd;
+    if constexpr (MODE == 3) inv_dd = fp64_inv_dd(a, dr);
+    else inv_dd = node_inv_dd(dr, a.sc->inv_dd, a.dd, a.local);
     // neighbourhood offsets, clamped at the grid faces (clamped values feed only cells
     // that do not exist or faces that are masked out)
     const int oxm = x > 0 ? -1 : 0, oxp = x + 1 < nx ? 1 : 0;
     const int oym = y > 0 ? -nx : 0, oyp = y + 1 < ny ? nx : 0;
     const int ozm = z > 0 ? -sxy : 0, ozp = z + 1 < nz ? sxy : 0;
     const int ox[3] = {oxm, 0, oxp}, oy[3] = {oym, 0, oyp}, oz[3] = {ozm, 0, ozp};
-    float g27[27];
-#pragma unroll
-    for (int k = 0; k < 27; ++k) g27[k] = a.ev[node + oz[k / 9] + oy[(k / 3) % 3] + ox[k % 3]];
-#pragma unroll
-    for (int k = 0; k < 27; ++k) g27[k] = dose_norm<float>(g27[k], dr, inv_dd);
-    const float F0 = live ? g27[13] * g27[13] : 0.0f;   // gamma0^2
-
-    const InvS2<float> is = inv_s2_of(a);
-    const bool bnd = oxm == 0 || oxp == 0 || oym == 0 || oyp == 0 || ozm == 0 || ozp == 0;
-    const bool open = live && F0 > 0.0f;   // a node of dose difference 0 visits no cell
-    float F = F0;
+    T g27[27];
     {
-        float r = zero_near<7, 0, 1, 2, 4>(g27, is);
-        r = vmin<float>(r, zero_near<6, 1, 1, 2, 4>(g27, is));
-        r = vmin<float>(r, zero_near<5, 2, 2, 1, 4>(g27, is));
-        r = vmin<float>(r, zero_near<3, 4, 4, 1, 2>(g27, is));
-        r = vmin<float>(r, zero_near<4, 3, 1, 2, 4>(g27, is));
-        r = vmin<float>(r, zero_near<2, 5, 1, 4, 2>(g27, is));
-        r = vmin<float>(r, zero_near<1, 6, 2, 4, 1>(g27, is));
-        r = vmin<float>(r, zero_near<0, 7, 1, 2, 4>(g27, is));
-        F = open && !bnd ? vmin<float>(F, r) : F;
+        float v[27];
+#pragma unroll
+        for (int k = 0; k < 27; ++k) v[k] = a.ev[node + oz[k / 9] + oy[(k / 3) % 3] + ox[k % 3]];
+        if constexpr (MODE == 3) {
+#pragma unroll
+            for (int k = 0; k < 27; ++k) s_g[wv][k][lane] = v[k];
+            s_dr[wv][lane] = dr;
+            s_inv[wv][lane] = inv_dd;
+        }
+#pragma unroll
+        for (int k = 0; k < 27; ++k) g27[k] = dose_norm<T>((T)v[k], (T)dr, inv_dd);
+    }
+    const T F0 = live ? g27[13] * g27[13] : T(0);   // gamma0^2
+
+    const InvS2<T> is = inv_s2_for<T>(a);
+    const bool bnd = oxm == 0 || oxp == 0 || oym == 0 || oyp == 0 || ozm == 0 || ozp == 0;
+    const bool open = live && F0 > T(0);   // a node of dose difference 0 visits no cell
+    T F = F0;
+    {
+        T r = zero_near<7, 0, 1, 2, 4>(g27, is);
+        r = vmin<T>(r, zero_near<6, 1, 1, 2, 4>(g27, is));
+        r = vmin<T>(r, zero_near<5, 2, 2, 1, 4>(g27, is));
+        r = vmin<T>(r, zero_near<3, 4, 4, 1, 2>(g27, is));
+        r = vmin<T>(r, zero_near<4, 3, 1, 2, 4>(g27, is));
+        r = vmin<T>(r, zero_near<2, 5, 1, 4, 2>(g27, is));
+        r = vmin<T>(r, zero_near<1, 6, 2, 4, 1>(g27, is));
+        r = vmin<T>(r, zero_near<0, 7, 1, 2, 4>(g27, is));
+        F = open && !bnd ? vmin<T>(F, r) : F;
     }
     // a neighbourhood whose doses span less than this holds no ill-conditioned tetrahedron
     bool suspect = false;
     if constexpr (MODE == 1) {
-        float lo = g27[0], hi = g27[0];
+        T lo = g27[0], hi = g27[0];
 #pragma unroll
         for (int k = 1; k < 27; ++k) {
-            lo = vmin<float>(lo, g27[k]);
-            hi = __builtin_fmaxf(hi, g27[k]);
+            lo = vmin<T>(lo, g27[k]);
+            hi = vmax<T>(hi, g27[k]);
         }
         suspect = open && !((hi - lo) * (hi - lo) < a.ill_span2);
     }
@@ -966,49 +1009,58 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
                 (uint16_t)(lane | (c << 6));
         q += (uint32_t)__popcll(mask);
     };
-    const float Fm = F + F * 0x1p-8f;
+    const T Fm = F + F * T(0x1p-8);
     const bool edge = open && bnd, inner = open && !bnd;
-    if (__ballot(edge || (inner && zg.far2_min < Fm)) != 0ull) {
+    if (__ballot(edge || (inner && (T)zg.far2_min < Fm)) != 0ull) {
         // corner ranges of the eight cells, pairs along x, then y, then z
-        float lo[18], hi[18];
+        T lo[18], hi[18];
 #pragma unroll
         for (int k = 0; k < 18; ++k) {
             const int r = k >> 1, p = 3 * r + (k & 1);
-            lo[k] = vmin<float>(g27[p], g27[p + 1]);
-            hi[k] = __builtin_fmaxf(g27[p], g27[p + 1]);
+            lo[k] = vmin<T>(g27[p], g27[p + 1]);
+            hi[k] = vmax<T>(g27[p], g27[p + 1]);
         }
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             const int k = ((c >> 2) * 3 + ((c >> 1) & 1)) * 2 + (c & 1);   // pair (z, y, x) of the cell
-            const float l = vmin<float>(vmin<float>(lo[k], lo[k + 2]), vmin<float>(lo[k + 6], lo[k + 8]));
-            const float h = __builtin_fmaxf(__builtin_fmaxf(hi[k], hi[k + 2]), __builtin_fmaxf(hi[k + 6], hi[k + 8]));
-            const float m = __builtin_fmaxf(__builtin_fmaxf(l, -h), 0.0f);
+            const T l = vmin<T>(vmin<T>(lo[k], lo[k + 2]), vmin<T>(lo[k + 6], lo[k + 8]));
+            const T h = vmax<T>(vmax<T>(hi[k], hi[k + 2]), vmax<T>(hi[k + 6], hi[k + 8]));
+            const T m = vmax<T>(vmax<T>(l, -h), T(0));
             const bool there = ((c & 1) || oxm != 0) && ((c & 2) || oym != 0) && ((c & 4) || ozm != 0);
-            push((inner && c != 7 && fmadd(m, m, zg.far2[c]) < Fm) || (edge && there), c);
+            push((inner && c != 7 && fmadd(m, m, (T)zg.far2[c]) < Fm) || (edge && there), c);
         }
     }
     bool redo = suspect;
     if (q != 0u || __ballot(redo) != 0ull) {
+        if constexpr (MODE != 3) {
 #pragma unroll
-        for (int k = 0; k < 27; ++k) s_g[wv][k][lane] = g27[k];
-        s_f[wv][lane] = f2u(F);
+            for (int k = 0; k < 27; ++k) s_g[wv][k][lane] = g27[k];
+        }
+        s_f[wv][lane] = __builtin_bit_cast(U, F);
         s_up[wv][lane] = (uint8_t)((oxp ? 1 : 0) | (oyp ? 2 : 0) | (ozp ? 4 : 0));
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     uint32_t n_fp64 = 0;
     GuardCtx gc{};
     // cell c of the node of lane nl, all faces it owns
-    auto cell_of = [&](int nl, int c, bool mask, auto gmode, bool& ill) -> float {
+    auto cell_of = [&](int nl, int c, bool mask, auto gmode, bool& ill) -> T {
         const float(*gn)[WAVE] = s_g[wv] + (((c >> 2) * 3 + ((c >> 1) & 1)) * 3 + (c & 1));
-        float g[8];
+        T g[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b) g[b] = gn[(b >> 2) * 9 + ((b >> 1) & 1) * 3 + (b & 1)][nl];
-        const Geo<float> G = geo_from_row(s_zero[c]);
+        Geo<T> G;
+        if constexpr (MODE == 3) {
+            const T dn = s_dr[wv][nl], in = s_inv[wv][nl];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) g[b] = dose_norm<T>(g[b], dn, in);
+            G = geo_fp64((c & 1) - 1, ((c >> 1) & 1) - 1, (c >> 2) - 1, a.sx * a.sx, a.sy * a.sy, a.sz * a.sz);
+        } else {
+            G = geo_from_row(s_zero[c]);
+        }
         const uint32_t up = s_up[wv][nl] | ~(uint32_t)c;   // a cell at -1 reaches back to the node
         if (mask)
-            return cell3<float, true, decltype(gmode)::value>(g, G, is, up & 1u, up & 2u, up & 4u, a.den_guard, gc, n_fp64,
-                                                               ill);
-        return cell3<float, false, decltype(gmode)::value>(g, G, is, true, true, true, a.den_guard, gc, n_fp64, ill);
+            return cell3<T, true, decltype(gmode)::value>(g, G, is, up & 1u, up & 2u, up & 4u, (T)a.den_guard, gc, n_fp64, ill);
+        return cell3<T, false, decltype(gmode)::value>(g, G, is, true, true, true, (T)a.den_guard, gc, n_fp64, ill);
     };
     bool ill = false;
     if (q != 0u) {
@@ -1020,21 +1072,23 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
             const bool whole = ((s_up[wv][nl] | ~(uint32_t)c) & 7u) == 7u;
             const bool mask = __ballot(on && !whole) != 0ull;
             if (on) {
-                const float v = cell_of(nl, c, mask, std::integral_constant<int, 0>{}, ill);
-                atomicMin(&s_f[wv][nl], f2u(v));
+                const T v = cell_of(nl, c, mask, std::integral_constant<int, 0>{}, ill);
+                atomicMin(&s_f[wv][nl], __builtin_bit_cast(U, v));
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        F = u2f(s_f[wv][lane]);
+        F = __builtin_bit_cast(T, s_f[wv][lane]);
     }
     uint32_t cells = open ? zero_cells(3, x, y, z, nx, ny, nz) : 0u;
     // rare: the tetrahedra of a steep neighbourhood are judged, and a node whose F fell to 0
     // counts the cells up to there, cell by cell in table order
-    const bool zero = open && F == 0.0f;
+    const bool zero = open && F == T(0);
     if (__ballot(redo || zero) != 0ull) {
         if (q == 0u && __ballot(redo) == 0ull) {
+            if constexpr (MODE != 3) {
 #pragma unroll
-            for (int k = 0; k < 27; ++k) s_g[wv][k][lane] = g27[k];
+                for (int k = 0; k < 27; ++k) s_g[wv][k][lane] = g27[k];
+            }
             s_up[wv][lane] = (uint8_t)((oxp ? 1 : 0) | (oyp ? 2 : 0) | (ozp ? 4 : 0));
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
@@ -1046,14 +1100,23 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
                 const bool there = ((c & 1) || oxm != 0) && ((c & 2) || oym != 0) && ((c & 4) || ozm != 0);
                 if (!there) continue;
                 const bool whole = (!(c & 1) || oxp != 0) && (!(c & 2) || oyp != 0) && (!(c & 4) || ozp != 0);
-                cells += F > 0.0f && whole ? 1u : 0u;
-                F = vmin<float>(F, cell_of(lane, c, true, std::integral_constant<int, GMODE>{}, ill));
+                cells += F > T(0) && whole ? 1u : 0u;
+                F = vmin<T>(F, cell_of(lane, c, true, std::integral_constant<int, GMODE>{}, ill));
             }
         }
     }
     const bool to_guard = MODE == 1 && ill && open;
-    const bool to_tail = live && !to_guard && F > a.k1;
-    zero_epilogue(a, sums, vb, live, node, F, tail_sort_key(a, node, F0, F), cells, to_tail, to_guard);
+    const bool to_tail = live && !to_guard && F > (T)a.k1;
+    if constexpr (MODE == 3) {
+        const unsigned long long fb = __builtin_bit_cast(unsigned long long, F);
+        zero_epilogue(a, sums, vb, live, node, (float)F, (uint32_t)fb, (uint32_t)(fb >> 32), cells, to_tail, false);
+    } else {
+        zero_epilogue(a, sums, vb, live, node, F, f2u(F), tail_sort_key(a, node, F0, F), cells, to_tail, to_guard);
+    }
+}
+
+__global__ __launch_bounds__(SEARCH_THREADS) void k_zero3_fp64(SearchArgs a, ZeroGeo zg, BlockSums* sums) {
+    zero3_body<3>(a, zg, sums, blockIdx.x);
 }
 
 template <int MODE>
@@ -1768,11 +1831,13 @@ __global__ __launch_bounds__(SEARCH_THREADS) void k_cell_range(const float* __re
                                                                float2* __restrict__ range) {
     if (*count < least) return;
     const int64_t sxy = (int64_t)nx * ny;
-    const int64_t c = (int64_t)blockIdx.x * SEARCH_THREADS + threadIdx.x;
+    const uint32_t cols = (uint32_t)((sxy + SEARCH_THREADS - 1) / SEARCH_THREADS);
+    const uint32_t zb = blockIdx.x / cols;
+    const int64_t c = (int64_t)(blockIdx.x - zb * cols) * SEARCH_THREADS + threadIdx.x;
     if (c >= sxy) return;
     const int x = (int)(c % nx), y = (int)(c / nx);
     const int ox = x + 1 < nx ? 1 : 0, oy = y + 1 < ny ? nx : 0;
-    const int z0 = blockIdx.y * RANGE_Z;
+    const int z0 = (int)zb * RANGE_Z;
     float v[RANGE_Z + 1][4];
 #pragma unroll
     for (int k = 0; k <= RANGE_Z; ++k) {
@@ -1799,7 +1864,8 @@ __global__ __launch_bounds__(SEARCH_THREADS) void k_cell_range(const float* __re
 struct alignas(16) TqNode {
     int x, y, z, node;
     float dr, inv_dd;
-    uint32_t f;      // F (non-negative float bits: an unsigned minimum is the float minimum)
+    uint32_t f;      // F (non-negative float bits: an unsigned minimum is the float minimum; FP64:
+                     // rounded up, which every float key is below exactly when it is below F)
     uint32_t inner;  // every cell with key below F lies inside the grid, whole
 };
 
@@ -1808,7 +1874,11 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
                                                 const uint32_t* __restrict__ order, uint32_t M, int first,
                                                 BlockSums* sums, uint32_t vb, uint32_t vgrid) {
     constexpr int NV = DIM == 3 ? 8 : 4;
+    constexpr bool FP64 = MODE == 3;
+    using T = typename std::conditional<FP64, double, float>::type;
     __shared__ TqNode s_node[TQ_GROUPS];
+    __shared__ unsigned long long s_f64[FP64 ? TQ_GROUPS : 1];   // FP64: F and 1 / dD of a group's node
+    __shared__ double s_inv64[FP64 ? TQ_GROUPS : 1];
     __shared__ uint2 s_queue[SEARCH_THREADS / WAVE][TQ_RING];   // row | group of the wave << 28, bound
     __shared__ TabEntry s_tab[TQ_TAB];
     __shared__ uint2 s_head[TQ_TAB];                            // key^2, offset in nodes
@@ -1819,7 +1889,8 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
     TqNode& self = wnode[lane / TQ_LANES];
     const int nx = a.nx, ny = a.ny, nz = a.nz, sxy = nx * ny;
     const float inv_dd_g = a.sc->inv_dd;
-    const InvS2<float> is = inv_s2_of(a);
+    const InvS2<T> is = inv_s2_for<T>(a);
+    const int wgrp = FP64 ? (threadIdx.x / WAVE) * (WAVE / TQ_LANES) : 0;   // first group of the wave
     const bool ranges = a.range != nullptr && M >= a.range_min;   // (N < 2^29: byte offsets fit 32 bits)
     uint32_t cells = 0, gm = 0, npass = 0, nborder = 0, long_rows = 0;
     GuardCtx gc{};
@@ -1860,12 +1931,14 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
     // the group's next node, loaded while the current one is walked: its dose one iteration
     // after its index, so that no load waits for another
     int p_node = 0;
+    uint32_t p_hi = 0;   // FP64: high word of the bound
     float p_f = 0.0f, p_dr = 0.0f;
     bool p_have = i < M, p_fresh = true;
     if (p_have) {
         const uint32_t item = order ? order[i] : i;
         p_node = (int)a.tail_node[item];
         p_f = u2f(a.tail_f[item]);
+        if constexpr (FP64) p_hi = a.tail_key_arr[item];
     }
 
     // One scan step.  KIND 0: each group its own node's rows, all in LDS and every cell inside
@@ -1960,7 +2033,7 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
                     for (int b = 0; b < 8; ++b)
                         g[b] = dose_norm<float>(a.ev[c0 + (b & 1) + ((b >> 1) & 1) * nx + ((b >> 2) & 1) * sxy], nd.dr,
                                                 nd.inv_dd);
-                    if (tets_ill(g, is, a.den_guard)) bad_key = vmin<float>(bad_key, __builtin_bit_cast(float, e.x));
+                    if (tets_ill(g, inv_s2_of(a), a.den_guard)) bad_key = vmin<float>(bad_key, __builtin_bit_cast(float, e.x));
                 }
                 if (KIND == 2)
                     for (int o = WAVE / 2; o > 0; o >>= 1) bad_key = vmin<float>(bad_key, __shfl_xor(bad_key, o));
@@ -1999,6 +2072,12 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
                 const int cz = DIM == 3 ? min(nz - 2 - z, z - 1) : cx;
                 const float fx = (float)cx, fy = (float)cy, fz = (float)cz;
                 const float lim = vmin<float>(a.s2x * (fx * fx), vmin<float>(a.s2y * (fy * fy), DIM == 3 ? a.s2z * (fz * fz) : Num<float>::inf()));
+                if constexpr (FP64) {
+                    const unsigned long long fb = ((unsigned long long)p_hi << 32) | f2u(p_f);
+                    s_f64[wgrp + lane / TQ_LANES] = fb;
+                    s_inv64[wgrp + lane / TQ_LANES] = fp64_inv_dd(a, p_dr);
+                    p_f = __double2float_ru(__builtin_bit_cast(double, fb));
+                }
                 const bool inner = cx > 0 && cy > 0 && cz > 0 && p_f < lim * 0.999f;
                 self = TqNode{x, y, z, p_node, p_dr, node_inv_dd(p_dr, inv_dd_g, a.dd, a.local), f2u(p_f), inner ? 1u : 0u};
             }
@@ -2014,6 +2093,7 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
                 const uint32_t item = order ? order[i] : i;
                 p_node = (int)a.tail_node[item];
                 p_f = u2f(a.tail_f[item]);
+                if constexpr (FP64) p_hi = a.tail_key_arr[item];
                 p_fresh = true;
             }
         }
@@ -2065,33 +2145,46 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
             if (proj) {
                 const int b0 = (DIM == 3 ? qz * sxy : 0) + qy * nx + qx;
                 const int ox = okx ? 1 : 0, oy = oky ? nx : 0, oz = (DIM == 3 && okz) ? sxy : 0;
-                float g[NV];
-                g[0] = a.ev[b0];
-                g[1] = a.ev[b0 + ox];
-                g[2] = a.ev[b0 + oy];
-                g[3] = a.ev[b0 + oy + ox];
+                float v[NV];
+                v[0] = a.ev[b0];
+                v[1] = a.ev[b0 + ox];
+                v[2] = a.ev[b0 + oy];
+                v[3] = a.ev[b0 + oy + ox];
                 if constexpr (DIM == 3) {
-                    g[4] = a.ev[b0 + oz];
-                    g[5] = a.ev[b0 + oz + ox];
-                    g[6] = a.ev[b0 + oz + oy];
-                    g[7] = a.ev[b0 + oz + oy + ox];
+                    v[4] = a.ev[b0 + oz];
+                    v[5] = a.ev[b0 + oz + ox];
+                    v[6] = a.ev[b0 + oz + oy];
+                    v[7] = a.ev[b0 + oz + oy + ox];
                 }
+                T inv = nd.inv_dd;
+                Geo<T> Gm;
+                if constexpr (FP64) {
+                    inv = s_inv64[wgrp + (int)((it.x >> 28) & 7u)];
+                    Gm = geo_fp64(e.ax, e.ay, e.az, a.sx * a.sx, a.sy * a.sy, DIM == 3 ? a.sz * a.sz : 0.0);
+                } else {
+                    Gm = geo_from_row(e);
+                }
+                T g[NV];
 #pragma unroll
-                for (int b = 0; b < NV; ++b) g[b] = dose_norm<float>(g[b], nd.dr, nd.inv_dd);
-                const Geo<float> Gm = geo_from_row(e);
-                float c;
+                for (int b = 0; b < NV; ++b) g[b] = dose_norm<T>((T)v[b], (T)nd.dr, inv);
+                T c;
                 if constexpr (DIM == 3) {
                     if (wave_masked)
-                        c = cell3<float, true, 0>(g, Gm, is, okx, oky, okz, a.den_guard, gc, dummy_fp64, dummy_ill);
+                        c = cell3<T, true, 0>(g, Gm, is, okx, oky, okz, (T)a.den_guard, gc, dummy_fp64, dummy_ill);
                     else
-                        c = cell3<float, false, 0>(g, Gm, is, true, true, true, a.den_guard, gc, dummy_fp64, dummy_ill);
+                        c = cell3<T, false, 0>(g, Gm, is, true, true, true, (T)a.den_guard, gc, dummy_fp64, dummy_ill);
                 } else {
                     if (wave_masked)
-                        c = cell2<float, true>(g, Gm, is, okx, oky);
+                        c = cell2<T, true>(g, Gm, is, okx, oky);
                     else
-                        c = cell2<float, false>(g, Gm, is, true, true);
+                        c = cell2<T, false>(g, Gm, is, true, true);
                 }
-                if (c < F) atomicMin(&owner->f, f2u(c));
+                if constexpr (FP64) {
+                    atomicMin(&s_f64[wgrp + (int)((it.x >> 28) & 7u)], __builtin_bit_cast(unsigned long long, c));
+                    atomicMin(&owner->f, f2u(__double2float_ru(c)));
+                } else if (c < F) {
+                    atomicMin(&owner->f, f2u(c));
+                }
             }
             q_head += take;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -2126,7 +2219,8 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
                 if (n0 > (int)LONG_WALK_ROWS && (uint32_t)n0 > long_rows)   // (it has at most n0 rows)
                     long_rows = max(long_rows, (uint32_t)resume_row(tab, tab_len, 0, F));
                 if (gl == 0 && !to_guard) {
-                    finish_node(a, nd.node, F, npass, nborder, gm);
+                    const float Ff = FP64 ? (float)__builtin_bit_cast(double, s_f64[FP64 ? wgrp + lane / TQ_LANES : 0]) : F;
+                    finish_node(a, nd.node, Ff, npass, nborder, gm);
                     cells += sum + zero_cells(DIM, nd.x, nd.y, nd.z, nx, ny, nz);
                 }
                 have = false;
@@ -2159,6 +2253,10 @@ __device__ __forceinline__ void tail_auto_body(const SearchArgs& a, const uint32
         tail_queue_body<DIM, MODE>(a, a.tab, sorted ? order : nullptr, *count, first, sums, vb, vgrid);
     else
         tail_group_body<DIM, MODE>(a, a.tab, order, count, first, g_req, 0, sums, vb, vgrid);
+}
+
+__global__ __launch_bounds__(SEARCH_THREADS) void k_tail_fp64(SearchArgs a, int first, BlockSums* sums) {
+    tail_queue_body<3, 3>(a, a.tab, nullptr, a.sc->n_tail, first, sums, blockIdx.x, gridDim.x);
 }
 
 template <int DIM, int MODE>
@@ -2337,6 +2435,15 @@ void tail_group(const SearchArgs& a, const uint32_t* order, const uint32_t* coun
     }
 }
 
+// The cell ranges that the queued walk of `count` nodes reads, where the map has them (every
+// launch of that walk comes after this).
+void cell_ranges(const SearchArgs& a, const uint32_t* count, hipStream_t s) {
+    if (!a.range) return;
+    const unsigned cols = (unsigned)(((int64_t)a.nx * a.ny + SEARCH_THREADS - 1) / SEARCH_THREADS);
+    hipLaunchKernelGGL(k_cell_range, dim3(cols * (unsigned)((a.nz + RANGE_Z - 1) / RANGE_Z)), dim3(SEARCH_THREADS), 0, s, a.ev,
+                       a.nx, a.ny, a.nz, count, a.range_min, a.range);
+}
+
 // Pass B over `order` (count on the device): one lane per node (G == 1) or G lanes.
 unsigned tail_pass(const SearchArgs& a, const SearchPlan& p, const uint32_t* order, const uint32_t* count,
                    int first, bool guarded, int spec, unsigned tb, BlockSums* sums, hipStream_t s) {
@@ -2355,11 +2462,7 @@ unsigned tail_pass(const SearchArgs& a, const SearchPlan& p, const uint32_t* ord
     unsigned gb = (p.M + groups - 1) / groups;
     if (gb > kTailBlocks) gb = kTailBlocks;
     if (G < 0 && spec == 0) {
-        if (a.range) {
-            const unsigned cols = (unsigned)(((int64_t)a.nx * a.ny + SEARCH_THREADS - 1) / SEARCH_THREADS);
-            hipLaunchKernelGGL(k_cell_range, dim3(cols, (unsigned)((a.nz + RANGE_Z - 1) / RANGE_Z)), dim3(SEARCH_THREADS), 0,
-                               s, a.ev, a.nx, a.ny, a.nz, count, a.range_min, a.range);
-        }
+        cell_ranges(a, count, s);
         const int sorted = p.hist != nullptr;
         if (p.ndim == 3) {
             if (guarded) hipLaunchKernelGGL((k_tail_auto<3, 1>), dim3(gb), dim3(SEARCH_THREADS), 0, s, a, order, sorted, count, first, G, sums);
@@ -2955,12 +3058,19 @@ hipError_t launch_search(const SearchArgs& a, const SearchPlan& p, hipStream_t s
     BlockSums* sums = a.sums;
     int used = 0;
     if (p.precision == 2) {
-        // FP64 throughout: one walk over all nodes from the first row
-        if (p.ndim == 3) walk<3, 3, false>(a, a.nodes, &a.sc->n_masked, 0, nb, sums, s);
+        // FP64 throughout.  3D: the key-0 pass and the queued walk as in FP32, whatever the
+        // tail's length and layout request (391 thousand nodes at 2.5 mm: one lane per node from
+        // row 0 took 145-400 us by the longest walk of each wave, this 63 + 16); 2D: one walk over all nodes from the
+        // first row
+        if (p.ndim == 3) hipLaunchKernelGGL(k_zero3_fp64, dim3(nb), dim3(SEARCH_THREADS), 0, s, a, p.zero, sums);
         else walk<2, 3, false>(a, a.nodes, &a.sc->n_masked, 0, nb, sums, s);
-        used = (int)nb;
         if (p.ev_shell_end) (void)hipEventRecord(p.ev_shell_end, s);
         if (p.ev_sort_end) (void)hipEventRecord(p.ev_sort_end, s);
+        if (p.ndim == 3 && a.tab_len > 8) {
+            const unsigned gb = (p.M + TQ_GROUPS - 1) / TQ_GROUPS;
+            cell_ranges(a, &a.sc->n_tail, s);
+            hipLaunchKernelGGL(k_tail_fp64, dim3(gb < kTailBlocks ? gb : kTailBlocks), dim3(SEARCH_THREADS), 0, s, a, 8, sums);
+        }
         if (p.ev_tail_end) (void)hipEventRecord(p.ev_tail_end, s);
     } else {
         const bool guarded = p.precision == 1 && p.ndim == 3;
