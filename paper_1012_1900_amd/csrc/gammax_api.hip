@@ -1358,6 +1358,7 @@ gammax_status_t gammax_map_grids(gammax_ctx_t* c, const gammax_problem_t* p, con
     HIPCHK(c, hipSetDevice(c->device));
     if ((st = grow(c, &c->g_work, &c->g_work_cap, 5 * nr)) != GAMMAX_OK) return st;
     if ((st = grow(c, &c->part, &c->part_cap, 2 * MAX_BLOCKS)) != GAMMAX_OK) return st;
+    if ((st = grow(c, &c->sums, &c->sums_cap, SUM_BINS)) != GAMMAX_OK) return st;
     GridsArgs a{};
     a.ref = ref;
     a.ev = ev;
@@ -1390,6 +1391,7 @@ gammax_status_t gammax_map_grids(gammax_ctx_t* c, const gammax_problem_t* p, con
     a.tail_list = c->g_work + 3 * nr;
     a.tail_f = reinterpret_cast<float*>(c->g_work + 4 * nr);
     a.part = c->part;
+    a.sums = c->sums;
     // the lower-key table of the evaluation grid, cached while it reaches far enough
     TableGeom g{};
     g.ndim = 3;
@@ -1411,25 +1413,31 @@ gammax_status_t gammax_map_grids(gammax_ctx_t* c, const gammax_problem_t* p, con
         } else {
             // the 27 key-0 cells one lane per node, then the walk of the nodes left
             if ((e = launch_grids_zero(a, opt.precision, s)) != hipSuccess) return e;
-            if ((e = launch_grids_tail(a, opt.precision, lanes, s)) != hipSuccess) return e;
+            if ((e = launch_grids_tail(a, opt.precision, opt.tail_lanes, s)) != hipSuccess) return e;
         }
-        if (opt.precision == GAMMAX_PREC_GUARDED) return launch_grids_walk(a, opt.precision, true, lanes, s);
-        return hipSuccess;
+        if (opt.precision == GAMMAX_PREC_GUARDED)
+            if ((e = launch_grids_walk(a, opt.precision, true, lanes, s)) != hipSuccess) return e;
+        // the counts, published as a one-grid map's are
+        return launch_grids_finish(a, c->d_seq, c->h_ring, s);
+    };
+    auto collect = [&](int slot) -> hipError_t {
+        ++c->seq;
+        const hipError_t e = hipStreamSynchronize(s);
+        *c->h_sc = c->h_ring[slot];
+        return e;
     };
     bool done = false;
     if (c->g_tab_valid && same_geom(c->g_geom, g)) {
         // a cached table for this geometry: the whole map on it, read back once at the end;
         // if the radius found has outgrown the table, the map runs again below on a new one
-        HIPCHK(c, hipMemsetAsync(c->d_sc, 0, sizeof(Scalars), s));
         HIPCHK(c, launch_grids_prep(a, s));
+        const int slot = claim_ring(c);
         HIPCHK(c, search(c->g_tab, (int)c->g_tab_len, c->g_k1));
-        HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
-        HIPCHK(c, hipStreamSynchronize(s));
+        HIPCHK(c, collect(slot));
         if ((st = scalar_errors(c, *c->h_sc, a.local != 0)) != GAMMAX_OK) return st;
         done = !((double)u2f(c->h_sc->r2_bits) >= c->g_geom.r2_cap && c->h_sc->n_masked > 0);
     }
     if (!done) {
-        HIPCHK(c, hipMemsetAsync(c->d_sc, 0, sizeof(Scalars), s));
         HIPCHK(c, launch_grids_prep(a, s));
         HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
@@ -1445,12 +1453,14 @@ gammax_status_t gammax_map_grids(gammax_ctx_t* c, const gammax_problem_t* p, con
                 c->g_geom = g;
                 c->g_tab_valid = true;
             }
+            const int slot = claim_ring(c);
             HIPCHK(c, search(c->g_tab, (int)c->g_tab_len, c->g_k1));
+            HIPCHK(c, collect(slot));
         } else if (c->h_sc->n_masked > 0) {
+            const int slot = claim_ring(c);
             HIPCHK(c, search(nullptr, 0, INFINITY));
+            HIPCHK(c, collect(slot));
         }
-        HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
-        HIPCHK(c, hipStreamSynchronize(s));
     }
     const float r2 = u2f(c->h_sc->r2_bits);
     if (res) {

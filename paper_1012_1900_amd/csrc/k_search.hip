@@ -282,6 +282,22 @@ __device__ __forceinline__ T dose_norm(T v, T dr, T inv) {
     return (v - dr) * inv;
 }
 
+// The corner doses of a cell whose lower corner has index b0 (a corner past the grid along an
+// axis: the one before it).  The corners of a row are one 8-byte load (4-byte aligned; on the
+// last column the pair before it): four loads per cell where eight gathers touched twice the
+// cache lines.
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+template <int DIM>
+__device__ __forceinline__ void cell_corners(const float* __restrict__ ev, int64_t b0, bool okx, int oy, int oz, float* v) {
+    const float* p = ev + b0 - (okx ? 0 : 1);
+#pragma unroll
+    for (int k = 0; k < (DIM == 3 ? 4 : 2); ++k) {
+        const f32x2u t = *reinterpret_cast<const f32x2u*>(p + ((k & 1) ? oy : 0) + ((k & 2) ? oz : 0));
+        v[2 * k] = okx ? t.x : t.y;
+        v[2 * k + 1] = t.y;
+    }
+}
+
 // Whether any of the six tetrahedra of a 3D cell has a normal-equation denominator above
 // den_guard: the test cell3 applies (GMODE 1), with its chain steps and its summation order.
 __device__ __forceinline__ bool tets_ill(const float* g, const InvS2<float>& is, float den_guard) {
@@ -714,13 +730,25 @@ __device__ __forceinline__ uint32_t zero_cells(int DIM, int x, int y, int z, int
 
 // End of a key-0 pass block (all its threads): a finished node's gamma, the block's counts,
 // and the appends of its tail (with the words bound and key) and guard nodes.  The counts of a wave come from ballots (a node
-// visits at most 8 cells), the waves' from one barrier, and only a block with tail or guard
-// nodes waits for the atomics that give it its slots.  (Two appends and a reduction of five
+// visits at most 27 cells), the waves' from one barrier, and only a block with tail or guard
+// nodes waits for the atomics that give it its slots.  all_cells: the cells of tail nodes are counted
+// here too (two grids).  (Two appends and a reduction of five
 // counts by shuffles, with eight barriers between them, took 34.0 and 191 us where this takes
 // 32.3 and 180: 391 thousand nodes at 2.5 mm, 3.1 million at 1.25 mm.)
-__device__ __forceinline__ void zero_epilogue(const SearchArgs& a, BlockSums* bins, uint32_t vb, bool live, int node,
+__device__ __forceinline__ void append_tail(const SearchArgs& a, uint32_t pos, int node, uint32_t bound, uint32_t key) {
+    a.tail_node[pos] = (uint32_t)node;
+    a.tail_f[pos] = bound;
+    a.tail_key_arr[pos] = key;
+    a.tail_pos[pos] = pos;
+}
+__device__ __forceinline__ void append_tail(const GridsArgs& a, uint32_t pos, int node, uint32_t bound, uint32_t) {
+    a.tail_list[pos] = (uint32_t)node;
+    a.tail_f[pos] = u2f(bound);
+}
+template <typename Args>
+__device__ __forceinline__ void zero_epilogue(const Args& a, BlockSums* bins, uint32_t vb, bool live, int node,
                                               float F, uint32_t bound, uint32_t key, uint32_t cells, bool to_tail,
-                                              bool to_guard) {
+                                              bool to_guard, bool all_cells = false) {
     constexpr int WAVES = SEARCH_THREADS / WAVE;
     __shared__ uint32_t s_n[6][WAVES];   // tail, guard, pass, border, cells, max gamma^2
     __shared__ uint32_t s_base[2];
@@ -731,10 +759,10 @@ __device__ __forceinline__ void zero_epilogue(const SearchArgs& a, BlockSums* bi
     const unsigned long long tb = __ballot(to_tail), gb = __ballot(to_guard);
     const uint32_t npass = (uint32_t)__popcll(__ballot(done && gam <= 1.0f));
     const uint32_t nborder = (uint32_t)__popcll(__ballot(done && fabsf(gam - 1.0f) <= 1e-5f));
-    cells = done ? cells : 0u;
+    cells = done || (all_cells && to_tail) ? cells : 0u;
     uint32_t ncells = 0u;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) ncells += (uint32_t)__popcll(__ballot((cells >> k) & 1u)) << k;
+    for (int k = 0; k < 5; ++k) ncells += (uint32_t)__popcll(__ballot((cells >> k) & 1u)) << k;
     uint32_t gm = done ? f2u(gam * gam) : 0u;
     for (int o = WAVE / 2; o > 0; o >>= 1) gm = max(gm, (uint32_t)__shfl_xor((int)gm, o));
     if (lane == 0) {
@@ -777,13 +805,7 @@ __device__ __forceinline__ void zero_epilogue(const SearchArgs& a, BlockSums* bi
     if (tot[0] + tot[1] == 0u) return;
     __syncthreads();
     const unsigned long long lt = (1ull << lane) - 1ull;
-    if (to_tail) {
-        const uint32_t pos = s_base[0] + off[0] + (uint32_t)__popcll(tb & lt);
-        a.tail_node[pos] = (uint32_t)node;
-        a.tail_f[pos] = bound;
-        a.tail_key_arr[pos] = key;
-        a.tail_pos[pos] = pos;
-    }
+    if (to_tail) append_tail(a, s_base[0] + off[0] + (uint32_t)__popcll(tb & lt), node, bound, key);
     if (to_guard) a.guard_list[s_base[1] + off[1] + (uint32_t)__popcll(gb & lt)] = (uint32_t)node;
 }
 
@@ -2333,32 +2355,11 @@ __device__ __forceinline__ void publish_scalars(const uint32_t* src, uint32_t* s
     __threadfence_system();
 }
 
-// End of a map in one launch: the partial slots of the passes are added to the scalars, the
-// nodes with an ill-conditioned tetrahedron are redone in FP64-guarded precision (GUARD: 3D,
-// guarded), and the scalars are published (ring: null where the caller reads them itself).
-// With no node to redo, block 0 does it all and the others return; else every block takes a
-// ticket after its share, and the last one publishes.  (A count reduction with the guard and
-// a publishing kernel behind it were two launches of 4.5 and 3.9 us at the end of every map;
-// this one takes 4.4.)
-template <bool GUARD>
-__global__ __launch_bounds__(SEARCH_THREADS) void k_finish(SearchArgs a, const BlockSums* __restrict__ sums,
-                                                           uint32_t* seq, Scalars* ring) {
+// One block: the partial slots added to the scalars, then the scalars published.
+__device__ __forceinline__ void finish_counts(const BlockSums* __restrict__ sums, Scalars* sc, float r2_cap,
+                                              uint32_t* seq, Scalars* ring) {
     constexpr int W = (int)(sizeof(Scalars) / sizeof(uint32_t));
-    __shared__ uint32_t s_last;
     __shared__ __align__(8) uint32_t s_sc[W];
-    Scalars* sc = a.sc;
-    if (GUARD && sc->n_guard != 0u) {
-        if (blockIdx.x == 0) finalize_body<true>(sums, SUM_BINS, sc, a.r2_cap);
-        walk_body<3, 2, false>(a, a.tab, a.guard_list, &sc->n_guard, 0, 0, nullptr, blockIdx.x, gridDim.x);
-        if (!ring) return;
-        __threadfence();
-        __syncthreads();
-        if (threadIdx.x == 0) s_last = atomicAdd(&sc->ticket, 1u) == gridDim.x - 1u ? 1u : 0u;
-        __syncthreads();
-        if (s_last != 0u) publish_scalars<false>(reinterpret_cast<const uint32_t*>(sc), seq, ring);
-        return;
-    }
-    if (blockIdx.x != 0) return;
     unsigned long long p = 0, b = 0, f = 0, c = 0;
     uint32_t m = 0;
     if (threadIdx.x < SUM_BINS) {
@@ -2390,7 +2391,7 @@ __global__ __launch_bounds__(SEARCH_THREADS) void k_finish(SearchArgs a, const B
     __syncthreads();
     if (threadIdx.x == 0) {
         Scalars* l = reinterpret_cast<Scalars*>(s_sc);
-        if (u2f(l->r2_bits) > a.r2_cap && l->n_masked > 0) l->flags |= FLAG_TABLE_SHORT;
+        if (u2f(l->r2_bits) > r2_cap && l->n_masked > 0) l->flags |= FLAG_TABLE_SHORT;
         for (int w = 0; w < SEARCH_THREADS / WAVE; ++w) {
             l->n_pass += s[0][w];
             l->n_border += s[1][w];
@@ -2402,6 +2403,37 @@ __global__ __launch_bounds__(SEARCH_THREADS) void k_finish(SearchArgs a, const B
     __syncthreads();
     if (threadIdx.x < W) reinterpret_cast<uint32_t*>(sc)[threadIdx.x] = s_sc[threadIdx.x];
     if (ring) publish_scalars<true>(s_sc, seq, ring);
+}
+// End of a map in one launch: the partial slots of the passes are added to the scalars, the
+// nodes with an ill-conditioned tetrahedron are redone in FP64-guarded precision (GUARD: 3D,
+// guarded), and the scalars are published (ring: null where the caller reads them itself).
+// With no node to redo, block 0 does it all and the others return; else every block takes a
+// ticket after its share, and the last one publishes.  (A count reduction with the guard and
+// a publishing kernel behind it were two launches of 4.5 and 3.9 us at the end of every map;
+// this one takes 4.4.)
+template <bool GUARD>
+__global__ __launch_bounds__(SEARCH_THREADS) void k_finish(SearchArgs a, const BlockSums* __restrict__ sums,
+                                                           uint32_t* seq, Scalars* ring) {
+    __shared__ uint32_t s_last;
+    Scalars* sc = a.sc;
+    if (GUARD && sc->n_guard != 0u) {
+        if (blockIdx.x == 0) finalize_body<true>(sums, SUM_BINS, sc, a.r2_cap);
+        walk_body<3, 2, false>(a, a.tab, a.guard_list, &sc->n_guard, 0, 0, nullptr, blockIdx.x, gridDim.x);
+        if (!ring) return;
+        __threadfence();
+        __syncthreads();
+        if (threadIdx.x == 0) s_last = atomicAdd(&sc->ticket, 1u) == gridDim.x - 1u ? 1u : 0u;
+        __syncthreads();
+        if (s_last != 0u) publish_scalars<false>(reinterpret_cast<const uint32_t*>(sc), seq, ring);
+        return;
+    }
+    if (blockIdx.x == 0) finish_counts(sums, sc, a.r2_cap, seq, ring);
+}
+
+// The counts and the publication alone (two grids).
+__global__ __launch_bounds__(SEARCH_THREADS) void k_finish_counts(const BlockSums* __restrict__ sums, Scalars* sc,
+                                                                  uint32_t* seq, Scalars* ring) {
+    finish_counts(sums, sc, Num<float>::inf(), seq, ring);
 }
 static_assert(SUM_BINS <= SEARCH_THREADS, "one partial slot per thread");
 
@@ -2629,23 +2661,40 @@ __global__ __launch_bounds__(256) void k_grids_max(GridsArgs a, int64_t nr, int6
     // 30-80 us); the listing kernel reduces the partials
     __shared__ uint32_t s_m[4];
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m > -Num<float>::inf() ? float_to_ord(m) : 0u;
-    if (__ballot(bad) != 0ull && (threadIdx.x & 63) == 0) atomicOr(&a.sc->flags, FLAG_NONFINITE);
+    __shared__ uint32_t s_bad[4];
+    const bool wbad = __ballot(bad) != 0ull;
+    if ((threadIdx.x & 63) == 0) {
+        s_m[threadIdx.x >> 6] = m > -Num<float>::inf() ? float_to_ord(m) : 0u;
+        s_bad[threadIdx.x >> 6] = wbad ? 1u : 0u;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) a.part[blockIdx.x] = max(max(s_m[0], s_m[1]), max(s_m[2], s_m[3]));
+    if (threadIdx.x == 0) {
+        a.part[blockIdx.x] = max(max(s_m[0], s_m[1]), max(s_m[2], s_m[3]));
+        a.part[MAX_BLOCKS + blockIdx.x] = s_bad[0] | s_bad[1] | s_bad[2] | s_bad[3];
+    }
+    // the map's scalars and partial counts start at 0 (no other block touches them here)
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < sizeof(Scalars) / sizeof(uint32_t)) reinterpret_cast<uint32_t*>(a.sc)[threadIdx.x] = 0u;
+        for (int j = threadIdx.x; j < SUM_BINS; j += 256) a.sums[j] = BlockSums{};
+    }
 }
 
 // Listing in chunks of 16 nodes per thread (4096 per block): one atomic per chunk on the
 // list counter (one per 256 nodes would serialise on that address).
 constexpr int GRIDS_PER_THREAD = 16;
 __global__ __launch_bounds__(256) void k_grids_list(GridsArgs a, int64_t nr, int nb_max) {
+    static_assert(GRIDS_PER_THREAD * 4 == 64, "one lane per (item, wave) count");
     __shared__ uint32_t s_wsum[4];
-    __shared__ uint32_t s_base;
+    __shared__ uint32_t s_cnt[64];
     // the dose maximum from k_grids_max's partials (every block reduces them itself)
-    uint32_t dm = 0u;
-    for (int j = threadIdx.x; j < nb_max; j += 256) dm = max(dm, a.part[j]);
+    uint32_t dm = 0u, nonfinite = 0u;
+    for (int j = threadIdx.x; j < nb_max; j += 256) {
+        dm = max(dm, a.part[j]);
+        nonfinite |= a.part[MAX_BLOCKS + j];
+    }
     for (int o = 32; o > 0; o >>= 1) dm = max(dm, (uint32_t)__shfl_xor((int)dm, o));
     if ((threadIdx.x & 63) == 0) s_wsum[threadIdx.x >> 6] = dm;
+    if (blockIdx.x == 0 && nonfinite != 0u) atomicOr(&a.sc->flags, FLAG_NONFINITE);
     __syncthreads();
     dm = max(max(s_wsum[0], s_wsum[1]), max(s_wsum[2], s_wsum[3]));
     __syncthreads();   // s_wsum is reused below
@@ -2662,7 +2711,7 @@ __global__ __launch_bounds__(256) void k_grids_list(GridsArgs a, int64_t nr, int
     // block-uniform trip count, so that every thread reaches the barriers
     for (int64_t b0 = (int64_t)blockIdx.x * chunk; b0 < nr; b0 += (int64_t)gridDim.x * chunk) {
         float F0[GRIDS_PER_THREAD], drs[GRIDS_PER_THREAD];
-        uint32_t takes = 0u, cnt = 0u;
+        uint32_t takes = 0u;
         // every reference load first, and the gamma = -1 stores after the chunk's loads: a
         // store between them (gamma may alias the doses, as far as the compiler knows) kept
         // each node's loads waiting for the previous node's
@@ -2686,7 +2735,6 @@ __global__ __launch_bounds__(256) void k_grids_list(GridsArgs a, int64_t nr, int
                     grids_cell<float>(a, u, c0, f);
                     F0[k] = grids_f0<float>(a, c0, f, dr, node_inv_dd(dr, inv_dd_g, (float)a.dd, a.local));
                     takes |= 1u << k;
-                    ++cnt;
                 }
             }
         }
@@ -2695,30 +2743,38 @@ __global__ __launch_bounds__(256) void k_grids_list(GridsArgs a, int64_t nr, int
             const int64_t r = b0 + threadIdx.x + 256 * k;
             if (r < nr) a.gamma[r] = -1.0f;
         }
-        // exclusive prefix of the per-thread counts over the block
-        uint32_t incl = cnt;
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t y = (uint32_t)__shfl_up((int)incl, o);
-            if (lane >= o) incl += y;
-        }
-        if (lane == 63) s_wsum[w] = incl;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const uint32_t tot = s_wsum[0] + s_wsum[1] + s_wsum[2] + s_wsum[3];
-            s_base = tot ? atomicAdd(&a.sc->n_masked, tot) : 0u;
+        // the chunk's nodes in grid order (neighbouring lanes of the later kernels then read
+        // neighbouring doses): counts per (item, wave), their exclusive prefix, one atomic.
+        // Listed thread by thread, neighbouring entries lay 256 nodes apart and a load of the
+        // key-0 pass touched 52 cache lines: that pass 86 us, 70 in grid order.
+#pragma unroll
+        for (int k = 0; k < GRIDS_PER_THREAD; ++k) {
+            const unsigned long long bal = __ballot((takes >> k) & 1u);
+            if (lane == 0) s_cnt[k * 4 + w] = (uint32_t)__popcll(bal);
         }
         __syncthreads();
-        uint32_t pos = s_base + incl - cnt;
-        for (int j2 = 0; j2 < w; ++j2) pos += s_wsum[j2];
-        __syncthreads();   // s_wsum / s_base are reused by the next chunk
+        if (w == 0) {
+            const uint32_t c = s_cnt[lane];
+            uint32_t incl = c;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t up = (uint32_t)__shfl_up((int)incl, o);
+                if (lane >= o) incl += up;
+            }
+            uint32_t base = 0u;
+            if (lane == 63 && incl != 0u) base = atomicAdd(&a.sc->n_masked, incl);
+            base = (uint32_t)__shfl((int)base, 63);
+            s_cnt[lane] = base + incl - c;
+        }
+        __syncthreads();
         uint32_t fb = 0u;
 #pragma unroll
         for (int k = 0; k < GRIDS_PER_THREAD; ++k) {
+            const unsigned long long bal = __ballot((takes >> k) & 1u);
             if ((takes >> k) & 1u) {
+                const uint32_t pos = s_cnt[k * 4 + w] + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
                 a.list[pos] = (uint32_t)(b0 + threadIdx.x + 256 * k);
                 a.f0[pos] = F0[k];
                 fb = max(fb, f2u(F0[k]));
-                ++pos;
             }
         }
         // the largest first bound: one atomic per block and chunk, only while it can raise it
@@ -2790,114 +2846,400 @@ __device__ __forceinline__ void grids_counts(Scalars* sc, uint32_t npass, uint32
     }
 }
 
-// The 27 key-0 cells (offsets a in {-1,0,1}^3 from the holding cell) of every listed node,
-// one lane per node, from the 4x4x4 evaluation neighbourhood loaded one z-pair of planes at
-// a time (clamped at the grid faces; cells that do not exist are skipped).  A node whose
-// bound is at most k1 is finished; the others go to the tail list.
-template <int GMODE>
-__global__ __launch_bounds__(256) void k_grids_zero(GridsArgs a) {
-    const uint32_t M = a.sc->n_masked;
-    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (blockIdx.x * 256 >= M) return;   // uniform
-    const bool live = i < M;
-    const int r = live ? (int)a.list[i] : (int)a.list[0];
+// A listed node as the lanes that project its cells read it.
+struct alignas(16) GridsNode {
+    int cz, cy, cx, r;       // holding cell, reference node
+    float fz, fy, fx, dr;    // position in that cell, reference dose
+    float inv_dd;
+    uint32_t f;              // F (non-negative float bits)
+    uint32_t pad[2];
+};
+// The evaluation grid's normalised spacings squared and their chain-block reciprocals.
+struct GridsGeo {
+    float sx2, sy2, sz2;
+    InvS2<float> is;
+};
+__device__ __forceinline__ GridsGeo grids_geo(const GridsArgs& a) {
+    GridsGeo q;
+    q.sx2 = (float)((a.eh[2] / a.dta) * (a.eh[2] / a.dta));
+    q.sy2 = (float)((a.eh[1] / a.dta) * (a.eh[1] / a.dta));
+    q.sz2 = (float)((a.eh[0] / a.dta) * (a.eh[0] / a.dta));
+    q.is = inv_s2<float>(q.sx2, q.sy2, q.sz2);
+    return q;
+}
+__device__ __forceinline__ GridsNode grids_node(const GridsArgs& a, int r, float dr, float F, float inv_dd_g) {
     double u[3];
     bool inside;
     grids_pos(a, r, u, inside);
     int c0[3];
     float f[3];
     grids_cell<float>(a, u, c0, f);
-    const float dr = a.ref[r];
-    const float inv_dd = node_inv_dd(dr, a.sc->inv_dd, (float)a.dd, a.local);
-    const float sx2 = (float)((a.eh[2] / a.dta) * (a.eh[2] / a.dta)), sy2 = (float)((a.eh[1] / a.dta) * (a.eh[1] / a.dta)),
-                sz2 = (float)((a.eh[0] / a.dta) * (a.eh[0] / a.dta));
-    const InvS2<float> is = inv_s2<float>(sx2, sy2, sz2);
+    return GridsNode{c0[0], c0[1], c0[2], r, f[0], f[1], f[2], dr, node_inv_dd(dr, inv_dd_g, (float)a.dd, a.local), f2u(F),
+                     {0u, 0u}};
+}
+// dist^2 to the faces of the cell at offset (az, ay, ax) from the node's holding cell (a cell
+// whose lower corner lies on the grid; mask: some lane's cell is cut by the grid's faces).
+__device__ __forceinline__ float grids_project(const GridsArgs& a, const GridsGeo& q, const GridsNode& n, int az, int ay,
+                                               int ax, bool okx, bool oky, bool okz, bool mask) {
+    const int enx = a.en[2], esxy = enx * a.en[1];
+    const int64_t b = (int64_t)(n.cz + az) * esxy + (int64_t)(n.cy + ay) * enx + (n.cx + ax);
+    float g[8];
+    cell_corners<3>(a.ev, b, okx, oky ? enx : 0, okz ? esxy : 0, g);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) g[k] = dose_norm<float>(g[k], n.dr, n.inv_dd);
+    const Geo<float> G = geo_frac<float>((float)ax - n.fx, (float)ay - n.fy, (float)az - n.fz, q.sx2, q.sy2, q.sz2, q.is);
+    GuardCtx gc{};
+    uint32_t n_fp64 = 0;
+    bool ill = false;
+    if (mask) return cell3<float, true, 0>(g, G, q.is, okx, oky, okz, a.den_guard, gc, n_fp64, ill);
+    return cell3<float, false, 0>(g, G, q.is, true, true, true, a.den_guard, gc, n_fp64, ill);
+}
+// Whether the whole cell with lower corner (cz, cy, cx) holds an ill-conditioned tetrahedron.
+__device__ __forceinline__ bool grids_ill(const GridsArgs& a, const GridsGeo& q, const GridsNode& n, int cz, int cy, int cx) {
+    const int enx = a.en[2], esxy = enx * a.en[1];
+    const int64_t b = (int64_t)cz * esxy + (int64_t)cy * enx + cx;
+    float g[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        g[k] = dose_norm<float>(a.ev[b + (k & 1) + ((k >> 1) & 1) * enx + (k >> 2) * esxy], n.dr, n.inv_dd);
+    return tets_ill(g, q.is, a.den_guard);
+}
+
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// The 27 key-0 cells (offsets a in {-1,0,1}^3 from the holding cell) of every listed node, one
+// lane per node: the holding cell is projected first; the others are tested by their exact
+// distance and the range of their corner doses (from the 4 x 4 x 4 evaluation neighbourhood,
+// read plane by plane, clamped at the grid's faces), and those that can still lower F are
+// queued in LDS and projected 64 at a time, whichever nodes they belong to.  A node whose
+// bound is then at most k1 is finished; the others go to the tail list.  Which of a wave's 64
+// nodes need a cell differs, so projecting it whenever one does took the 27 cells' time for
+// the few that each node needs: 434 thousand nodes on a grid of half the spacing 129 us, now
+// 66-72 (4200 instructions of a wave, half of its time; three waves per SIMD, which four with
+// 52 spilled registers do not beat: 95 against 86 us before the list was in grid order).
+//
+// The guard judges every whole cell (not only the projected ones: which those are depends on
+// the nodes that share the wave), by the range of the neighbourhood first.
+template <int GMODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_grids_zero(GridsArgs a) {
+    __shared__ GridsNode s_node[256];
+    __shared__ uint16_t s_item[4][26 * 64];   // queued cells: node's lane | cell << 6
+    const uint32_t M = a.sc->n_masked;
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.x * 256 >= M) return;   // uniform
+    const bool live = i < M;
+    const int lane = threadIdx.x & 63;
+    const int r = (int)a.list[live ? i : 0u];
+    GridsNode* wnode = s_node + (threadIdx.x & ~63u);
+    uint16_t* item = s_item[threadIdx.x >> 6];
+    const GridsGeo q = grids_geo(a);
+    GridsNode n = grids_node(a, r, a.ref[r], live ? a.f0[i] : 0.0f, a.sc->inv_dd);
     const int enx = a.en[2], eny = a.en[1], enz = a.en[0];
     // per axis: does the cell at -1 exist, is the cell at +1 whole
-    const bool lox = c0[2] > 0, loy = c0[1] > 0, loz = c0[0] > 0;
-    const bool hix = c0[2] + 2 < enx, hiy = c0[1] + 2 < eny, hiz = c0[0] + 2 < enz;
-    const bool bnd = !(lox && loy && loz && hix && hiy && hiz);
-    const bool wave_masked = __ballot(live && bnd) != 0ull;
-    auto cl = [](int v, int n) { return v < 0 ? 0 : (v > n - 1 ? n - 1 : v); };
-    int ix[4], iy[4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        ix[d] = cl(c0[2] - 1 + d, enx);
-        iy[d] = cl(c0[1] - 1 + d, eny);
+    const bool lox = n.cx > 0, loy = n.cy > 0, loz = n.cz > 0;
+    const bool hix = n.cx + 2 < enx, hiy = n.cy + 2 < eny, hiz = n.cz + 2 < enz;
+    {
+        const float c = grids_project(a, q, n, 0, 0, 0, true, true, true, false);
+        n.f = f2u(live ? vmin<float>(u2f(n.f), c) : u2f(n.f));
     }
-    float F = live ? a.f0[i] : 0.0f;
-    uint32_t cells = 0, n_fp64 = 0;
-    bool ill = false;
-    GuardCtx gc{};
-#pragma unroll 1
-    for (int az = -1; az <= 1; ++az) {
-        // the two planes of this slab of cells
-        float pl[2][16];
+    wnode[lane] = n;
+    const float Fm = u2f(n.f) + u2f(n.f) * 0x1p-8f;
+
+    // squared distance of the cells at -1 and +1 per axis
+    const float dxl = q.sx2 * (n.fx * n.fx), dxh = q.sx2 * ((1.0f - n.fx) * (1.0f - n.fx));
+    const float dyl = q.sy2 * (n.fy * n.fy), dyh = q.sy2 * ((1.0f - n.fy) * (1.0f - n.fy));
+    const float dzl = q.sz2 * (n.fz * n.fz), dzh = q.sz2 * ((1.0f - n.fz) * (1.0f - n.fz));
+    auto cl = [](int v, int m) { return v < 0 ? 0 : (v > m - 1 ? m - 1 : v); };
+    const bool rows4 = __ballot(!(lox && hix)) == 0ull;   // no lane's row is clamped along x
+    uint32_t nq = 0;
+    float all_lo = Num<float>::inf(), all_hi = -Num<float>::inf();
+    float plo[9], phi[9];   // ranges of the 3 x 3 squares of the plane before
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int64_t zb = (int64_t)cl(c0[0] + az + p, enz) * eny;
+    for (int p = 0; p < 4; ++p) {
+        float v[16];
+        const int64_t zb = (int64_t)cl(n.cz - 1 + p, enz) * eny;
+        if (rows4) {   // a row's four doses in one load
+#pragma unroll
+            for (int dy = 0; dy < 4; ++dy) {
+                const f32x4u t = *reinterpret_cast<const f32x4u*>(a.ev + (zb + cl(n.cy - 1 + dy, eny)) * enx + (n.cx - 1));
+                v[dy * 4] = t.x;
+                v[dy * 4 + 1] = t.y;
+                v[dy * 4 + 2] = t.z;
+                v[dy * 4 + 3] = t.w;
+            }
+        } else {
 #pragma unroll
             for (int dy = 0; dy < 4; ++dy)
 #pragma unroll
                 for (int dx = 0; dx < 4; ++dx)
-                    pl[p][dy * 4 + dx] = a.ev[(zb + iy[dy]) * enx + ix[dx]];
+                    v[dy * 4 + dx] = a.ev[(zb + cl(n.cy - 1 + dy, eny)) * enx + cl(n.cx - 1 + dx, enx)];
+        }
+        float clo[9], chi[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            const int b = (k / 3) * 4 + k % 3;
+            clo[k] = vmin<float>(vmin<float>(v[b], v[b + 1]), vmin<float>(v[b + 4], v[b + 5]));
+            chi[k] = vmax<float>(vmax<float>(v[b], v[b + 1]), vmax<float>(v[b + 4], v[b + 5]));
+        }
+        if (p > 0) {
+            const int az = p - 2;
+#pragma unroll
+            for (int k = 0; k < 9; ++k) {
+                const int ay = k / 3 - 1, ax = k % 3 - 1;
+                if (az == 0 && ay == 0 && ax == 0) continue;
+                const float lo = dose_norm<float>(vmin<float>(plo[k], clo[k]), n.dr, n.inv_dd);
+                const float hi = dose_norm<float>(vmax<float>(phi[k], chi[k]), n.dr, n.inv_dd);
+                if (GMODE == 1) {
+                    all_lo = vmin<float>(all_lo, lo);
+                    all_hi = vmax<float>(all_hi, hi);
+                }
+                const float m = vmax<float>(vmax<float>(lo, -hi), 0.0f);
+                const float d = (ax < 0 ? dxl : (ax > 0 ? dxh : 0.0f)) + (ay < 0 ? dyl : (ay > 0 ? dyh : 0.0f)) +
+                                (az < 0 ? dzl : (az > 0 ? dzh : 0.0f));
+                const bool there = (ax >= 0 || lox) && (ay >= 0 || loy) && (az >= 0 || loz);
+                const bool need = live && there && fmadd(m, m, d) < Fm;
+                const unsigned long long mask = __ballot(need);
+                if (need)
+                    item[nq + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] =
+                        (uint16_t)(lane | (((az + 1) * 9 + k) << 6));
+                nq += (uint32_t)__popcll(mask);
+            }
         }
 #pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int k = 0; k < 16; ++k) pl[p][k] = dose_norm<float>(pl[p][k], dr, inv_dd);
-        const bool ez = az < 0 ? loz : true, okz = az > 0 ? hiz : true;
-#pragma unroll
-        for (int ay = -1; ay <= 1; ++ay)
-#pragma unroll
-            for (int ax = -1; ax <= 1; ++ax) {
-                float g[8];
-#pragma unroll
-                for (int b = 0; b < 8; ++b)
-                    g[b] = pl[(b >> 2) & 1][(ay + 1 + ((b >> 1) & 1)) * 4 + (ax + 1 + (b & 1))];
-                const bool ey = ay < 0 ? loy : true, oky = ay > 0 ? hiy : true;
-                const bool ex = ax < 0 ? lox : true, okx = ax > 0 ? hix : true;
-                const bool exists = live && ex && ey && ez;
-                const bool whole = okx && oky && okz;
-                cells += (exists && (whole || !wave_masked)) ? 1u : 0u;
-                const bool need = exists && grids_need(g, (float)ax, (float)ay, (float)az, f, sx2, sy2, sz2, F);
-                float v = Num<float>::inf();
-                if (__ballot(need) != 0ull && need) {
-                    const Geo<float> G = geo_frac<float>((float)ax - f[2], (float)ay - f[1], (float)az - f[0], sx2,
-                                                         sy2, sz2, is);
-                    if (wave_masked)
-                        v = cell3<float, true, GMODE>(g, G, is, okx, oky, okz, a.den_guard, gc, n_fp64, ill);
-                    else
-                        v = cell3<float, false, GMODE>(g, G, is, true, true, true, a.den_guard, gc, n_fp64, ill);
-                }
-                F = vmin<float>(F, v);
-            }
+        for (int k = 0; k < 9; ++k) {
+            plo[k] = clo[k];
+            phi[k] = chi[k];
+        }
     }
-    ill = ill && live;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll 1
+    for (uint32_t h = 0; h < nq; h += 64) {
+        const bool on = h + lane < nq;
+        const uint32_t it = on ? item[h + lane] : (uint32_t)(13u << 6);
+        const GridsNode o = wnode[it & 63u];
+        const int c = (int)(it >> 6), az = c / 9 - 1, ay = (c / 3) % 3 - 1, ax = c % 3 - 1;
+        const bool okx = o.cx + ax + 1 < enx, oky = o.cy + ay + 1 < eny, okz = o.cz + az + 1 < enz;
+        const bool mask = __ballot(on && !(okx && oky && okz)) != 0ull;
+        if (on) {
+            const float v = grids_project(a, q, o, az, ay, ax, okx, oky, okz, mask);
+            atomicMin(&wnode[it & 63u].f, f2u(v));
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const float F = u2f(wnode[lane].f);
+    bool ill = false;
+    if (GMODE == 1) {
+        const bool suspect = live && !((all_hi - all_lo) * (all_hi - all_lo) <
+                                       (a.den_guard * 0.999f - 1.0f) / ((q.is.x + q.is.y) + q.is.z));
+        if (__ballot(suspect) != 0ull && suspect) {   // rare
+#pragma unroll 1
+            for (int c = 0; c < 27; ++c) {
+                const int cz = n.cz + c / 9 - 1, cy = n.cy + (c / 3) % 3 - 1, cx = n.cx + c % 3 - 1;
+                if (cz >= 0 && cy >= 0 && cx >= 0 && cz + 1 < enz && cy + 1 < eny && cx + 1 < enx)
+                    ill = ill || grids_ill(a, q, n, cz, cy, cx);
+            }
+        }
+    }
     const bool to_guard = GMODE == 1 && ill;
     const bool to_tail = live && !to_guard && F > a.k1;
+    const uint32_t cells = (1u + lox + hix) * (1u + loy + hiy) * (1u + loz + hiz);
+    zero_epilogue(a, a.sums, blockIdx.x, live, r, F, f2u(F), 0u, cells, to_tail, to_guard, true);
+}
+
+// The walk of the tail list in the automatic layout: the scan, pooled projections and finish of
+// tail_queue_body, for nodes between the evaluation grid's nodes.  A row's test takes the exact
+// distance of its cell (the key is its least over the holding cell) and the range of its
+// corner doses; visited cells and ill-conditioned tetrahedra are those of the rows below the
+// final F.  68 us of the 16-lane walk at 36 thousand nodes, 46 here.
+template <int GMODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_grids_tail(GridsArgs a) {
+    constexpr int FIRST = 27;   // rows of the key-0 cells
+    __shared__ GridsNode s_node[TQ_GROUPS];
+    __shared__ uint2 s_queue[4][TQ_RING];   // row | group of the wave << 28, bound
+    const uint32_t M = a.sc->n_tail;
+    const int lane = threadIdx.x & 63, gl = lane & (TQ_LANES - 1), gsh = lane & ~(TQ_LANES - 1);
+    const unsigned long long gmask = (1ull << TQ_LANES) - 1ull;
+    uint2* queue = s_queue[threadIdx.x >> 6];
+    GridsNode* wnode = s_node + (threadIdx.x >> 6) * (WAVE / TQ_LANES);
+    GridsNode& self = wnode[lane / TQ_LANES];
+    const float inv_dd_g = a.sc->inv_dd;
+    const GridsGeo q = grids_geo(a);
+    const int enx = a.en[2], eny = a.en[1], enz = a.en[0];
+    const float ill_span2 = (a.den_guard * 0.999f - 1.0f) / ((q.is.x + q.is.y) + q.is.z);
+    auto row_head = [&](int n) -> int4 {   // key^2 (infinite past the table) and offset
+        return n < a.tab_len ? *reinterpret_cast<const int4*>(&a.tab[n]) : make_int4(0x7F800000, 0, 0, 0);
+    };
     uint32_t npass = 0, nborder = 0, gm = 0;
-    unsigned long long ncells = 0;
-    if (live && !to_guard && !to_tail) {
-        const float gam = sqrtf(F);
-        a.gamma[r] = gam;
-        npass = gam <= 1.0f;
-        nborder = fabsf(gam - 1.0f) <= 1e-5f;
-        gm = f2u(gam * gam);
-        ncells = cells;
+    unsigned long long cells = 0;
+    uint32_t i = blockIdx.x * TQ_GROUPS + threadIdx.x / TQ_LANES;
+    const uint32_t stride = gridDim.x * TQ_GROUPS;
+    if (blockIdx.x * TQ_GROUPS >= M) return;   // uniform
+    if (gl == 0) self = GridsNode{};
+    bool have = false, done = false;
+    int n0 = FIRST;
+    uint32_t q_head = 0, q_tail = 0, q_last = 0, lane_cells = 0, whole = 0;
+    float key[TQ_ROWS], ill_key = Num<float>::inf();
+#pragma unroll
+    for (int k = 0; k < TQ_ROWS; ++k) key[k] = 0.0f;
+
+    for (;;) {
+        if (!have && i < M) {
+            const int r = (int)a.tail_list[i];
+            const float f = a.tail_f[i], dr = a.ref[r];
+            if (gl == 0) self = grids_node(a, r, dr, f, inv_dd_g);
+            n0 = FIRST;
+            q_last = q_head;
+            lane_cells = whole = 0u;
+            ill_key = Num<float>::inf();
+            have = true;
+            done = false;
+            i += stride;
+        }
+        if (__ballot(have) == 0ull) break;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+
+        // scan
+        if (q_tail - q_head < WAVE && __ballot(have && !done) != 0ull) {
+            const bool scan = have && !done;
+            const GridsNode nd = self;
+            const float F = u2f(nd.f), Fm = F + F * 0x1p-8f;
+            bool past = false;
+            if (scan) {
+                lane_cells += __popc(whole);
+                whole = 0u;
+            }
+            float lb[TQ_ROWS];
+            uint32_t work = 0u, before = q_tail;
+            bool suspect = false;
+            float v[TQ_ROWS][8];
+#pragma unroll
+            for (int k = 0; k < TQ_ROWS; ++k) {
+                lb[k] = 0.0f;
+#pragma unroll
+                for (int b = 0; b < 8; ++b) v[k][b] = 0.0f;
+                if (scan) {
+                    const int4 e = row_head(n0 + k * TQ_LANES + gl);
+                    key[k] = __builtin_bit_cast(float, e.x);
+                    const int cx = nd.cx + e.y, cy = nd.cy + e.z, cz = nd.cz + e.w;
+                    const bool in = (unsigned)cx < (unsigned)enx && (unsigned)cy < (unsigned)eny &&
+                                    (unsigned)cz < (unsigned)enz && key[k] < F;
+                    const bool okx = cx + 1 < enx, oky = cy + 1 < eny, okz = cz + 1 < enz;
+                    past = past || !(key[k] < F);
+                    if (in) {
+                        work |= 1u << k;
+                        whole |= okx && oky && okz ? (1u << k) : 0u;
+                        const int64_t b = ((int64_t)cz * eny + cy) * enx + cx;
+                        cell_corners<3>(a.ev, b, okx, oky ? enx : 0, okz ? enx * eny : 0, v[k]);
+                        const float x = (float)e.y - nd.fx, y = (float)e.z - nd.fy, z = (float)e.w - nd.fz;
+                        const float dx = vmax<float>(vmax<float>(x, -x - 1.0f), 0.0f);
+                        const float dy = vmax<float>(vmax<float>(y, -y - 1.0f), 0.0f);
+                        const float dz = vmax<float>(vmax<float>(z, -z - 1.0f), 0.0f);
+                        lb[k] = (q.sx2 * (dx * dx) + q.sy2 * (dy * dy)) + q.sz2 * (dz * dz);
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < TQ_ROWS; ++k) {
+                float lo = v[k][0], hi = v[k][0];
+#pragma unroll
+                for (int b = 1; b < 8; ++b) {
+                    lo = vmin<float>(lo, v[k][b]);
+                    hi = vmax<float>(hi, v[k][b]);
+                }
+                lo = dose_norm<float>(lo, nd.dr, nd.inv_dd);
+                hi = dose_norm<float>(hi, nd.dr, nd.inv_dd);
+                const float m = vmax<float>(vmax<float>(lo, -hi), 0.0f);
+                lb[k] = fmadd(m, m, lb[k]);
+                const bool need = ((work >> k) & 1u) && lb[k] < Fm;
+                if (GMODE == 1) suspect = suspect || (((whole >> k) & 1u) && !((hi - lo) * (hi - lo) < ill_span2));
+                const unsigned long long mask = __ballot(need);
+                if (need)
+                    queue[(q_tail + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))) &
+                          (TQ_RING - 1)] =
+                        make_uint2((uint32_t)(n0 + k * TQ_LANES + gl) | ((uint32_t)(lane / TQ_LANES) << 28), f2u(lb[k]));
+                q_tail += (uint32_t)__popcll(mask);
+            }
+            if (GMODE == 1 && __ballot(scan && suspect) != 0ull && scan) {   // rare
+#pragma nounroll
+                for (int k = 0; k < TQ_ROWS; ++k) {
+                    if (!((whole >> k) & 1u)) continue;
+                    const int4 e = row_head(n0 + k * TQ_LANES + gl);
+                    if (grids_ill(a, q, nd, nd.cz + e.w, nd.cy + e.z, nd.cx + e.y))
+                        ill_key = vmin<float>(ill_key, __builtin_bit_cast(float, e.x));
+                }
+            }
+            const unsigned long long pb = __ballot(past);
+            if (scan) {
+                n0 += TQ_STEP;
+                done = ((pb >> gsh) & gmask) != 0ull;
+                if (q_tail != before) q_last = q_tail;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+
+        // project
+        const uint32_t queued = q_tail - q_head;
+        if (queued >= WAVE || (queued > 0u && __popcll(__ballot(have && !done)) <= TQ_FEW * TQ_LANES)) {
+            const uint32_t take = queued < WAVE ? queued : WAVE;
+            const uint2 it = queue[(q_head + lane) & (TQ_RING - 1)];
+            GridsNode* owner = &wnode[(it.x >> 28) & 7u];
+            const GridsNode nd = *owner;
+            const float F = u2f(nd.f);
+            const bool proj = (uint32_t)lane < take && u2f(it.y) < F + F * 0x1p-8f;
+            const int4 e = row_head(proj ? (int)(it.x & 0x0FFFFFFFu) : FIRST);
+            const bool okx = nd.cx + e.y + 1 < enx, oky = nd.cy + e.z + 1 < eny, okz = nd.cz + e.w + 1 < enz;
+            const bool mask = __ballot(proj && !(okx && oky && okz)) != 0ull;
+            if (proj) atomicMin(&owner->f, f2u(grids_project(a, q, nd, e.w, e.z, e.y, okx, oky, okz, mask)));
+            q_head += take;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+
+        // finish
+        const bool fin = have && done && (int32_t)(q_head - q_last) >= 0;
+        if (__ballot(fin) != 0ull) {
+            const GridsNode nd = self;
+            const float F = u2f(nd.f);
+            if (fin) {
+#pragma unroll
+                for (int k = 0; k < TQ_ROWS; ++k) lane_cells += ((whole >> k) & 1u) && key[k] < F ? 1u : 0u;
+                for (int s0 = n0 - TQ_STEP;
+                     s0 > FIRST && !(__builtin_bit_cast(float, row_head(s0 - 1).x) < F); s0 -= TQ_STEP) {
+#pragma unroll
+                    for (int k = 0; k < TQ_ROWS; ++k) {
+                        const int4 e = row_head(s0 - TQ_STEP + k * TQ_LANES + gl);
+                        const int cx = nd.cx + e.y, cy = nd.cy + e.z, cz = nd.cz + e.w;
+                        const bool w = cx >= 0 && cx + 1 < enx && cy >= 0 && cy + 1 < eny && cz >= 0 && cz + 1 < enz;
+                        lane_cells -= w && !(__builtin_bit_cast(float, e.x) < F) ? 1u : 0u;
+                    }
+                }
+            }
+            const uint32_t sum = sum8(lane_cells);
+            const bool to_guard = GMODE == 1 && ((__ballot(fin && ill_key < F) >> gsh) & gmask) != 0ull;
+            const bool put = fin && to_guard && gl == 0;
+            if (fin) {
+                if (gl == 0 && !to_guard) {
+                    const float gam = sqrtf(F);
+                    a.gamma[nd.r] = gam;
+                    npass += gam <= 1.0f;
+                    nborder += fabsf(gam - 1.0f) <= 1e-5f;
+                    gm = max(gm, f2u(gam * gam));
+                    cells += sum;
+                }
+                have = false;
+            }
+            if (GMODE == 1) {
+                const unsigned long long gb = __ballot(put);
+                if (gb != 0ull) {   // rare: one atomic per wave
+                    uint32_t base = 0u;
+                    if (lane == 0) base = atomicAdd(&a.sc->n_guard, (uint32_t)__popcll(gb));
+                    base = (uint32_t)__shfl((int)base, 0);
+                    if (put) a.guard_list[base + (uint32_t)__popcll(gb & ((1ull << lane) - 1ull))] = (uint32_t)nd.r;
+                }
+            }
+        }
     }
-    const uint32_t tpos = block_append(to_tail, &a.sc->n_tail);
-    if (to_tail) {
-        a.tail_list[tpos] = (uint32_t)r;
-        a.tail_f[tpos] = F;
-    }
-    if (GMODE == 1) {
-        const uint32_t gpos = block_append(to_guard, &a.sc->n_guard);
-        if (to_guard) a.guard_list[gpos] = (uint32_t)r;
-    }
-    // tail nodes count their key-0 cells in the walk's total: add them here
-    if (to_tail) ncells = cells;
-    grids_counts(a.sc, npass, nborder, ncells, gm);
+    block_sums(a.sums, blockIdx.x, npass, nborder, 0u, (uint32_t)cells, gm);
 }
 
 // LIST 0: the listed nodes from row 0; 1: the guard list (FP64) from row 0; 2: the tail
@@ -2906,6 +3248,7 @@ template <typename T, int GMODE, int LIST>
 __global__ __launch_bounds__(256) void k_grids_walk(GridsArgs a, int G) {
     constexpr bool GUARD = LIST == 1;
     const uint32_t M = LIST == 1 ? a.sc->n_guard : (LIST == 2 ? a.sc->n_tail : a.sc->n_masked);
+    if (M == 0u) return;   // (the guard list, as a rule)
     const uint32_t* list = LIST == 1 ? a.guard_list : (LIST == 2 ? a.tail_list : a.list);
     const int first = LIST == 2 ? 27 : 0;
     const int GROUPS = 256 / G;
@@ -3139,8 +3482,7 @@ hipError_t launch_grids_prep(const GridsArgs& a, hipStream_t s) {
     const int64_t nr = (int64_t)a.rn[0] * a.rn[1] * a.rn[2];
     const int64_t ne = (int64_t)a.en[0] * a.en[1] * a.en[2];
     const int64_t n = nr > ne ? nr : ne;
-    constexpr int64_t kMaxBlocks = 512;   // partials each listing block reduces (<= MAX_BLOCKS)
-    static_assert(kMaxBlocks <= MAX_BLOCKS, "the partials buffer holds MAX_BLOCKS words");
+    constexpr int64_t kMaxBlocks = MAX_BLOCKS;   // partials each listing block reduces
     const int64_t nb1 = (n + 256 * GRIDS_MAX_ITEMS - 1) / (256 * GRIDS_MAX_ITEMS);
     const unsigned b1 = (unsigned)(nb1 < kMaxBlocks ? nb1 : kMaxBlocks);
     hipLaunchKernelGGL(k_grids_max, dim3(b1), dim3(256), 0, s, a, nr, ne);
@@ -3152,11 +3494,16 @@ hipError_t launch_grids_prep(const GridsArgs& a, hipStream_t s) {
 
 hipError_t launch_grids_walk(const GridsArgs& a, int precision, bool guard, int lanes, hipStream_t s) {
     const int G = lanes;
-    const dim3 grid(2048), block(256);
+    const dim3 grid(guard ? 512 : 2048), block(256);
     if (guard) hipLaunchKernelGGL((k_grids_walk<double, 0, 1>), grid, block, 0, s, a, G);
     else if (precision == 2) hipLaunchKernelGGL((k_grids_walk<double, 0, 0>), grid, block, 0, s, a, G);
     else if (precision == 1) hipLaunchKernelGGL((k_grids_walk<float, 1, 0>), grid, block, 0, s, a, G);
     else hipLaunchKernelGGL((k_grids_walk<float, 0, 0>), grid, block, 0, s, a, G);
+    return hipGetLastError();
+}
+
+hipError_t launch_grids_finish(const GridsArgs& a, uint32_t* seq, Scalars* ring, hipStream_t s) {
+    hipLaunchKernelGGL(k_finish_counts, dim3(1), dim3(SEARCH_THREADS), 0, s, a.sums, a.sc, seq, ring);
     return hipGetLastError();
 }
 
@@ -3169,6 +3516,14 @@ hipError_t launch_grids_zero(const GridsArgs& a, int precision, hipStream_t s) {
 }
 
 hipError_t launch_grids_tail(const GridsArgs& a, int precision, int lanes, hipStream_t s) {
+    if (lanes == 0) {
+        const int64_t nr = (int64_t)a.rn[0] * a.rn[1] * a.rn[2];
+        const int64_t nb = (nr + TQ_GROUPS - 1) / TQ_GROUPS;
+        const dim3 g((unsigned)(nb < kTailBlocks ? nb : kTailBlocks)), b(SEARCH_THREADS);
+        if (precision == 1) hipLaunchKernelGGL(k_grids_tail<1>, g, b, 0, s, a);
+        else hipLaunchKernelGGL(k_grids_tail<0>, g, b, 0, s, a);
+        return hipGetLastError();
+    }
     const dim3 grid(2048), block(256);
     if (precision == 1) hipLaunchKernelGGL((k_grids_walk<float, 1, 2>), grid, block, 0, s, a, lanes);
     else hipLaunchKernelGGL((k_grids_walk<float, 0, 2>), grid, block, 0, s, a, lanes);
