@@ -525,10 +525,12 @@ PrepArgs make_prep_args(gammax_ctx* c, const CallSetup& cs) {
     return pa;
 }
 
-gammax_status_t enqueue_prep(gammax_ctx* c, const CallSetup& cs, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+// joined: see launch_prep.
+gammax_status_t enqueue_prep(gammax_ctx* c, const CallSetup& cs, bool joined, hipStream_t s, hipEvent_t ev0,
+                             hipEvent_t ev1) {
     if (ev0) HIPCHK(c, hipEventRecord(ev0, s));
     const PrepArgs pa = make_prep_args(c, cs);
-    HIPCHK(c, launch_prep(pa, s));
+    HIPCHK(c, launch_prep(pa, joined, s));
     if (ev1) HIPCHK(c, hipEventRecord(ev1, s));
     return GAMMAX_OK;
 }
@@ -938,7 +940,7 @@ gammax_status_t enqueue_steady(gammax_ctx* c, const CallSetup& cs, bool timing, 
     gammax_status_t st;
     const uint32_t n = (uint32_t)cs.n;
     const float r2_cap = round_down_float(c->tab_geom.r2_cap);
-    if ((st = enqueue_prep(c, cs, s, timing ? c->ev[0] : nullptr, timing ? c->ev[1] : nullptr)) != GAMMAX_OK)
+    if ((st = enqueue_prep(c, cs, true, s, timing ? c->ev[0] : nullptr, timing ? c->ev[1] : nullptr)) != GAMMAX_OK)
         return st;
     return enqueue_search(c, cs, n, r2_cap, s, timing);
 }
@@ -1051,7 +1053,7 @@ gammax_status_t gammax_map(gammax_ctx_t* c, const gammax_problem_t* p, const gam
     }
 
     // table build: compaction first, then the table for the radius found, then the search
-    if ((st = enqueue_prep(c, cs, s, timing ? c->ev[0] : nullptr, timing ? c->ev[1] : nullptr)) != GAMMAX_OK)
+    if ((st = enqueue_prep(c, cs, false, s, timing ? c->ev[0] : nullptr, timing ? c->ev[1] : nullptr)) != GAMMAX_OK)
         return st;
     HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
@@ -1803,7 +1805,7 @@ gammax_status_t enqueue_batch(gammax_ctx* c, BatchState* b, const BatchPlan& P, 
         return GAMMAX_OK;
     }
     for (int i = 0; i < P.n; ++i)
-        if ((st = enqueue_prep(b->subs[i], P.cs[i], s, nullptr, nullptr)) != GAMMAX_OK)
+        if ((st = enqueue_prep(b->subs[i], P.cs[i], false, s, nullptr, nullptr)) != GAMMAX_OK)
             return fail(c, st, "pair " + std::to_string(i) + ": " + b->subs[i]->err);
     if (P.key0)
         HIPCHK(c, launch_batch_key0(b->d_pairs, list(BatchPlan::L_KEY0), P.count[BatchPlan::L_KEY0], s));
@@ -2290,7 +2292,7 @@ gammax_status_t gammax_map_noalloc(const gammax_problem_t* p, const gammax_optio
     pa.nodes = nodes_arr;
     pa.sums = L.sums;
     pa.mbits = reinterpret_cast<unsigned long long*>(L.blockcnt + prep_mbits_offset(n));
-    HIPCHK(nullptr, launch_prep(pa, s));
+    HIPCHK(nullptr, launch_prep(pa, false, s));
     Scalars h{};
     if ((st = na_read_scalars(L, &h, s)) != GAMMAX_OK) return st;
     if ((st = scalar_errors(nullptr, h, p->norm == GAMMAX_LOCAL)) != GAMMAX_OK) return st;

@@ -38,8 +38,10 @@ constexpr uint32_t LONG_WALK_ROWS = 256;
 // contended atomics on a single address).
 struct BlockSums {
     unsigned long long pass, border, fp64, cells;
-    uint32_t maxg2, pad;
+    uint32_t maxg2;
+    uint32_t prep;   // one-launch compaction: its block's max gamma0^2 bits, | PREP_BAD (else 0)
 };
+constexpr uint32_t PREP_BAD = 1u << 31;   // a dose of the block is not finite (gamma0^2 has no sign)
 constexpr int SUM_BINS = 256;   // partial-count slots of one gamma map (zeroed by the prep)
 
 // One row of the sorted cell table.  Everything that depends only on the cell offset
@@ -119,7 +121,13 @@ int64_t prep_words(int64_t n);
 // Offset (32-bit words, even) of the mask bits within the prep words: after the tile counts
 // and the group words.
 int64_t prep_mbits_offset(int64_t n);
-hipError_t launch_prep(const PrepArgs& a, hipStream_t s);
+// Largest grid that one launch compacts.  Every block reads all of D_r, so its time grows with
+// the grid while three launches cost about the same: whole maps of n x n nodes took 41.6 us
+// against 43.0 (n = 224) and 43.1 against 42.6 (256).
+constexpr int64_t PREP_SMALL_MAX = 49152;
+// joined: the search's closing kernel runs before the scalars are read, so that r2_bits and
+// flags may still lie in the partial slots.
+hipError_t launch_prep(const PrepArgs& a, bool joined, hipStream_t s);
 // Only the dose maximum, the finiteness flag, the threshold value and the global 1/dD
 // (uses ref, ev, n, thr, dd, sc, part).
 hipError_t launch_dose_scalars(const PrepArgs& a, hipStream_t s);

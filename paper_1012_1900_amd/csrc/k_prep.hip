@@ -1,7 +1,7 @@
 // Normalisation, mask, gamma0 and ordered compaction (Algorithm A2 step 2, "Kernel 1"),
 // plus the stand-alone pass-rate reduction.
 //
-// Three launches, each a coalesced stream over the dose arrays; results cross blocks only
+// Three launches (one for small grids, k_prep_small), each a coalesced stream over the dose arrays; results cross blocks only
 // at kernel boundaries or through atomic adds (a cross-block hand-over inside a kernel
 // would need device-scope release fences, which write back the XCD's L2):
 //   1. maximum and finiteness of D_r: one partial per block (block 0 also clears the
@@ -118,6 +118,26 @@ __device__ __forceinline__ bool node_masked(float dr, float thr_val, int local) 
     return dr >= thr_val && (!local || dr > 0.0f);
 }
 
+// The scalars that every map starts with, but flags and n_masked.
+__device__ __forceinline__ void prep_scalars(Scalars* sc, uint32_t dm, float thr_val, float inv_dd) {
+    sc->dmax_ord = dm;
+    sc->thr_val = thr_val;
+    sc->inv_dd = inv_dd;
+    sc->r2_bits = 0u;
+    sc->n_tail = 0u;
+    sc->n_guard = 0u;
+    sc->maxg2_bits = 0u;
+    sc->n_fallback = 0u;
+    sc->sort_overflow = 0u;
+    sc->long_rows = 0u;
+    sc->n_fallback_inline = 0u;
+    sc->ticket = 0u;
+    sc->n_pass = 0ull;
+    sc->n_border = 0ull;
+    sc->n_fp64 = 0ull;
+    sc->n_cells = 0ull;
+}
+
 // 2. every block: the dose maximum from the partials, then per tile the masked count, max
 // gamma0^2 and -1 for unmasked nodes.  Block 0 stores the scalars of this map.
 __device__ __forceinline__ void prep_count_body(const PrepArgs& a, int nb_red, int vb) {
@@ -154,25 +174,9 @@ __device__ __forceinline__ void prep_count_body(const PrepArgs& a, int nb_red, i
     if (vb == 0) {
         for (int j = threadIdx.x; j < SUM_BINS; j += PREP_THREADS) a.sums[j] = BlockSums{};
         if (threadIdx.x == 0) {
-            Scalars* sc = a.sc;
-            sc->dmax_ord = dm;
-            if (bad) atomicOr(&sc->flags, FLAG_NONFINITE);
-            sc->thr_val = thr_val;
-            sc->inv_dd = inv_dd_g;
-            sc->r2_bits = 0u;
-            sc->n_masked = 0u;
-            sc->n_tail = 0u;
-            sc->n_guard = 0u;
-            sc->maxg2_bits = 0u;
-            sc->n_fallback = 0u;
-            sc->sort_overflow = 0u;
-            sc->long_rows = 0u;
-            sc->n_fallback_inline = 0u;
-            sc->ticket = 0u;
-            sc->n_pass = 0ull;
-            sc->n_border = 0ull;
-            sc->n_fp64 = 0ull;
-            sc->n_cells = 0ull;
+            if (bad) atomicOr(&a.sc->flags, FLAG_NONFINITE);
+            prep_scalars(a.sc, dm, thr_val, inv_dd_g);
+            a.sc->n_masked = 0u;
         }
     }
     uint32_t cnt = 0u, best = 0u;
@@ -272,6 +276,116 @@ __device__ __forceinline__ void prep_emit_body(const PrepArgs& a, int vb) {
 }
 
 __global__ __launch_bounds__(PREP_THREADS) void k_prep_emit(PrepArgs a) { prep_emit_body(a, blockIdx.x); }
+
+// 1-3 in one launch, for grids where the three launches cost more than the work in them: every
+// block of 1024 nodes reads all of D_r itself (from L2 after the first), takes the maximum and
+// counts the masked nodes before its own, so nothing crosses blocks but the largest gamma0^2
+// and the finiteness of D_e, which go to the block's partial slot and are joined where the
+// counts are.  Launch latency and one pass of dependent loads bound it: 4.5 us at 64x64 and 7.7
+// at 173x200, against 10.0 and 10.5 in three launches and the gaps between them.
+constexpr int SMALL_THREADS = 1024, SMALL_STEP = 8;
+constexpr int SMALL_STEPS = (int)(PREP_SMALL_MAX / (SMALL_THREADS * SMALL_STEP));
+static_assert(PREP_SMALL_MAX % (SMALL_THREADS * SMALL_STEP) == 0, "whole steps");
+static_assert(PREP_SMALL_MAX / SMALL_THREADS <= SUM_BINS, "one partial slot per block");
+
+__global__ __launch_bounds__(SMALL_THREADS) void k_prep_small(PrepArgs a) {
+    constexpr int W = SMALL_THREADS / WAVE;
+    __shared__ uint32_t s_a[W], s_b[W], s_c[W];
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    const int vb = blockIdx.x, n = (int)a.n;
+    const int i = vb * SMALL_THREADS + (int)threadIdx.x;
+    const float dr = a.ref[i < n ? i : n - 1], de = a.ev[i < n ? i : n - 1];
+    float r[SMALL_STEPS][SMALL_STEP];
+    // the bits as integers: the largest of them is the largest dose where one is not negative;
+    // finiteness from the largest magnitude
+    int32_t mi = INT32_MIN;
+    uint32_t ma = 0u;
+#pragma unroll
+    for (int g = 0; g < SMALL_STEPS; ++g)
+        if (g * SMALL_STEP * SMALL_THREADS < n)
+#pragma unroll
+            for (int k = 0; k < SMALL_STEP; ++k) {
+                const int j = (g * SMALL_STEP + k) * SMALL_THREADS + (int)threadIdx.x;
+                r[g][k] = a.ref[j < n ? j : n - 1];
+            }
+#pragma unroll
+    for (int g = 0; g < SMALL_STEPS; ++g)
+        if (g * SMALL_STEP * SMALL_THREADS < n)
+#pragma unroll
+            for (int k = 0; k < SMALL_STEP; ++k) {
+                mi = max(mi, (int32_t)f2u(r[g][k]));
+                ma = max(ma, f2u(r[g][k]) & 0x7fffffffu);
+            }
+    uint32_t dm = float_to_ord(u2f((uint32_t)mi));
+    if (mi < 0) {   // this thread's doses are all negative: integers order those the other way
+        for (int j = (int)threadIdx.x; j < n; j += SMALL_THREADS) dm = max(dm, float_to_ord(a.ref[j]));
+    }
+    dm = wave_max_u32(dm);
+    bool bad = __ballot(!isfinite(u2f(ma)) || (i < n && !isfinite(de))) != 0ull;
+    if (lane == 0) {
+        s_a[w] = dm;
+        s_b[w] = bad ? 1u : 0u;
+    }
+    __syncthreads();
+    bad = false;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        dm = max(dm, s_a[k]);
+        bad |= s_b[k] != 0u;
+    }
+    const float dmax = ord_to_float(dm);
+    const float thr_val = a.thr * dmax;
+    const float inv_dd_g = 1.0f / (a.dd * dmax);
+    // the masked nodes before this block's (block vb's nodes are step vb of the loop)
+    uint32_t before = 0u;
+#pragma unroll
+    for (int g = 0; g < SMALL_STEPS; ++g)
+        if (g * SMALL_STEP < vb)
+#pragma unroll
+            for (int k = 0; k < SMALL_STEP; ++k)
+                if (g * SMALL_STEP + k < vb)
+                    before += (uint32_t)__popcll(__ballot(node_masked(r[g][k], thr_val, a.local)));
+    const bool m = i < n && node_masked(dr, thr_val, a.local);
+    const unsigned long long bal = __ballot(m);
+    uint32_t best = 0u;
+    if (m) best = f2u(gamma0_sq(de, dr, node_inv_dd(dr, inv_dd_g, a.dd, a.local)));
+    else if (i < n) a.gamma[i] = -1.0f;
+    best = wave_max_u32(best);
+    __syncthreads();   // (s_a, s_b are read)
+    if (lane == 0) {
+        s_a[w] = before;
+        s_b[w] = (uint32_t)__popcll(bal);
+        s_c[w] = best;
+    }
+    __syncthreads();
+    uint32_t off = 0u, tot = 0u;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        off += s_a[k] + (k < w ? s_b[k] : 0u);
+        tot += s_a[k] + s_b[k];
+        best = max(best, s_c[k]);
+    }
+    const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (WAVE - lane));
+    if (m) a.nodes[off + (uint32_t)__popcll(bal & lt)] = (uint32_t)i;
+    // the partial slots: this block's, and block 0 those that no block has
+    if (threadIdx.x == 0) {
+        BlockSums b{};
+        b.prep = (best & ~PREP_BAD) | (bad ? PREP_BAD : 0u);   // (a NaN of finite doses has either sign)
+        a.sums[vb] = b;
+    }
+    if (vb == 0) {
+        const int j = (int)gridDim.x + (int)threadIdx.x;
+        if (j < SUM_BINS) a.sums[j] = BlockSums{};
+    }
+    // the scalars but n_masked: block 0; n_masked: the last block
+    if (threadIdx.x == 0) {
+        if (vb == 0) {
+            a.sc->flags = 0u;
+            prep_scalars(a.sc, dm, thr_val, inv_dd_g);
+        }
+        if (vb == (int)gridDim.x - 1) a.sc->n_masked = tot;
+    }
+}
 
 // Same-address atomics from many blocks serialise (1024 blocks on three counters set the
 // kernel's time: 25 us for 0.3 M nodes, 4.0 us now), so at most 256 blocks of 1024 threads run,
@@ -379,7 +493,12 @@ int64_t prep_mbits_offset(int64_t n) {
 
 int64_t prep_words(int64_t n) { return prep_mbits_offset(n) + 2 * prep_tiles(n) * (PREP_TILE / 64); }
 
-hipError_t launch_prep(const PrepArgs& a, hipStream_t s) {
+hipError_t launch_prep(const PrepArgs& a, bool joined, hipStream_t s) {
+    if (joined && a.n <= PREP_SMALL_MAX) {
+        const unsigned nb = (unsigned)((a.n + SMALL_THREADS - 1) / SMALL_THREADS);
+        hipLaunchKernelGGL(k_prep_small, dim3(nb), dim3(SMALL_THREADS), 0, s, a);
+        return hipGetLastError();
+    }
     const int nbr = reduce_blocks(a.n);
     const int64_t nb = prep_tiles(a.n);
     hipLaunchKernelGGL(k_dose_max, dim3(nbr), dim3(PREP_THREADS), 0, s, a);

@@ -2295,32 +2295,39 @@ __global__ __launch_bounds__(SEARCH_THREADS) __attribute__((amdgpu_waves_per_eu(
 template <bool ADD = false>
 __device__ __forceinline__ void finalize_body(const BlockSums* __restrict__ sums, int n, Scalars* sc,
                                               float r2_cap) {
-    if (threadIdx.x == 0 && u2f(sc->r2_bits) > r2_cap && sc->n_masked > 0) sc->flags |= FLAG_TABLE_SHORT;
     unsigned long long p = 0, b = 0, f = 0, c = 0;
-    uint32_t m = 0;
+    uint32_t m = 0, r2 = 0, bad = 0;
     for (int j = threadIdx.x; j < n; j += SEARCH_THREADS) {
         p += sums[j].pass;
         b += sums[j].border;
         f += sums[j].fp64;
         c += sums[j].cells;
         m = max(m, sums[j].maxg2);
+        r2 = max(r2, sums[j].prep & ~PREP_BAD);
+        bad |= sums[j].prep & PREP_BAD;
     }
     __shared__ unsigned long long s[4][SEARCH_THREADS];
-    __shared__ uint32_t sm[SEARCH_THREADS];
+    __shared__ uint32_t sm[SEARCH_THREADS], sr[SEARCH_THREADS];
+    bad = (uint32_t)__syncthreads_or((int)bad);
     s[0][threadIdx.x] = p;
     s[1][threadIdx.x] = b;
     s[2][threadIdx.x] = f;
     s[3][threadIdx.x] = c;
     sm[threadIdx.x] = m;
+    sr[threadIdx.x] = r2;
     __syncthreads();
     for (int h = SEARCH_THREADS / 2; h > 0; h >>= 1) {
         if ((int)threadIdx.x < h) {
             for (int k = 0; k < 4; ++k) s[k][threadIdx.x] += s[k][threadIdx.x + h];
             sm[threadIdx.x] = max(sm[threadIdx.x], sm[threadIdx.x + h]);
+            sr[threadIdx.x] = max(sr[threadIdx.x], sr[threadIdx.x + h]);
         }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
+        if (sr[0] > sc->r2_bits) sc->r2_bits = sr[0];
+        if (bad != 0u) sc->flags |= FLAG_NONFINITE;
+        if (u2f(sc->r2_bits) > r2_cap && sc->n_masked > 0) sc->flags |= FLAG_TABLE_SHORT;
         if (ADD) {
             if (s[0][0]) atomicAdd(&sc->n_pass, s[0][0]);
             if (s[1][0]) atomicAdd(&sc->n_border, s[1][0]);
@@ -2361,7 +2368,7 @@ __device__ __forceinline__ void finish_counts(const BlockSums* __restrict__ sums
     constexpr int W = (int)(sizeof(Scalars) / sizeof(uint32_t));
     __shared__ __align__(8) uint32_t s_sc[W];
     unsigned long long p = 0, b = 0, f = 0, c = 0;
-    uint32_t m = 0;
+    uint32_t m = 0, r2 = 0, bad = 0;
     if (threadIdx.x < SUM_BINS) {
         const BlockSums v = sums[threadIdx.x];
         p = v.pass;
@@ -2369,17 +2376,21 @@ __device__ __forceinline__ void finish_counts(const BlockSums* __restrict__ sums
         f = v.fp64;
         c = v.cells;
         m = v.maxg2;
+        r2 = v.prep & ~PREP_BAD;
+        bad = v.prep & PREP_BAD;
     }
     if (threadIdx.x < W) s_sc[threadIdx.x] = reinterpret_cast<const uint32_t*>(sc)[threadIdx.x];
     __shared__ unsigned long long s[4][SEARCH_THREADS / WAVE];
-    __shared__ uint32_t sm[SEARCH_THREADS / WAVE];
+    __shared__ uint32_t sm[SEARCH_THREADS / WAVE], sr[SEARCH_THREADS / WAVE];
     for (int o = WAVE / 2; o > 0; o >>= 1) {
         p += (unsigned long long)__shfl_xor((long long)p, o);
         b += (unsigned long long)__shfl_xor((long long)b, o);
         f += (unsigned long long)__shfl_xor((long long)f, o);
         c += (unsigned long long)__shfl_xor((long long)c, o);
         m = max(m, (uint32_t)__shfl_xor((int)m, o));
+        r2 = max(r2, (uint32_t)__shfl_xor((int)r2, o));
     }
+    bad = __ballot(bad != 0u) != 0ull ? PREP_BAD : 0u;
     if ((threadIdx.x & (WAVE - 1)) == 0) {
         const int w = threadIdx.x / WAVE;
         s[0][w] = p;
@@ -2387,10 +2398,15 @@ __device__ __forceinline__ void finish_counts(const BlockSums* __restrict__ sums
         s[2][w] = f;
         s[3][w] = c;
         sm[w] = m;
+        sr[w] = r2 | bad;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         Scalars* l = reinterpret_cast<Scalars*>(s_sc);
+        for (int w = 0; w < SEARCH_THREADS / WAVE; ++w) {
+            l->r2_bits = max(l->r2_bits, sr[w] & ~PREP_BAD);
+            if (sr[w] & PREP_BAD) l->flags |= FLAG_NONFINITE;
+        }
         if (u2f(l->r2_bits) > r2_cap && l->n_masked > 0) l->flags |= FLAG_TABLE_SHORT;
         for (int w = 0; w < SEARCH_THREADS / WAVE; ++w) {
             l->n_pass += s[0][w];
