@@ -6,9 +6,11 @@ HIP stream.  Importing this module fails loudly when the library has not been bu
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
 import math
 import os
+import struct
 import threading
 from dataclasses import dataclass
 from typing import Optional, Sequence, Tuple
@@ -226,14 +228,40 @@ class GammaResult:
     long_walk_rows: int = 0
 
 
-def _torch():
-    import torch
-    return torch
+# A map of a small plane takes the library about 25 us, so what the binding adds to a call counts:
+# 11.5 us with a getattr per result field, a stream object and a device guard per call, 6.6 with
+# the three helpers below.
+_RESULT_STRUCT = struct.Struct("@" + "".join(t._type_ for _, t in Result._fields_))
+assert _RESULT_STRUCT.size <= C.sizeof(Result)
+assert [f for f, _ in Result._fields_] == list(GammaResult.__dataclass_fields__)
+
+
+def _result(r) -> GammaResult:
+    return GammaResult(*_RESULT_STRUCT.unpack_from(r))
+
+
+_NO_GUARD = contextlib.nullcontext()
+
+
+def _on_device(device, ctx=None):
+    """Guard of the current device around a call on ``device``: none needed where it is the
+    current one already and the context's (the library selects the context's device)."""
+    if device.index == torch.cuda.current_device() and (ctx is None or ctx.device == device.index):
+        return _NO_GUARD
+    return torch.cuda.device(device)
+
+
+def _raw_stream(stream, device):
+    """HIP stream handle of ``stream``, or of the current stream of ``device``."""
+    if stream is not None:
+        return stream.cuda_stream
+    if device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _dev_tensor(t, name):
-    torch = _torch()
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a device (cuda/hip) tensor")
     if t.dtype != torch.float32:
         raise TypeError(f"{name} must be float32")
@@ -299,7 +327,6 @@ def gammax_map(ref, ev, spacing: Sequence[float], dd: float, dta: float,
     in mm in the same axis order.  gamma is -1 where a node is not evaluated.
     ``order_key``: with ``sort="given"``, a float32 device tensor shaped like ``ref``.
     """
-    torch = _torch()
     _dev_tensor(ref, "ref")
     _dev_tensor(ev, "ev")
     if ref.shape != ev.shape or ref.device != ev.device:
@@ -318,12 +345,12 @@ def gammax_map(ref, ev, spacing: Sequence[float], dd: float, dta: float,
     o = make_options(sort, precision, cond_threshold, timing, tail_lanes, cell_lanes, radius, model,
                      radius_factor, cnn_pool, projection, _order_key_ptr(order_key, ref))
     r = Result()
-    s = stream if stream is not None else torch.cuda.current_stream(ref.device)
-    with torch.cuda.device(ref.device):
+    s = _raw_stream(stream, ref.device)
+    with _on_device(ref.device, ctx):
         st = _lib.gammax_map(ctx.handle, C.byref(p), C.byref(o), ref.data_ptr(), ev.data_ptr(),
-                             out.data_ptr(), C.byref(r), _vp(s.cuda_stream))
+                             out.data_ptr(), C.byref(r), s)
     ctx.check(st)
-    res = GammaResult(**{f[0]: getattr(r, f[0]) for f in Result._fields_})
+    res = _result(r)
     return out, res
 
 
@@ -339,7 +366,7 @@ class MapTicket:
         if self._res is None:
             r = Result()
             self.ctx.check(_lib.gammax_map_wait(self.ctx.handle, self.ticket, C.byref(r)))
-            self._res = GammaResult(**{f[0]: getattr(r, f[0]) for f in Result._fields_})
+            self._res = _result(r)
             self._keep = None
         return self._res
 
@@ -353,7 +380,6 @@ def gammax_map_async(ref, ev, spacing: Sequence[float], dd: float, dta: float,
     """Queue a gamma map without waiting (``gammax_map_async``); the returned ticket's
     ``wait()`` gives the GammaResult.  The tensors are kept alive until then and must not
     be modified before it."""
-    torch = _torch()
     _dev_tensor(ref, "ref")
     _dev_tensor(ev, "ev")
     if ref.shape != ev.shape or ref.device != ev.device:
@@ -372,10 +398,10 @@ def gammax_map_async(ref, ev, spacing: Sequence[float], dd: float, dta: float,
     o = make_options(sort, precision, cond_threshold, False, tail_lanes, cell_lanes, radius, model,
                      radius_factor, cnn_pool, projection, _order_key_ptr(order_key, ref))
     t = C.c_uint64(0)
-    s = stream if stream is not None else torch.cuda.current_stream(ref.device)
-    with torch.cuda.device(ref.device):
+    s = _raw_stream(stream, ref.device)
+    with _on_device(ref.device, ctx):
         st = _lib.gammax_map_async(ctx.handle, C.byref(p), C.byref(o), ref.data_ptr(), ev.data_ptr(),
-                                   out.data_ptr(), C.byref(t), _vp(s.cuda_stream))
+                                   out.data_ptr(), C.byref(t), s)
     ctx.check(st)
     return MapTicket(ctx, t.value, out, (ref, ev, model, order_key))
 
@@ -384,7 +410,6 @@ def gamma_map(ref_dose, eval_dose, spacing: Sequence[float], dd: float, dta: flo
               dose_threshold: float = 0.1, local: bool = False) -> Tuple[object, float]:
     """The paper's problem statement: (gamma tensor, pass rate) with default options,
     through the flat C entry point ``gamma_map``."""
-    torch = _torch()
     _dev_tensor(ref_dose, "ref_dose")
     _dev_tensor(eval_dose, "eval_dose")
     if ref_dose.shape != eval_dose.shape:
@@ -394,11 +419,11 @@ def gamma_map(ref_dose, eval_dose, spacing: Sequence[float], dd: float, dta: flo
     sp = (C.c_double * 3)(*(list(map(float, spacing)) + [0.0] * (3 - nd)))
     out = torch.empty_like(ref_dose)
     pr = C.c_double(float("nan"))
-    s = torch.cuda.current_stream(ref_dose.device)
-    with torch.cuda.device(ref_dose.device):
+    s = _raw_stream(None, ref_dose.device)
+    with _on_device(ref_dose.device):
         st = _lib.gamma_map(ref_dose.data_ptr(), eval_dose.data_ptr(), nd, shape, sp, float(dd),
                             float(dta), float(dose_threshold), LOCAL if local else GLOBAL,
-                            out.data_ptr(), C.byref(pr), _vp(s.cuda_stream))
+                            out.data_ptr(), C.byref(pr), s)
     if st != OK:
         raise GammaxError(st)
     return out, pr.value
@@ -416,7 +441,6 @@ def gammax_map_noalloc(ref, ev, spacing: Sequence[float], dd: float, dta: float,
     workspace is the library's fixed device array).  ``out`` (float32, shaped like ``ref``)
     receives gamma and must be given: the binding allocates nothing either.  Returns the
     GammaResult.  Calls that overlap on one GPU race."""
-    torch = _torch()
     _dev_tensor(ref, "ref")
     _dev_tensor(ev, "ev")
     _dev_tensor(out, "out")
@@ -428,29 +452,27 @@ def gammax_map_noalloc(ref, ev, spacing: Sequence[float], dd: float, dta: float,
     o = make_options(sort, precision, cond_threshold, False, tail_lanes, cell_lanes, "plain", None, 1.1, 0,
                      projection, None)
     r = Result()
-    s = stream if stream is not None else torch.cuda.current_stream(ref.device)
-    with torch.cuda.device(ref.device):
+    s = _raw_stream(stream, ref.device)
+    with _on_device(ref.device):
         st = _lib.gammax_map_noalloc(C.byref(p), C.byref(o), ref.data_ptr(), ev.data_ptr(), out.data_ptr(),
-                                     C.byref(r), _vp(s.cuda_stream))
+                                     C.byref(r), s)
     if st != OK:
         raise GammaxError(st)
-    return GammaResult(**{f[0]: getattr(r, f[0]) for f in Result._fields_})
+    return _result(r)
 
 
 def sort_pairs(keys, vals, ctx: Optional[Context] = None):
     """Stable ascending sort of uint32 (key, value) pairs in place (int32 tensors holding
     the uint32 bit patterns)."""
-    torch = _torch()
     for t, nm in ((keys, "keys"), (vals, "vals")):
         if t.device.type != "cuda" or t.dtype != torch.int32 or not t.is_contiguous():
             raise TypeError(f"{nm} must be a contiguous int32 device tensor")
     if keys.numel() != vals.numel():
         raise ValueError("keys and vals differ in length")
     ctx = ctx or context(keys.device.index or 0)
-    s = torch.cuda.current_stream(keys.device)
-    with torch.cuda.device(keys.device):
-        st = _lib.gammax_sort_pairs(ctx.handle, keys.data_ptr(), vals.data_ptr(), keys.numel(),
-                                    _vp(s.cuda_stream))
+    s = _raw_stream(None, keys.device)
+    with _on_device(keys.device, ctx):
+        st = _lib.gammax_sort_pairs(ctx.handle, keys.data_ptr(), vals.data_ptr(), keys.numel(), s)
     ctx.check(st)
     return keys, vals
 
@@ -458,7 +480,6 @@ def sort_pairs(keys, vals, ctx: Optional[Context] = None):
 def build_table(shape: Sequence[int], spacing_over_dta: Sequence[float], radius: float,
                 cap: Optional[int] = None, device: int = 0, ctx: Optional[Context] = None):
     """Sorted cell table: (key2 float32 tensor [T], offsets int32 tensor [T, 3])."""
-    torch = _torch()
     nd = len(shape)
     if cap is None:
         cap = 1
@@ -472,24 +493,22 @@ def build_table(shape: Sequence[int], spacing_over_dta: Sequence[float], radius:
     shp = (C.c_int64 * 3)(*(list(shape) + [0] * (3 - nd)))
     sp = (C.c_double * 3)(*(list(map(float, spacing_over_dta)) + [0.0] * (3 - nd)))
     ctx = ctx or context(device)
-    s = torch.cuda.current_stream(dev)
-    with torch.cuda.device(dev):
+    s = _raw_stream(None, dev)
+    with _on_device(dev, ctx):
         st = _lib.gammax_build_table(ctx.handle, nd, shp, sp, float(radius), key2.data_ptr(),
-                                     offs.data_ptr(), int(cap), C.byref(n), _vp(s.cuda_stream))
+                                     offs.data_ptr(), int(cap), C.byref(n), s)
     ctx.check(st)
     return key2[: n.value], offs[: n.value]
 
 
 def pass_count(gamma, ctx: Optional[Context] = None) -> Tuple[int, int, int]:
     """(evaluated, pass, borderline) counts of a gamma map on the device."""
-    torch = _torch()
     _dev_tensor(gamma, "gamma")
     ctx = ctx or context(gamma.device.index or 0)
     counts = (C.c_uint64 * 3)()
-    s = torch.cuda.current_stream(gamma.device)
-    with torch.cuda.device(gamma.device):
-        st = _lib.gammax_pass_count(ctx.handle, gamma.data_ptr(), gamma.numel(), counts,
-                                    _vp(s.cuda_stream))
+    s = _raw_stream(None, gamma.device)
+    with _on_device(gamma.device, ctx):
+        st = _lib.gammax_pass_count(ctx.handle, gamma.data_ptr(), gamma.numel(), counts, s)
     ctx.check(st)
     return int(counts[0]), int(counts[1]), int(counts[2])
 
@@ -600,7 +619,6 @@ class Model:
 
     def forward(self, feats):
         """y for a batch of feature crops: int16/uint16 tensor (B, c0+8, c1+8, c2+8, 2)."""
-        torch = _torch()
         if feats.dim() != 5 or feats.shape[-1] != 2 or feats.dtype not in (torch.int16, torch.uint16):
             raise ValueError("features must be a (B, z, y, x, 2) 16-bit tensor")
         if not feats.is_contiguous() or feats.device.type != "cuda":
@@ -608,16 +626,15 @@ class Model:
         b = feats.shape[0]
         crop = (C.c_int64 * 3)(*[int(n) - 8 for n in feats.shape[1:4]])
         y = torch.empty((b, crop[0], crop[1], crop[2]), dtype=torch.float32, device=feats.device)
-        s = torch.cuda.current_stream(feats.device)
-        with torch.cuda.device(feats.device):
-            st = _lib.gammax_model_forward(self.handle, b, crop, feats.data_ptr(), y.data_ptr(), _vp(s.cuda_stream))
+        s = _raw_stream(None, feats.device)
+        with _on_device(feats.device, self):
+            st = _lib.gammax_model_forward(self.handle, b, crop, feats.data_ptr(), y.data_ptr(), s)
         self.check(st)
         return y
 
     def train_step(self, feats, gamma, lr: float, beta1: float = 0.9, beta2: float = 0.999,
                    eps: float = 1e-8) -> float:
         """One Adam step on a batch of crops; returns the loss before the step."""
-        torch = _torch()
         if feats.dim() != 5 or feats.shape[-1] != 2 or feats.dtype not in (torch.int16, torch.uint16):
             raise ValueError("features must be a (B, z, y, x, 2) 16-bit tensor")
         _dev_tensor(gamma, "gamma")
@@ -627,26 +644,25 @@ class Model:
             raise ValueError("gamma must have shape (B, c0, c1, c2)")
         hp = Adam(lr, beta1, beta2, eps)
         loss = C.c_double()
-        s = torch.cuda.current_stream(feats.device)
-        with torch.cuda.device(feats.device):
+        s = _raw_stream(None, feats.device)
+        with _on_device(feats.device, self):
             st = _lib.gammax_model_train_step(self.handle, b, crop, feats.data_ptr(), gamma.data_ptr(),
-                                              C.byref(hp), C.byref(loss), _vp(s.cuda_stream))
+                                              C.byref(hp), C.byref(loss), s)
         self.check(st)
         return loss.value
 
     def predict(self, ref, ev, spacing: Sequence[float], dd: float, dta: float = 3.0,
                 ctx: Optional[Context] = None):
         """y = log(gamma_hat + 0.01) on the grid of a 3D dose pair (float32 tensor)."""
-        torch = _torch()
         _dev_tensor(ref, "ref")
         _dev_tensor(ev, "ev")
         ctx = ctx or context(ref.device.index or 0)
         prob = make_problem(ref.shape, spacing, dd, dta, 0.1, False)
         y = torch.empty_like(ref)
-        s = torch.cuda.current_stream(ref.device)
-        with torch.cuda.device(ref.device):
+        s = _raw_stream(None, ref.device)
+        with _on_device(ref.device, ctx):
             st = _lib.gammax_model_predict(ctx.handle, self.handle, C.byref(prob), ref.data_ptr(),
-                                           ev.data_ptr(), y.data_ptr(), _vp(s.cuda_stream))
+                                           ev.data_ptr(), y.data_ptr(), s)
         ctx.check(st)
         return y
 
@@ -657,7 +673,6 @@ def predict_nodes(model, ref, ev, spacing: Sequence[float], dd: float, nodes, dt
     ``pool=2``: from the pair average-pooled 2x2x2 (``gammax_model_predict_nodes_pooled``)."""
     if pool not in (0, 2):
         raise ValueError("pool must be 0 or 2")
-    torch = _torch()
     _dev_tensor(ref, "ref")
     _dev_tensor(ev, "ev")
     if nodes.dtype != torch.int32 or nodes.device != ref.device or not nodes.is_contiguous():
@@ -665,11 +680,11 @@ def predict_nodes(model, ref, ev, spacing: Sequence[float], dd: float, nodes, dt
     ctx = ctx or context(ref.device.index or 0)
     prob = make_problem(ref.shape, spacing, dd, dta, 0.1, False)
     y = torch.empty(nodes.numel(), dtype=torch.float32, device=ref.device)
-    s = torch.cuda.current_stream(ref.device)
-    with torch.cuda.device(ref.device):
+    s = _raw_stream(None, ref.device)
+    with _on_device(ref.device, ctx):
         fn = _lib.gammax_model_predict_nodes_pooled if pool == 2 else _lib.gammax_model_predict_nodes
         st = fn(ctx.handle, model.handle, C.byref(prob), ref.data_ptr(), ev.data_ptr(), nodes.data_ptr(),
-                nodes.numel(), y.data_ptr(), _vp(s.cuda_stream))
+                nodes.numel(), y.data_ptr(), s)
     ctx.check(st)
     return y
 
@@ -678,7 +693,6 @@ def model_features(ref, ev, spacing: Sequence[float], dd: float, dta: float = 3.
                    ctx: Optional[Context] = None):
     """Input features of a 3D pair on the grid padded by 4: int16 tensor (z+8, y+8, x+8, 2)
     holding bf16 bit patterns."""
-    torch = _torch()
     _dev_tensor(ref, "ref")
     _dev_tensor(ev, "ev")
     if ref.dim() != 3:
@@ -687,10 +701,10 @@ def model_features(ref, ev, spacing: Sequence[float], dd: float, dta: float = 3.
     prob = make_problem(ref.shape, spacing, dd, dta, 0.1, False)
     feat = torch.empty((ref.shape[0] + 8, ref.shape[1] + 8, ref.shape[2] + 8, 2), dtype=torch.int16,
                        device=ref.device)
-    s = torch.cuda.current_stream(ref.device)
-    with torch.cuda.device(ref.device):
+    s = _raw_stream(None, ref.device)
+    with _on_device(ref.device, ctx):
         st = _lib.gammax_model_features(ctx.handle, C.byref(prob), ref.data_ptr(), ev.data_ptr(),
-                                        feat.data_ptr(), _vp(s.cuda_stream))
+                                        feat.data_ptr(), s)
     ctx.check(st)
     return feat
 
@@ -719,7 +733,6 @@ def gammax_batch(pairs, *, precision: str = "guarded", cond_threshold: float = 1
     ``dd``, ``dta`` and optionally ``threshold`` (default 0.1) and ``local`` (default False).
     Returns (list of gamma tensors, list of GammaResult).
     """
-    torch = _torch()
     n = len(pairs)
     if n == 0:
         return [], []
@@ -744,11 +757,11 @@ def gammax_batch(pairs, *, precision: str = "guarded", cond_threshold: float = 1
                      cnn_pool, projection)
     o.autotune = 1 if autotune else 0
     res = (Result * n)()
-    s = stream if stream is not None else torch.cuda.current_stream(dev)
-    with torch.cuda.device(dev):
-        st = _lib.gammax_batch(ctx.handle, n, probs, refs, evs, gams, C.byref(o), res, _vp(s.cuda_stream))
+    s = _raw_stream(stream, dev)
+    with _on_device(dev, ctx):
+        st = _lib.gammax_batch(ctx.handle, n, probs, refs, evs, gams, C.byref(o), res, s)
     ctx.check(st)
-    results = [GammaResult(**{f[0]: getattr(r, f[0]) for f in Result._fields_}) for r in res]
+    results = [_result(r) for r in res]
     return out_list, results
 
 
@@ -769,7 +782,6 @@ def gammax_map_grids(ref, ev, ref_spacing: Sequence[float], ev_spacing: Sequence
     3D): ``ev`` (float32 device tensor) sampled at ``ev_origin + j * ev_spacing`` mm in the
     frame where reference node k sits at ``k * ref_spacing``.  Returns (gamma on the
     reference grid, GammaResult); gamma is -1 where a node is not evaluated."""
-    torch = _torch()
     _dev_tensor(ref, "ref")
     _dev_tensor(ev, "ev")
     if ref.dim() not in (2, 3) or ev.dim() != ref.dim() or ref.device != ev.device:
@@ -789,12 +801,12 @@ def gammax_map_grids(ref, ev, ref_spacing: Sequence[float], ev_spacing: Sequence
         g.origin_mm[i] = float(ev_origin[i])
     o = make_options("none", precision, cond_threshold, False, tail_lanes, 0)
     r = Result()
-    s = stream if stream is not None else torch.cuda.current_stream(ref.device)
-    with torch.cuda.device(ref.device):
+    s = _raw_stream(stream, ref.device)
+    with _on_device(ref.device, ctx):
         st = _lib.gammax_map_grids(ctx.handle, C.byref(p), C.byref(g), ref.data_ptr(), ev.data_ptr(), out.data_ptr(),
-                                   C.byref(o), C.byref(r), _vp(s.cuda_stream))
+                                   C.byref(o), C.byref(r), s)
     ctx.check(st)
-    return out, GammaResult(**{f[0]: getattr(r, f[0]) for f in Result._fields_})
+    return out, _result(r)
 
 
 _lib.gammax_map_many.restype = C.c_int
@@ -812,7 +824,6 @@ def gammax_map_many(pairs, *, sort: str = "none", precision: str = "guarded", co
     ``dd``, ``dta`` and optionally ``threshold`` (default 0.1) and ``local`` (default False).
     Returns (list of gamma tensors, list of GammaResult).
     """
-    torch = _torch()
     n = len(pairs)
     if n == 0:
         return [], []
@@ -835,11 +846,11 @@ def gammax_map_many(pairs, *, sort: str = "none", precision: str = "guarded", co
     ctx = ctx or context(dev.index or 0)
     o = make_options(sort, precision, cond_threshold, False, tail_lanes, 0, radius, model, radius_factor, cnn_pool)
     res = (Result * n)()
-    s = stream if stream is not None else torch.cuda.current_stream(dev)
-    with torch.cuda.device(dev):
-        st = _lib.gammax_map_many(ctx.handle, n, probs, refs, evs, gams, C.byref(o), res, _vp(s.cuda_stream))
+    s = _raw_stream(stream, dev)
+    with _on_device(dev, ctx):
+        st = _lib.gammax_map_many(ctx.handle, n, probs, refs, evs, gams, C.byref(o), res, s)
     ctx.check(st)
-    return out_list, [GammaResult(**{f[0]: getattr(r, f[0]) for f in Result._fields_}) for r in res]
+    return out_list, [_result(r) for r in res]
 
 
 def tune_save(path: str, ctx: Context):
