@@ -243,6 +243,7 @@ __device__ __forceinline__ void conv16_rows(const uint16_t* tile, const U4 (&w)[
     const uint32_t hi = (uint32_t)(g >> 1);
     const char* tb = reinterpret_cast<const char*>(tile);
     const int ry0 = wv * FNRY;
+    if (t.y0 + ry0 >= a.oy) return;   // (no row of this wave is in the output)
     // lane's node (ry0, z 0, x j), channel half g & 1
     const uint32_t rbase = (uint32_t)((ry0 * FLX + j) * NODE_B + (g & 1) * 16);
     // per-kind bases: the second tap of the lane's group (hi) sits one node along x (x pairs),
@@ -329,19 +330,25 @@ __device__ __forceinline__ void conv16_rows(const uint16_t* tile, const U4 (&w)[
     }
 }
 
-// Layer 1 (2 -> 16 channels, ReLU, bf16) of NODES nodes of a box of BX x BY x BZ output
-// nodes, written into a 16-channel LDS tile (node-major, 32 bytes per node).  `feat` is the
-// staged 2-channel input box, (BX + 2) x (BY + 2) x (BZ + 2).  16 consecutive box nodes per
-// product (a lane's node index picks its own input address); 2 chunks of 4 taps x 2
-// channels per lane, in layer 1's k order (l1_tap); each wave takes groups w, w + 8, ..., two at a time.  w0: the layer's
-// 2 fragments of this lane; b0: the biases of this lane's 4 output channels.  The same
-// chunks, operands and rounding as k_conv<2, 0>, so the values are those it stores.
+// Layer 1 (2 -> 16 channels, ReLU, bf16) of a box of BX x BY x BZ output nodes (of its first
+// `rows` rows along y at least), written into a 16-channel LDS tile (node-major, 32 bytes per
+// node).  `feat` is the staged 2-channel input box, (BX + 2) x (BY + 2) x (BZ + 2).  A product
+// takes 16 nodes, 2 chunks of 4 taps x 2 channels per lane in layer 1's k order (l1_tap).
+// w0: the layer's 2 fragments of this lane; b0: the biases of this lane's 4 output channels.
+//
+// A wave takes the rows y = w and w + 8 of every plane, 16 nodes along x each: their addresses
+// differ by immediates, so a product costs its 8 reads and the epilogue.  What the 16 x 16
+// columns leave over (rows from 16 on, nodes from x = 16 on) follows in groups of 16 with
+// an address per lane.  (16 consecutive nodes of the flattened box per product took a division
+// and an address per node and read: most of the fused kernel's vector instructions.  Layers 1
+// and 2 of a 96x128x128 grid: 52 us then, 47 now.)
 template <int BX, int BY, int BZ>
 __device__ __forceinline__ void layer1_to_lds(const uint16_t* feat, uint16_t* out, const U4 (&w0)[2],
-                                              const float (&b0)[4]) {
-    constexpr int NODES = BX * BY * BZ, NGRP = (NODES + 15) / 16;
+                                              const float (&b0)[4], int rows) {
     constexpr int IX = BX + 2, IY = BY + 2;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int WAVES = FTHREADS / 64;
+    static_assert(BX >= 16 && BY >= 2 * WAVES, "the first 16 nodes of 16 rows go to the waves by row");
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int j = lane & 15, g = lane >> 4;
     // per-lane offsets (in input nodes) of the 4 taps of each chunk: tap l1_read_tap(c, g, q)
     int toff[8];
@@ -358,40 +365,57 @@ __device__ __forceinline__ void layer1_to_lds(const uint16_t* feat, uint16_t* ou
             toff[c * 4 + q] = (g & 2) ? ((g & 1) ? tt[3] : tt[2]) : ((g & 1) ? tt[1] : tt[0]);
         }
     const uint32_t* fw = reinterpret_cast<const uint32_t*>(feat);
+    auto product = [&](const uint32_t* (&p)[8], int imm) -> f32x4 {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            acc = mfma_bf16(w0[c], U4{p[4 * c][imm], p[4 * c + 1][imm], p[4 * c + 2][imm], p[4 * c + 3][imm]}, acc);
+        return acc;
+    };
+    auto store = [&](uint16_t* o, const f32x4& v) {
+        uint2 st;
+        st.x = pack2bf(fmaxf(v[0] + b0[0], 0.f), fmaxf(v[1] + b0[1], 0.f));
+        st.y = pack2bf(fmaxf(v[2] + b0[2], 0.f), fmaxf(v[3] + b0[3], 0.f));
+        *reinterpret_cast<uint2*>(o) = st;
+    };
+    {
+        const uint32_t* p[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) p[k] = fw + wv * IX + j + toff[k];
+        uint16_t* o = out + (wv * BX + j) * 16 + 4 * g;
+#pragma unroll
+        for (int yy = 0; yy < 2; ++yy) {
+            if (wv + yy * WAVES >= rows) break;
+#pragma unroll
+            for (int z = 0; z < BZ; ++z)
+                store(o + (z * BY + yy * WAVES) * BX * 16, product(p, (z * IY + yy * WAVES) * IX));
+        }
+    }
+    // left over: EY rows of 16 nodes per plane, then EX nodes of every row
+    constexpr int EX = BX - 16, EY = BY - 2 * WAVES, ROWG = EY * BZ, NB = EX * BY * BZ;
+    constexpr int LEFT = ROWG + (NB + 15) / 16;
+    if constexpr (LEFT > 0) {
 #pragma unroll 1
-    for (int grp = wv; grp < NGRP; grp += 2 * (FTHREADS / 64)) {
-        int n[2], base[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            n[h] = (grp + h * (FTHREADS / 64)) * 16 + j;
-            const int m = n[h] < NODES ? n[h] : NODES - 1;
-            const int lx = m % BX, r = m / BX;
-            base[h] = ((r / BY) * IY + r % BY) * IX + lx;
-        }
-        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            U4 b0v, b1v;
-            b0v.x = fw[base[0] + toff[c * 4 + 0]];
-            b0v.y = fw[base[0] + toff[c * 4 + 1]];
-            b0v.z = fw[base[0] + toff[c * 4 + 2]];
-            b0v.w = fw[base[0] + toff[c * 4 + 3]];
-            b1v.x = fw[base[1] + toff[c * 4 + 0]];
-            b1v.y = fw[base[1] + toff[c * 4 + 1]];
-            b1v.z = fw[base[1] + toff[c * 4 + 2]];
-            b1v.w = fw[base[1] + toff[c * 4 + 3]];
-            acc0 = mfma_bf16(w0[c], b0v, acc0);
-            acc1 = mfma_bf16(w0[c], b1v, acc1);
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const f32x4 v = h ? acc1 : acc0;
-            if (n[h] < NODES) {
-                uint2 st;
-                st.x = pack2bf(fmaxf(v[0] + b0[0], 0.f), fmaxf(v[1] + b0[1], 0.f));
-                st.y = pack2bf(fmaxf(v[2] + b0[2], 0.f), fmaxf(v[3] + b0[3], 0.f));
-                *reinterpret_cast<uint2*>(&out[n[h] * 16 + 4 * g]) = st;
+        for (int q = wv; q < LEFT; q += WAVES) {
+            int x, y, z;
+            bool in = true;
+            if (q < ROWG) {
+                x = j;
+                y = 2 * WAVES + q % EY;
+                z = q / EY;
+            } else {
+                const int n = (q - ROWG) * 16 + j;
+                in = n < NB;
+                const int m = in ? n : NB - 1, r = m / EX;
+                x = 16 + m % EX;
+                y = r % BY;
+                z = r / BY;
             }
+            const uint32_t* p[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) p[k] = fw + (z * IY + y) * IX + x + toff[k];
+            const f32x4 v = product(p, 0);
+            if (in) store(out + ((z * BY + y) * BX + x) * 16 + 4 * g, v);
         }
     }
 }
@@ -433,7 +457,7 @@ __global__ __launch_bounds__(FTHREADS) __attribute__((amdgpu_waves_per_eu(4))) v
         for (int r = 0; r < 4; ++r) b0[r] = bl[4 * g + r];
         // compute into LDS rows, then copy out: reuse the rows of the output box
         __shared__ __align__(16) uint16_t ob[FX * FY * FZ * 16];
-        layer1_to_lds<FX, FY, FZ>(tile, ob, w0, b0);
+        layer1_to_lds<FX, FY, FZ>(tile, ob, w0, b0, a.oy - t.y0);
         __syncthreads();
         // store the box: 2 x 16 bytes per node, node-major as the output volume
         for (int u = threadIdx.x; u < FX * FY * FZ * 2; u += FTHREADS) {
@@ -485,7 +509,7 @@ __global__ __launch_bounds__(FTHREADS) __attribute__((amdgpu_waves_per_eu(4))) v
     stage_box<2, FX + 4, FY + 4, FZ + 4>(a.feat + (int64_t)t.vol * a.feat_vstride, a.fx, a.fy, a.fz, t.x0, t.y0,
                                          t.z0, fb);
     __syncthreads();
-    layer1_to_lds<FLX, FLY, FLZ>(fb, tile, w0, b0);
+    layer1_to_lds<FLX, FLY, FLZ>(fb, tile, w0, b0, l2.oy - t.y0 + 2);
     __syncthreads();
     conv16_rows<0>(tile, w2, bl, l2, t);
 }
