@@ -40,6 +40,7 @@ struct BlockSums {
     unsigned long long pass, border, fp64, cells;
     uint32_t maxg2;
     uint32_t prep;   // one-launch compaction: its block's max gamma0^2 bits, | PREP_BAD (else 0)
+    uint32_t claims, pad;   // queued walk: claims made on the pool of this slot
 };
 constexpr uint32_t PREP_BAD = 1u << 31;   // a dose of the block is not finite (gamma0^2 has no sign)
 constexpr int SUM_BINS = 256;   // partial-count slots of one gamma map (zeroed by the prep)

@@ -1882,6 +1882,47 @@ __global__ __launch_bounds__(SEARCH_THREADS) void k_cell_range(const float* __re
             range[(z0 + k) * sxy + c] = make_float2(vmin<float>(lo[k], lo[k + 1]), __builtin_fmaxf(hi[k], hi[k + 1]));
 }
 
+// List entries of the queued walk's groups.  Of a list of TQ_OPEN_ROUNDS entries per group or
+// more, the first TQ_DEALT sixteenths are dealt out in strides of the whole grid (an entry per
+// group and round); the rest lie in up to TQ_POOLS pools and are claimed TQ_CLAIM at a time by
+// the waves of the pool's blocks that get there first, since the cost of a node varies and
+// waves with cheap nodes ran dry long before the last one (a wave lived 80 % of the launch on
+// average).  Dealt out / claimed: 1908 / 1540 us for 1.25 M nodes with a 5 % dose error, 213 /
+// 204 for 482535 nodes at 192x256x256, 175 / 168 for 349353 under local normalisation.  (Dealing
+// 1/4, 5/8 or 3/4 of the list, 16 to 64 pools and claims of 16 differ by less than 5 %; one pool
+// for all took 360 us for the second: atomics on one address take about 8 ns each.)
+constexpr uint32_t TQ_OPEN_ROUNDS = 8, TQ_DEALT = 6;
+constexpr uint32_t TQ_CLAIM = 8;
+constexpr uint32_t TQ_POOLS = 64;   // of 64 waves each in a full grid
+static_assert(TQ_POOLS * 4 <= SUM_BINS, "a partial slot per pool, four apart");
+static_assert(TQ_CLAIM >= WAVE / TQ_LANES, "one claim serves every group of a wave");
+static_assert(TQ_OPEN_ROUNDS * TQ_DEALT / 16u >= 2u, "the entries in flight at the start are dealt ones");
+// The dealt part of a list of M entries (whole rounds of `stride`).
+__device__ __forceinline__ uint32_t tq_split(uint32_t M, uint32_t stride) {
+    return M / stride < TQ_OPEN_ROUNDS ? M : (uint32_t)((uint64_t)M * TQ_DEALT / 16u) / stride * stride;
+}
+// The next open entry of every group with `want` (the same in the lanes of a group).  st: the
+// wave's claim (its next entry and end; in LDS, since the walk has no registers to spare).
+__device__ __forceinline__ uint32_t tq_claim(bool want, int lane, uint32_t split, uint32_t vb, uint32_t vgrid,
+                                             BlockSums* sums, uint2* st) {
+    const unsigned long long m = __ballot(want && (lane & (TQ_LANES - 1)) == 0);
+    const uint32_t next = (uint32_t)__builtin_amdgcn_readfirstlane((int)st->x);
+    const uint32_t c = (uint32_t)__popcll(m), left = (uint32_t)__builtin_amdgcn_readfirstlane((int)st->y) - next;
+    const uint32_t rank = (uint32_t)__popcll(m & ((1ull << (lane & ~(TQ_LANES - 1))) - 1ull));
+    uint32_t i = next + rank;
+    if (c <= left) {
+        if (lane == 0) st->x = next + c;
+        return i;
+    }
+    const uint32_t pools = min(vgrid, TQ_POOLS), pool = vb % pools;
+    uint32_t v = 0u;
+    if (lane == 0) v = atomicAdd(&sums[4u * pool].claims, 1u);
+    const uint32_t base = split + ((uint32_t)__builtin_amdgcn_readfirstlane((int)v) * pools + pool) * TQ_CLAIM;
+    if (rank >= left) i = base + (rank - left);
+    if (lane == 0) *st = make_uint2(base + (c - left), base + TQ_CLAIM);
+    return i;
+}
+
 // The node of a group, read by the group's scan and by the lanes that project its cells.
 struct alignas(16) TqNode {
     int x, y, z, node;
@@ -1889,6 +1930,13 @@ struct alignas(16) TqNode {
     uint32_t f;      // F (non-negative float bits: an unsigned minimum is the float minimum; FP64:
                      // rounded up, which every float key is below exactly when it is below F)
     uint32_t inner;  // every cell with key below F lies inside the grid, whole
+};
+
+// What a group has finished.  In LDS: kept in registers, these and the last step's keys made the
+// walk spill twelve, and a reload waits for the loads in flight (178 -> 171 us for 349353
+// nodes under local normalisation).
+struct TqCounts {
+    uint32_t pass, border, cells, maxg2, long_rows;
 };
 
 template <int DIM, int MODE>
@@ -1899,22 +1947,23 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
     constexpr bool FP64 = MODE == 3;
     using T = typename std::conditional<FP64, double, float>::type;
     __shared__ TqNode s_node[TQ_GROUPS];
+    __shared__ TqCounts s_counts[TQ_GROUPS];
+    __shared__ uint2 s_claim[SEARCH_THREADS / WAVE];
     __shared__ unsigned long long s_f64[FP64 ? TQ_GROUPS : 1];   // FP64: F and 1 / dD of a group's node
     __shared__ double s_inv64[FP64 ? TQ_GROUPS : 1];
     __shared__ uint2 s_queue[SEARCH_THREADS / WAVE][TQ_RING];   // row | group of the wave << 28, bound
     __shared__ TabEntry s_tab[TQ_TAB];
     __shared__ uint2 s_head[TQ_TAB];                            // key^2, offset in nodes
     const int lane = threadIdx.x & (WAVE - 1), gl = lane & (TQ_LANES - 1), gsh = lane & ~(TQ_LANES - 1);
-    const unsigned long long lt = (1ull << lane) - 1ull;
     uint2* queue = s_queue[threadIdx.x / WAVE];
     TqNode* wnode = s_node + (threadIdx.x / WAVE) * (WAVE / TQ_LANES);
     TqNode& self = wnode[lane / TQ_LANES];
+    TqCounts& counts = s_counts[threadIdx.x / TQ_LANES];   // kept by the group's first lane
     const int nx = a.nx, ny = a.ny, nz = a.nz, sxy = nx * ny;
     const float inv_dd_g = a.sc->inv_dd;
     const InvS2<T> is = inv_s2_for<T>(a);
     const int wgrp = FP64 ? (threadIdx.x / WAVE) * (WAVE / TQ_LANES) : 0;   // first group of the wave
     const bool ranges = a.range != nullptr && M >= a.range_min;   // (N < 2^29: byte offsets fit 32 bits)
-    uint32_t cells = 0, gm = 0, npass = 0, nborder = 0, long_rows = 0;
     GuardCtx gc{};
     uint32_t dummy_fp64 = 0;
     bool dummy_ill = false;
@@ -1925,7 +1974,11 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
     for (int u = threadIdx.x; u < tab_lds * 4; u += SEARCH_THREADS)
         reinterpret_cast<uint4*>(s_tab)[u] = reinterpret_cast<const uint4*>(tab)[u];
     // (a group that never gets a node still reads one in the steps of the others: node 0)
-    if (gl == 0) self = TqNode{};
+    if (gl == 0) {
+        self = TqNode{};
+        counts = TqCounts{};
+    }
+    if (lane == 0) s_claim[threadIdx.x / WAVE] = make_uint2(0u, 0u);
     for (int u = threadIdx.x; u < tab_lds; u += SEARCH_THREADS) {
         const TabEntry& e = tab[u];
         s_head[u] = make_uint2(f2u(e.key2), (uint32_t)((e.az * ny + e.ay) * nx + e.ax));
@@ -1940,16 +1993,13 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
     };
 
     uint32_t i = vb * TQ_GROUPS + threadIdx.x / TQ_LANES;
-    const uint32_t stride = vgrid * TQ_GROUPS;
+    const uint32_t stride = vgrid * TQ_GROUPS, split = tq_split(M, stride);
     bool have = false, done = false;
     int n0 = 0;                           // the node's next row
     uint32_t q_head = 0, q_tail = 0;      // of the wave's queue (uniform)
     uint32_t q_last = 0;                  // the node's last queued cell lies before this position
     uint32_t lane_cells = 0, whole = 0;   // whole cells of this lane's rows; of the last step only
-    float key[TQ_ROWS];                   // the last step's keys
     float ill_key = Num<float>::inf();    // smallest key of a cell with an ill-conditioned tetrahedron
-#pragma unroll
-    for (int k = 0; k < TQ_ROWS; ++k) key[k] = 0.0f;
     // the group's next node, loaded while the current one is walked: its dose one iteration
     // after its index, so that no load waits for another
     int p_node = 0;
@@ -1962,6 +2012,7 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
         p_f = u2f(a.tail_f[item]);
         if constexpr (FP64) p_hi = a.tail_key_arr[item];
     }
+    i += stride;   // (the entry after next from here on)
 
     // One scan step.  KIND 0: each group its own node's rows, all in LDS and every cell inside
     // the grid; 1: the same without those conditions; 2: the whole wave the rows of group wg's
@@ -2069,8 +2120,6 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
                 n0 += WAVE * TQ_ROWS;
             } else {
                 whole = full;
-#pragma unroll
-                for (int k = 0; k < TQ_ROWS; ++k) key[k] = kk[k];
                 n0 += TQ_STEP;
                 done = ((pb >> gsh) & ((1ull << TQ_LANES) - 1ull)) != 0ull;
             }
@@ -2083,6 +2132,7 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
             p_dr = a.ref[p_node];
             p_fresh = false;
         }
+        bool want = false;
         if (!have && p_have) {
             const uint32_t row = fast_div((uint32_t)p_node, a.div_nx);
             const int z = DIM == 3 ? (int)fast_div(row, a.div_ny) : 0;
@@ -2109,7 +2159,6 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
             ill_key = Num<float>::inf();
             have = true;
             done = false;
-            i += stride;
             p_have = i < M;
             if (p_have) {
                 const uint32_t item = order ? order[i] : i;
@@ -2118,6 +2167,12 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
                 if constexpr (FP64) p_hi = a.tail_key_arr[item];
                 p_fresh = true;
             }
+            i += stride;
+            want = i >= split;
+        }
+        if (split < M && __ballot(want) != 0ull) {
+            const uint32_t k = tq_claim(want, lane, split, vb, vgrid, sums, &s_claim[threadIdx.x / WAVE]);
+            if (want) i = k;
         }
         if (__ballot(have) == 0ull) break;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -2219,7 +2274,9 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
             const float F = u2f(nd.f);
             if (fin) {
 #pragma unroll
-                for (int k = 0; k < TQ_ROWS; ++k) lane_cells += ((whole >> k) & 1u) && key[k] < F ? 1u : 0u;
+                for (int k = 0; k < TQ_ROWS; ++k)
+                    if ((whole >> k) & 1u)
+                        lane_cells += __builtin_bit_cast(float, row_head(n0 - TQ_STEP + k * TQ_LANES + gl).x) < F ? 1u : 0u;
                 // steps before the last whose rows the projections have since put past F (rare)
                 for (int s0 = n0 - TQ_STEP;
                      s0 > 0 && !(__builtin_bit_cast(float, row_head(s0 - 1).x) < F); s0 -= TQ_STEP) {
@@ -2238,12 +2295,16 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
             if constexpr (MODE == 1)
                 to_guard = ((__ballot(fin && ill_key < F) >> gsh) & ((1ull << TQ_LANES) - 1ull)) != 0ull;
             if (fin) {
-                if (n0 > (int)LONG_WALK_ROWS && (uint32_t)n0 > long_rows)   // (it has at most n0 rows)
-                    long_rows = max(long_rows, (uint32_t)resume_row(tab, tab_len, 0, F));
-                if (gl == 0 && !to_guard) {
-                    const float Ff = FP64 ? (float)__builtin_bit_cast(double, s_f64[FP64 ? wgrp + lane / TQ_LANES : 0]) : F;
-                    finish_node(a, nd.node, Ff, npass, nborder, gm);
-                    cells += sum + zero_cells(DIM, nd.x, nd.y, nd.z, nx, ny, nz);
+                if (gl == 0) {
+                    TqCounts c = counts;
+                    if (n0 > (int)LONG_WALK_ROWS && (uint32_t)n0 > c.long_rows)   // (it has at most n0 rows)
+                        c.long_rows = max(c.long_rows, (uint32_t)resume_row(tab, tab_len, 0, F));
+                    if (!to_guard) {
+                        const float Ff = FP64 ? (float)__builtin_bit_cast(double, s_f64[FP64 ? wgrp + lane / TQ_LANES : 0]) : F;
+                        finish_node(a, nd.node, Ff, c.pass, c.border, c.maxg2);
+                        c.cells += sum + zero_cells(DIM, nd.x, nd.y, nd.z, nx, ny, nz);
+                    }
+                    counts = c;
                 }
                 have = false;
             }
@@ -2254,16 +2315,19 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
                     uint32_t base = 0u;
                     if (lane == 0) base = atomicAdd(&a.sc->n_guard, (uint32_t)__popcll(gb));
                     base = (uint32_t)__shfl((int)base, 0);
-                    if (put) a.guard_list[base + (uint32_t)__popcll(gb & lt)] = (uint32_t)nd.node;
+                    if (put) a.guard_list[base + (uint32_t)__popcll(gb & ((1ull << lane) - 1ull))] = (uint32_t)nd.node;
                 }
             }
         }
     }
+    TqCounts c{};
+    if (gl == 0) c = counts;
+    uint32_t long_rows = c.long_rows;
     if (__ballot(long_rows > LONG_WALK_ROWS) != 0ull) {
         for (int o = WAVE / 2; o > 0; o >>= 1) long_rows = max(long_rows, (uint32_t)__shfl_xor((int)long_rows, o));
         if (lane == 0) atomicMax(&a.sc->long_rows, long_rows);
     }
-    block_sums(sums, vb, npass, nborder, 0u, cells, gm);
+    block_sums(sums, vb, c.pass, c.border, 0u, c.cells, c.maxg2);
 }
 
 // The walk of the automatic layout (vb / vgrid: this block and the number of blocks).

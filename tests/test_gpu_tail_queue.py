@@ -69,3 +69,22 @@ def test_sorted_tail_takes_the_queued_walk_too():
     got, rg = gx.gammax_map(*a, sort="dd")
     assert rw.n_tail >= MIN_TAIL
     assert np.array_equal(host(got), host(want)) and rg.n_cells == rw.n_cells
+
+
+@pytest.mark.parametrize("shape", [(63, 65, 64), (64, 64, 64), (71, 67, 61), (541, 541)])
+def test_tail_whose_nodes_are_claimed(shape):
+    """Every node walks again: lists of less than eight entries per group of the launch (dealt
+    out), of eight, and of ragged lengths past that (the rest claimed by the waves), 3D and 2D,
+    in list order and sorted."""
+    import paper_1012_1900_amd as gx
+    rng = np.random.default_rng(shape[1])
+    ref = np.full(shape, 0.75, dtype=np.float32)
+    ev = (ref + 0.04 + 0.004 * rng.standard_normal(shape)).astype(np.float32)
+    a = (dev(ref), dev(ev), (1.0,) * len(shape), 0.03, 3.0, 0.0, False)
+    want, rw = gx.gammax_map(*a, tail_lanes=1, ctx=gx.Context(0))
+    assert rw.n_tail == ref.size
+    ctx = gx.Context(0)
+    for opt in ({}, {}, dict(sort="bound")):
+        got, rg = gx.gammax_map(*a, ctx=ctx, **opt)
+        assert np.array_equal(host(got), host(want)), opt
+        assert (rg.n_cells, rg.n_tail, rg.n_pass) == (rw.n_cells, rw.n_tail, rw.n_pass), opt
