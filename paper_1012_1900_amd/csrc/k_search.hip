@@ -1817,6 +1817,7 @@ constexpr int TQ_LONG = 256;   // rows after which a walk goes on in steps of th
 constexpr int TQ_FEW = 2;      // groups with rows left at which a partial batch is projected
 constexpr int TQ_TAB = 192;    // table rows staged in LDS
 constexpr int TQ_RING = 512;   // queue slots of a wave: 63 left over and a step of 8 groups fit
+static_assert(TQ_TAB <= SEARCH_THREADS, "two grids: a thread per staged row");
 static_assert(WAVE - 1 + WAVE * TQ_ROWS <= TQ_RING && (TQ_RING & (TQ_RING - 1)) == 0, "queue ring");
 
 // Sum over the 8 lanes of a group by data-parallel primitives (no LDS round trip): lanes 1
@@ -3130,37 +3131,46 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // tail_queue_body, for nodes between the evaluation grid's nodes.  A row's test takes the exact
 // distance of its cell (the key is its least over the holding cell) and the range of its
 // corner doses; visited cells and ill-conditioned tetrahedra are those of the rows below the
-// final F.  68 us of the 16-lane walk at 36 thousand nodes, 46 here.
+// final F.  68 us of the 16-lane walk at 36 thousand nodes, 40 here (46 with the table in memory
+// and the finished counts in registers).
 template <int GMODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_grids_tail(GridsArgs a) {
     constexpr int FIRST = 27;   // rows of the key-0 cells
     __shared__ GridsNode s_node[TQ_GROUPS];
-    __shared__ uint2 s_queue[4][TQ_RING];   // row | group of the wave << 28, bound
+    __shared__ TqCounts s_counts[TQ_GROUPS];   // kept by the group's first lane
+    __shared__ uint2 s_queue[4][TQ_RING];      // row | group of the wave << 28, bound
+    __shared__ int4 s_head[TQ_TAB];            // key^2 and offset of the first rows of a walk
     const uint32_t M = a.sc->n_tail;
     const int lane = threadIdx.x & 63, gl = lane & (TQ_LANES - 1), gsh = lane & ~(TQ_LANES - 1);
     const unsigned long long gmask = (1ull << TQ_LANES) - 1ull;
     uint2* queue = s_queue[threadIdx.x >> 6];
     GridsNode* wnode = s_node + (threadIdx.x >> 6) * (WAVE / TQ_LANES);
     GridsNode& self = wnode[lane / TQ_LANES];
+    TqCounts& counts = s_counts[threadIdx.x / TQ_LANES];
     const float inv_dd_g = a.sc->inv_dd;
     const GridsGeo q = grids_geo(a);
     const int enx = a.en[2], eny = a.en[1], enz = a.en[0];
     const float ill_span2 = (a.den_guard * 0.999f - 1.0f) / ((q.is.x + q.is.y) + q.is.z);
     auto row_head = [&](int n) -> int4 {   // key^2 (infinite past the table) and offset
+        if (n < FIRST + TQ_TAB) return s_head[n - FIRST];
         return n < a.tab_len ? *reinterpret_cast<const int4*>(&a.tab[n]) : make_int4(0x7F800000, 0, 0, 0);
     };
-    uint32_t npass = 0, nborder = 0, gm = 0;
-    unsigned long long cells = 0;
     uint32_t i = blockIdx.x * TQ_GROUPS + threadIdx.x / TQ_LANES;
     const uint32_t stride = gridDim.x * TQ_GROUPS;
     if (blockIdx.x * TQ_GROUPS >= M) return;   // uniform
-    if (gl == 0) self = GridsNode{};
+    if (gl == 0) {
+        self = GridsNode{};
+        counts = TqCounts{};
+    }
+    if (threadIdx.x < TQ_TAB) {
+        const int n = FIRST + (int)threadIdx.x;
+        s_head[threadIdx.x] = n < a.tab_len ? *reinterpret_cast<const int4*>(&a.tab[n]) : make_int4(0x7F800000, 0, 0, 0);
+    }
+    __syncthreads();
     bool have = false, done = false;
     int n0 = FIRST;
     uint32_t q_head = 0, q_tail = 0, q_last = 0, lane_cells = 0, whole = 0;
-    float key[TQ_ROWS], ill_key = Num<float>::inf();
-#pragma unroll
-    for (int k = 0; k < TQ_ROWS; ++k) key[k] = 0.0f;
+    float ill_key = Num<float>::inf();
 
     for (;;) {
         if (!have && i < M) {
@@ -3199,12 +3209,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 for (int b = 0; b < 8; ++b) v[k][b] = 0.0f;
                 if (scan) {
                     const int4 e = row_head(n0 + k * TQ_LANES + gl);
-                    key[k] = __builtin_bit_cast(float, e.x);
+                    const float key = __builtin_bit_cast(float, e.x);
                     const int cx = nd.cx + e.y, cy = nd.cy + e.z, cz = nd.cz + e.w;
                     const bool in = (unsigned)cx < (unsigned)enx && (unsigned)cy < (unsigned)eny &&
-                                    (unsigned)cz < (unsigned)enz && key[k] < F;
+                                    (unsigned)cz < (unsigned)enz && key < F;
                     const bool okx = cx + 1 < enx, oky = cy + 1 < eny, okz = cz + 1 < enz;
-                    past = past || !(key[k] < F);
+                    past = past || !(key < F);
                     if (in) {
                         work |= 1u << k;
                         whole |= okx && oky && okz ? (1u << k) : 0u;
@@ -3282,7 +3292,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             const float F = u2f(nd.f);
             if (fin) {
 #pragma unroll
-                for (int k = 0; k < TQ_ROWS; ++k) lane_cells += ((whole >> k) & 1u) && key[k] < F ? 1u : 0u;
+                for (int k = 0; k < TQ_ROWS; ++k)
+                    if ((whole >> k) & 1u)
+                        lane_cells += __builtin_bit_cast(float, row_head(n0 - TQ_STEP + k * TQ_LANES + gl).x) < F ? 1u : 0u;
                 for (int s0 = n0 - TQ_STEP;
                      s0 > FIRST && !(__builtin_bit_cast(float, row_head(s0 - 1).x) < F); s0 -= TQ_STEP) {
 #pragma unroll
@@ -3301,10 +3313,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 if (gl == 0 && !to_guard) {
                     const float gam = sqrtf(F);
                     a.gamma[nd.r] = gam;
-                    npass += gam <= 1.0f;
-                    nborder += fabsf(gam - 1.0f) <= 1e-5f;
-                    gm = max(gm, f2u(gam * gam));
-                    cells += sum;
+                    TqCounts c = counts;
+                    c.pass += gam <= 1.0f;
+                    c.border += fabsf(gam - 1.0f) <= 1e-5f;
+                    c.maxg2 = max(c.maxg2, f2u(gam * gam));
+                    c.cells += sum;
+                    counts = c;
                 }
                 have = false;
             }
@@ -3319,7 +3333,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             }
         }
     }
-    block_sums(a.sums, blockIdx.x, npass, nborder, 0u, (uint32_t)cells, gm);
+    TqCounts c{};
+    if (gl == 0) c = counts;
+    block_sums(a.sums, blockIdx.x, c.pass, c.border, 0u, c.cells, c.maxg2);
 }
 
 // LIST 0: the listed nodes from row 0; 1: the guard list (FP64) from row 0; 2: the tail
