@@ -277,6 +277,72 @@ __device__ __forceinline__ void prep_emit_body(const PrepArgs& a, int vb) {
 
 __global__ __launch_bounds__(PREP_THREADS) void k_prep_emit(PrepArgs a) { prep_emit_body(a, blockIdx.x); }
 
+// The same, EMIT_TILES tiles per block (large grids): the prefix is summed once for all of them, a
+// lane holds the mask word of one (tile, item) and their slots come from one scan.  A word
+// without nodes costs a test.  One tile per block is bound by its chain of dependent loads,
+// which a large grid runs several times per slot: 16.9 us at 192x256x256 (12288 tiles), 9.5 at
+// 160x200x200 (6250), 7.0 at 117x171x171 (3342), 4.1 at 96x128x128 (1536); this takes 9.0, 6.4,
+// 6.0 and 5.3.
+constexpr int64_t EMIT_WIDE_MIN = 3072;   // tiles
+constexpr int EMIT_TILES = 8, EMIT_WORDS = EMIT_TILES * PREP_ITEMS;   // words per wave
+static_assert(EMIT_WORDS <= WAVE && WAVE % EMIT_WORDS == 0, "a lane per word");
+__global__ __launch_bounds__(PREP_THREADS) void k_prep_emit_wide(PrepArgs a) {
+    constexpr int W = PREP_THREADS / WAVE;
+    __shared__ uint32_t s_cnt[EMIT_WORDS][W];
+    __shared__ uint32_t s_pre[W];
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    const int t0 = blockIdx.x * EMIT_TILES;
+    const int l = lane % EMIT_WORDS, tile = t0 + l / PREP_ITEMS;
+    // lane l: the word of tile t0 + l / PREP_ITEMS, item l % PREP_ITEMS, this wave's nodes
+    unsigned long long word = 0ull;
+    if (tile < a.ntiles)
+        word = a.mbits[((int64_t)tile * PREP_TILE + (int64_t)(l % PREP_ITEMS) * PREP_THREADS) / WAVE + w];
+    {
+        const int grp = t0 >> a.super_shift;
+        uint32_t v = 0u;
+        for (int j = threadIdx.x; j < grp; j += PREP_THREADS) v += a.super[j];
+        for (int t = (grp << a.super_shift) + threadIdx.x; t < t0; t += PREP_THREADS) v += a.blockcnt[t];
+        v = wave_sum_u32(v);
+        if (lane == 0) s_pre[w] = v;
+    }
+    if (lane < EMIT_WORDS) s_cnt[l][w] = (uint32_t)__popcll(word);
+    __syncthreads();
+    uint32_t run = 0u;
+    for (int j = 0; j < W; ++j) run += s_pre[j];
+    // slots: the words in (tile, item) order, the waves' within a word
+    uint32_t off = 0u, tot = 0u;
+    for (int j = 0; j < W; ++j) {
+        const uint32_t c = s_cnt[l][j];
+        off += j < w ? c : 0u;
+        tot += c;
+    }
+    uint32_t incl = tot;
+    for (int o = 1; o < EMIT_WORDS; o <<= 1) {
+        const uint32_t up = (uint32_t)__shfl_up((int)incl, o, EMIT_WORDS);
+        incl += l >= o ? up : 0u;
+    }
+    off += run + incl - tot;
+    const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (WAVE - lane));
+#pragma unroll 4
+    for (int k = 0; k < EMIT_WORDS; ++k) {
+        const unsigned long long bal =
+            ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(word >> 32), k) << 32) |
+            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)word, k);
+        if (bal == 0ull) continue;
+        const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)off, k);
+        if ((bal >> lane) & 1ull)
+            a.nodes[at + (uint32_t)__popcll(bal & lt)] =
+                (uint32_t)((int64_t)(t0 + k / PREP_ITEMS) * PREP_TILE + (k % PREP_ITEMS) * PREP_THREADS + threadIdx.x);
+    }
+    if (t0 + EMIT_TILES >= a.ntiles) {
+        uint32_t mx = 0u, none = 0u;
+        for (int j = threadIdx.x; j < a.n_super; j += PREP_THREADS) mx = max(mx, a.super[a.n_super + j]);
+        block_max_or(mx, none);
+        if (threadIdx.x == EMIT_WORDS - 1) a.sc->n_masked = run + incl;
+        if (threadIdx.x == 0) a.sc->r2_bits = mx;
+    }
+}
+
 // 1-3 in one launch, for grids where the three launches cost more than the work in them: every
 // block of 1024 nodes reads all of D_r itself (from L2 after the first), takes the maximum and
 // counts the masked nodes before its own, so nothing crosses blocks but the largest gamma0^2
@@ -503,7 +569,11 @@ hipError_t launch_prep(const PrepArgs& a, bool joined, hipStream_t s) {
     const int64_t nb = prep_tiles(a.n);
     hipLaunchKernelGGL(k_dose_max, dim3(nbr), dim3(PREP_THREADS), 0, s, a);
     hipLaunchKernelGGL(k_prep_count, dim3((unsigned)nb), dim3(PREP_THREADS), 0, s, a, nbr);
-    hipLaunchKernelGGL(k_prep_emit, dim3((unsigned)nb), dim3(PREP_THREADS), 0, s, a);
+    if (nb >= EMIT_WIDE_MIN)
+        hipLaunchKernelGGL(k_prep_emit_wide, dim3((unsigned)((nb + EMIT_TILES - 1) / EMIT_TILES)), dim3(PREP_THREADS), 0,
+                           s, a);
+    else
+        hipLaunchKernelGGL(k_prep_emit, dim3((unsigned)nb), dim3(PREP_THREADS), 0, s, a);
     return hipGetLastError();
 }
 
