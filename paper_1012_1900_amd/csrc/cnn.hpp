@@ -93,7 +93,7 @@ hipError_t launch_cnn_tail(const float* ref, const float* ev, const int n[3], co
                            const uint32_t* nodes, const uint32_t* count, int max_blocks, const uint16_t* const frag[3],
                            const float* const bias[3], const float* w4, const float* b4, float* y, uint32_t* key,
                            hipStream_t s);
-hipError_t launch_features(const float* ref, const float* ev, const int n[3], const Scalars* sc, uint16_t* feat,
+hipError_t launch_features(const float* ref, const float* ev, const int n[3], const DosePartials& dp, uint16_t* feat,
                            hipStream_t s);
 // Coarse grid of the 2x2x2 average pooling of an n grid: ceil(n / 2) per axis.
 void pool2_shape(const int n[3], int c[3]);

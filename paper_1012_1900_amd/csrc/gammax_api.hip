@@ -873,21 +873,41 @@ gammax_status_t scalar_errors(gammax_ctx* c, const Scalars& h, bool local) {
 
 gammax_status_t device_errors(gammax_ctx* c, bool local) { return scalar_errors(c, *c->h_sc, local); }
 
+gammax_status_t dose_args(gammax_ctx* c, const gammax_problem_t* p, const float* ref, const float* ev, int64_t n,
+                          PrepArgs* pa) {
+    const gammax_status_t st = grow(c, &c->part, &c->part_cap, 2 * MAX_BLOCKS);
+    if (st != GAMMAX_OK) return st;
+    *pa = PrepArgs{};
+    pa->ref = ref;
+    pa->ev = ev;
+    pa->n = n;
+    pa->thr = (float)p->dose_threshold;
+    pa->dd = (float)p->dd;
+    pa->local = p->norm == GAMMAX_LOCAL ? 1 : 0;
+    pa->sc = c->d_sc;
+    pa->part = c->part;
+    return GAMMAX_OK;
+}
+
 // Dose maximum and the global 1/dD of a pair into the context's scalars.
 gammax_status_t enqueue_dose_scalars(gammax_ctx* c, const gammax_problem_t* p, const float* ref, const float* ev,
                                      int64_t n, hipStream_t s) {
-    gammax_status_t st = grow(c, &c->part, &c->part_cap, 2 * MAX_BLOCKS);
+    PrepArgs pa;
+    const gammax_status_t st = dose_args(c, p, ref, ev, n, &pa);
     if (st != GAMMAX_OK) return st;
-    PrepArgs pa{};
-    pa.ref = ref;
-    pa.ev = ev;
-    pa.n = n;
-    pa.thr = (float)p->dose_threshold;
-    pa.dd = (float)p->dd;
-    pa.local = p->norm == GAMMAX_LOCAL ? 1 : 0;
-    pa.sc = c->d_sc;
-    pa.part = c->part;
     HIPCHK(c, launch_dose_scalars(pa, s));
+    return GAMMAX_OK;
+}
+
+// The same, with the network's features of the grid.
+gammax_status_t enqueue_features(gammax_ctx* c, const gammax_problem_t* p, const float* ref, const float* ev, int64_t n,
+                                 const int o[3], uint16_t* feat, hipStream_t s) {
+    PrepArgs pa;
+    const gammax_status_t st = dose_args(c, p, ref, ev, n, &pa);
+    if (st != GAMMAX_OK) return st;
+    DosePartials dp;
+    HIPCHK(c, launch_dose_partials(pa, &dp, s));
+    HIPCHK(c, launch_features(ref, ev, o, dp, feat, s));
     return GAMMAX_OK;
 }
 
@@ -1560,8 +1580,7 @@ gammax_status_t gammax_model_features(gammax_ctx_t* c, const gammax_problem_t* p
     if (st != GAMMAX_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     HIPCHK(c, hipSetDevice(c->device));
-    if ((st = enqueue_dose_scalars(c, p, ref, ev, n, s)) != GAMMAX_OK) return st;
-    HIPCHK(c, launch_features(ref, ev, o, c->d_sc, feat, s));
+    if ((st = enqueue_features(c, p, ref, ev, n, o, feat, s)) != GAMMAX_OK) return st;
     HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     return device_errors(c, false);
@@ -1580,8 +1599,7 @@ gammax_status_t gammax_model_predict(gammax_ctx_t* c, gammax_model_t* m, const g
     HIPCHK(c, hipSetDevice(c->device));
     CnnWs w;
     if ((st = grow_cnn(c, o, &w)) != GAMMAX_OK) return st;
-    if ((st = enqueue_dose_scalars(c, p, ref, ev, n, s)) != GAMMAX_OK) return st;
-    HIPCHK(c, launch_features(ref, ev, o, c->d_sc, w.feat, s));
+    if ((st = enqueue_features(c, p, ref, ev, n, o, w.feat, s)) != GAMMAX_OK) return st;
     HIPCHK(c, model_forward(m, w.feat, 1, o, nullptr, w.a2, w.a3, y, s));
     HIPCHK(c, hipMemcpyAsync(c->h_sc, c->d_sc, sizeof(Scalars), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));

@@ -129,6 +129,15 @@ constexpr int64_t PREP_SMALL_MAX = 49152;
 // joined: the search's closing kernel runs before the scalars are read, so that r2_bits and
 // flags may still lie in the partial slots.
 hipError_t launch_prep(const PrepArgs& a, bool joined, hipStream_t s);
+// The dose maximum and finiteness of both doses, one partial per block, for a kernel that
+// reduces them itself and stores the scalars.
+struct DosePartials {
+    const uint32_t* part;
+    int n;
+    float dd, thr;
+    Scalars* sc;
+};
+hipError_t launch_dose_partials(const PrepArgs& a, DosePartials* dp, hipStream_t s);
 // Only the dose maximum, the finiteness flag, the threshold value and the global 1/dD
 // (uses ref, ev, n, thr, dd, sc, part).
 hipError_t launch_dose_scalars(const PrepArgs& a, hipStream_t s);

@@ -862,24 +862,65 @@ __global__ __launch_bounds__(64) void k_pack(const float* __restrict__ theta, Pa
 }
 
 // Features on the grid padded by 4: f0 = D_r * fl32(1/Dmax), f1 = (D_e - D_r) * inv_dd,
-// both bf16; 0 outside the grid.  Dmax and inv_dd come from the prep's scalars.
+// both bf16; 0 outside the grid.  Every block reduces the dose-maximum partials itself (a few KB
+// from L2), and block 0 stores the scalars.  A wave takes whole rows, so a row's coordinates
+// are one uniform division.  (A division per node in 64 bits, and a launch for the scalars in
+// between, took 8.7 + 1.9 us at 96x128x128; this takes 8.1.  2048 blocks: 1024 took 8.6, 4096 9.8.)
+constexpr int FEAT_STEPS = 4;   // 64-node steps of a row whose loads are in flight together
 __global__ __launch_bounds__(256) void k_features(const float* __restrict__ ref, const float* __restrict__ ev,
-                                                  int nz, int ny, int nx, const Scalars* __restrict__ sc,
+                                                  int nz, int ny, int nx, DosePartials dp,
                                                   uint16_t* __restrict__ feat) {
-    const int pz = nz + 8, py = ny + 8, px = nx + 8;
-    const int64_t total = (int64_t)pz * py * px;
-    const float dmax = ord_to_float(sc->dmax_ord);
+    __shared__ uint32_t s_m[4], s_f[4];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    uint32_t dm = 0u, bad = 0u;
+#pragma unroll
+    for (int k = 0; k < MAX_BLOCKS / 256; ++k) {
+        const int j = (int)threadIdx.x + 256 * k, jj = j < dp.n ? j : 0;
+        dm = max(dm, dp.part[jj]);
+        bad |= dp.part[MAX_BLOCKS + jj];
+    }
+    for (int o = 32; o > 0; o >>= 1) dm = max(dm, (uint32_t)__shfl_xor((int)dm, o));
+    bad = __ballot(bad != 0u) != 0ull ? 1u : 0u;
+    if (lane == 0) {
+        s_m[w] = dm;
+        s_f[w] = bad;
+    }
+    __syncthreads();
+    dm = max(max(s_m[0], s_m[1]), max(s_m[2], s_m[3]));
+    const float dmax = ord_to_float(dm);
     const float inv_max = 1.0f / dmax;
-    const float inv_dd = sc->inv_dd;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        const int x = (int)(i % px) - 4, y = (int)((i / px) % py) - 4, z = (int)(i / ((int64_t)px * py)) - 4;
-        uint32_t q = 0u;
-        if (x >= 0 && x < nx && y >= 0 && y < ny && z >= 0 && z < nz) {
-            const int64_t n = ((int64_t)z * ny + y) * nx + x;
-            const float r = ref[n], e = ev[n];
-            q = (uint32_t)f2bf(r * inv_max) | ((uint32_t)f2bf((e - r) * inv_dd) << 16);
+    const float inv_dd = 1.0f / (dp.dd * dmax);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        dp.sc->dmax_ord = dm;
+        dp.sc->flags = (s_f[0] | s_f[1] | s_f[2] | s_f[3]) ? FLAG_NONFINITE : 0u;
+        dp.sc->thr_val = dp.thr * dmax;
+        dp.sc->inv_dd = inv_dd;
+    }
+    const int py = ny + 8, px = nx + 8;
+    const int64_t rows = (int64_t)(nz + 8) * py;
+    for (int64_t row = (int64_t)blockIdx.x * 4 + w; row < rows; row += (int64_t)gridDim.x * 4) {
+        const int64_t pz = rows < ((int64_t)1 << 32) ? (int64_t)((uint32_t)row / (uint32_t)py) : row / py;
+        const int z = (int)pz - 4, y = (int)(row - pz * py) - 4;
+        const bool in = (unsigned)z < (unsigned)nz && (unsigned)y < (unsigned)ny;
+        const int64_t n0 = in ? ((int64_t)z * ny + y) * nx : 0;
+        uint32_t* out = reinterpret_cast<uint32_t*>(feat) + row * px;
+        for (int x0 = 0; x0 < px; x0 += 64 * FEAT_STEPS) {
+            float r[FEAT_STEPS], e[FEAT_STEPS];
+#pragma unroll
+            for (int k = 0; k < FEAT_STEPS; ++k) {
+                const int x = x0 + 64 * k + lane - 4;
+                const bool ok = in && (unsigned)x < (unsigned)nx;
+                r[k] = ok ? ref[n0 + x] : 0.0f;
+                e[k] = ok ? ev[n0 + x] : 0.0f;
+            }
+#pragma unroll
+            for (int k = 0; k < FEAT_STEPS; ++k) {
+                const int x = x0 + 64 * k + lane - 4;
+                const bool ok = in && (unsigned)x < (unsigned)nx;
+                const uint32_t q = (uint32_t)f2bf(r[k] * inv_max) | ((uint32_t)f2bf((e[k] - r[k]) * inv_dd) << 16);
+                if (x + 4 < px) out[x + 4] = ok ? q : 0u;
+            }
         }
-        reinterpret_cast<uint32_t*>(feat)[i] = q;
     }
 }
 
@@ -1464,10 +1505,12 @@ hipError_t launch_cnn_tail(const float* ref, const float* ev, const int n[3], co
     return hipGetLastError();
 }
 
-hipError_t launch_features(const float* ref, const float* ev, const int n[3], const Scalars* sc, uint16_t* feat,
+hipError_t launch_features(const float* ref, const float* ev, const int n[3], const DosePartials& dp, uint16_t* feat,
                            hipStream_t s) {
-    const int64_t total = (int64_t)(n[0] + 8) * (n[1] + 8) * (n[2] + 8);
-    hipLaunchKernelGGL(k_features, dim3(grid_for(total, 4096)), dim3(256), 0, s, ref, ev, n[0], n[1], n[2], sc, feat);
+    const int64_t rows = (int64_t)(n[0] + 8) * (n[1] + 8);
+    const int64_t nb = (rows + 3) / 4;
+    hipLaunchKernelGGL(k_features, dim3((unsigned)(nb < 2048 ? nb : 2048)), dim3(256), 0, s, ref, ev, n[0], n[1], n[2],
+                       dp, feat);
     return hipGetLastError();
 }
 

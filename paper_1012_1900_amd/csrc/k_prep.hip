@@ -577,9 +577,18 @@ hipError_t launch_prep(const PrepArgs& a, bool joined, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_dose_scalars(const PrepArgs& a, hipStream_t s) {
+hipError_t launch_dose_partials(const PrepArgs& a, DosePartials* dp, hipStream_t s) {
     const int nbr = reduce_blocks(a.n);
     hipLaunchKernelGGL(k_dose_max_both, dim3(nbr), dim3(PREP_THREADS), 0, s, a);
+    *dp = DosePartials{a.part, nbr, a.dd, a.thr, a.sc};
+    return hipGetLastError();
+}
+
+hipError_t launch_dose_scalars(const PrepArgs& a, hipStream_t s) {
+    DosePartials dp;
+    const hipError_t e = launch_dose_partials(a, &dp, s);
+    if (e != hipSuccess) return e;
+    const int nbr = dp.n;
     hipLaunchKernelGGL(k_dose_finish, dim3(1), dim3(PREP_THREADS), 0, s, a, nbr);
     return hipGetLastError();
 }
