@@ -106,8 +106,10 @@ typedef struct {
     double cond_threshold;    /* condition-number bound of the FP64 guard, default 1e6 */
     int32_t timing;           /* 1: time the phases with HIP events (fills ms_* in the result) */
     int32_t tail_lanes;       /* lanes that share one node in the walk past the key-0 cells:
-                                 0 = automatic, 1 = one lane per node (the paper's layout),
-                                 8, 16, 32 or 64 = that many table rows of a node at once */
+                                 0 = automatic (by the number of nodes that walk: lane groups,
+                                 or from 16384 on a scan with pooled projections), 1 = one
+                                 lane per node (the paper's layout), 8, 16, 32 or 64 = that
+                                 many table rows of a node at once */
     int32_t cell_lanes;       /* layout of the pass over the key-0 cells: 0 = automatic
                                  (one lane per node), 1 = one lane per node, 4 (2D) or
                                  8 (3D) = one lane per cell */
@@ -139,7 +141,8 @@ typedef struct {
     uint64_t n_pass;          /* nodes with gamma <= 1 */
     uint64_t n_borderline;    /* nodes with |gamma - 1| <= 1e-5 (their pass decision is precision-bound) */
     uint64_t n_fp64_tets;     /* tetrahedron projections redone in FP64 by the guard */
-    uint64_t n_cells;         /* full grid cells evaluated by the search, summed over nodes */
+    uint64_t n_cells;         /* full grid cells visited by the search, summed over nodes (a
+                                 visited cell that its dose bound rules out is not projected) */
     uint64_t n_tail;          /* nodes that walked past the key-0 cells */
     uint64_t n_guarded;       /* nodes redone because they met an ill-conditioned tetrahedron */
     double pass_rate;         /* n_pass / n_evaluated (NaN when n_evaluated == 0) */
@@ -257,7 +260,7 @@ typedef struct {
  * the others get gamma = -1.  Each node walks a table of evaluation cells sorted by a key
  * that bounds the distance from below for any node position inside its holding cell, from
  * the nearest vertex of that cell.  Options: precision (FP32, guarded, FP64), tail_lanes
- * (0 = 16, or 8, 16, 32, 64 lanes per node), cond_threshold; the plain radius and no sort
+ * (0 = automatic, or 8, 16, 32, 64 lanes per node), cond_threshold; the plain radius and no sort
  * only (others: GAMMAX_E_PARAM).  Result: counts, max gamma, dose max, search radius (the
  * largest first bound) and table length.  Synchronises `stream`.
  */

@@ -1431,14 +1431,14 @@ gammax_status_t gammax_map_grids(gammax_ctx_t* c, const gammax_problem_t* p, con
         a.k1 = k1;
         hipError_t e;
         if (opt.precision == GAMMAX_PREC_FP64) {
-            if ((e = launch_grids_walk(a, opt.precision, false, lanes, s)) != hipSuccess) return e;
+            if ((e = launch_grids_fp64(a, false, lanes, s)) != hipSuccess) return e;
         } else {
             // the 27 key-0 cells one lane per node, then the walk of the nodes left
             if ((e = launch_grids_zero(a, opt.precision, s)) != hipSuccess) return e;
             if ((e = launch_grids_tail(a, opt.precision, opt.tail_lanes, s)) != hipSuccess) return e;
         }
         if (opt.precision == GAMMAX_PREC_GUARDED)
-            if ((e = launch_grids_walk(a, opt.precision, true, lanes, s)) != hipSuccess) return e;
+            if ((e = launch_grids_fp64(a, true, lanes, s)) != hipSuccess) return e;
         // the counts, published as a one-grid map's are
         return launch_grids_finish(a, c->d_seq, c->h_ring, s);
     };

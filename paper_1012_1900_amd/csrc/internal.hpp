@@ -321,9 +321,8 @@ struct GridsArgs {
 // Dose maximum and finiteness, then the listing of the evaluated nodes with their first
 // bound (and gamma = -1 everywhere else); zeroes the scalars and partial counts first.
 hipError_t launch_grids_prep(const GridsArgs& a, hipStream_t s);
-// The walk of the listed nodes: precision 0 FP32, 1 FP32 with the guard (ill-conditioned
-// nodes go to the guard list), 2 FP64; guard: walk the guard list in FP64 instead.
-hipError_t launch_grids_walk(const GridsArgs& a, int precision, bool guard, int lanes, hipStream_t s);
+// The walk of the listed nodes (guard: of the guard list) in FP64, from row 0.
+hipError_t launch_grids_fp64(const GridsArgs& a, bool guard, int lanes, hipStream_t s);
 // FP32 (precision 0, or 1 with the guard): the 27 key-0 cells of every listed node from its
 // shared 4x4x4 neighbourhood, one lane per node; nodes not finished go to the tail list, and
 // the walk of that list starts past the key-0 rows (lanes 0: the queued walk, else that many

@@ -2870,14 +2870,13 @@ __global__ __launch_bounds__(256) void k_grids_list(GridsArgs a, int64_t nr, int
     }
 }
 
-// G lanes per node walk the lower-key table of the evaluation grid from row 0.
 // Whether the cell at offset (ax, ay, az) from the holding cell can still lower F.  The node
 // (at f inside the holding cell) is at least the cell's geometric distance from it, and the
 // PL dose inside the cell lies between its vertex values, so when those share a sign the
 // cell is at least dist^2 + (smallest |g|)^2 away.  A cell at or above F (1 + 2^-8) is
 // skipped: the margin is far above the rounding of the projections, so it could not have
-// lowered F either.  The bound needs no projection, so the guard judges only the cells that
-// are projected: a skipped cell's conditioning cannot change the result.
+// lowered F either.  The bound needs no projection, so this walk's guard judges only the cells
+// that are projected: a skipped cell's conditioning cannot change the result.
 __device__ __forceinline__ bool grids_need(const float* g, float ax, float ay, float az, const float* f, float sx2,
                                            float sy2, float sz2, float F) {
     float gmin = g[0], gmax = g[0];
@@ -3338,8 +3337,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     block_sums(a.sums, blockIdx.x, c.pass, c.border, 0u, c.cells, c.maxg2);
 }
 
-// LIST 0: the listed nodes from row 0; 1: the guard list (FP64) from row 0; 2: the tail
-// list of the key-0 pass from the first row past the key-0 cells.
+// G lanes per node walk the lower-key table of the evaluation grid.  LIST 0: the listed nodes
+// from row 0 (FP64 maps); 1: the guard list (FP64) from row 0; 2: the tail list of the key-0
+// pass from the first row past the key-0 cells (an explicit number of lanes).
 template <typename T, int GMODE, int LIST>
 __global__ __launch_bounds__(256) void k_grids_walk(GridsArgs a, int G) {
     constexpr bool GUARD = LIST == 1;
@@ -3588,13 +3588,9 @@ hipError_t launch_grids_prep(const GridsArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_grids_walk(const GridsArgs& a, int precision, bool guard, int lanes, hipStream_t s) {
-    const int G = lanes;
-    const dim3 grid(guard ? 512 : 2048), block(256);
-    if (guard) hipLaunchKernelGGL((k_grids_walk<double, 0, 1>), grid, block, 0, s, a, G);
-    else if (precision == 2) hipLaunchKernelGGL((k_grids_walk<double, 0, 0>), grid, block, 0, s, a, G);
-    else if (precision == 1) hipLaunchKernelGGL((k_grids_walk<float, 1, 0>), grid, block, 0, s, a, G);
-    else hipLaunchKernelGGL((k_grids_walk<float, 0, 0>), grid, block, 0, s, a, G);
+hipError_t launch_grids_fp64(const GridsArgs& a, bool guard, int lanes, hipStream_t s) {
+    if (guard) hipLaunchKernelGGL((k_grids_walk<double, 0, 1>), dim3(512), dim3(256), 0, s, a, lanes);
+    else hipLaunchKernelGGL((k_grids_walk<double, 0, 0>), dim3(2048), dim3(256), 0, s, a, lanes);
     return hipGetLastError();
 }
 
