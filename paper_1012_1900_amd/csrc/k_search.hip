@@ -940,6 +940,26 @@ __device__ __forceinline__ T zero_near(const T* g27, const InvS2<T>& is) {
     return near_faces<V, A, B, CC>(g, is);
 }
 
+// LDS of the pass: one block of it for every mode of a kernel.  A batch's kernels hold several, and
+// with arrays of their own per mode few blocks fit a compute unit: the key-0 phase of 64 mixed
+// pairs took 4.24 ms and the tail phase 4.82; they take 3.5 and 1.67.
+template <bool FP64>
+struct ZeroLds {
+    static constexpr int WAVES = SEARCH_THREADS / WAVE;
+    float g[WAVES][27][WAVE];          // neighbourhoods of the wave's nodes, normalised (FP64: doses)
+    typename std::conditional<FP64, unsigned long long, uint32_t>::type f[WAVES][WAVE];   // their F (non-negative bits)
+    float dr[FP64 ? WAVES : 1][WAVE];
+    double inv[FP64 ? WAVES : 1][WAVE];
+    uint16_t item[WAVES][8 * WAVE];    // queued cells: node's lane | cell << 6
+    uint8_t up[WAVES][WAVE];           // bit i: the grid goes on past the node along axis i
+    TabEntry zero[8];
+};
+template <bool FP64>
+__device__ __forceinline__ ZeroLds<FP64>& zero_lds() {
+    __shared__ ZeroLds<FP64> s;
+    return s;
+}
+
 // MODE 0: FP32; MODE 1: FP32 and flag ill-conditioned tetrahedra; MODE 3: FP64 (a tail node's
 // bound is left as a double in tail_f and tail_key_arr).  vb: the block's index in the node list (256 nodes each).
 template <int MODE>
@@ -947,14 +967,14 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
     constexpr int GMODE = MODE == 1 ? 1 : 0;
     using T = typename std::conditional<MODE == 3, double, float>::type;
     using U = typename std::conditional<MODE == 3, unsigned long long, uint32_t>::type;
-    constexpr int WAVES = SEARCH_THREADS / WAVE;
-    __shared__ float s_g[WAVES][27][WAVE];          // neighbourhoods of the wave's nodes, normalised (FP64: doses)
-    __shared__ U s_f[WAVES][WAVE];                  // their F (non-negative bits)
-    __shared__ float s_dr[MODE == 3 ? WAVES : 1][WAVE];
-    __shared__ double s_inv[MODE == 3 ? WAVES : 1][WAVE];
-    __shared__ uint16_t s_item[WAVES][8 * WAVE];    // queued cells: node's lane | cell << 6
-    __shared__ uint8_t s_up[WAVES][WAVE];           // bit i: the grid goes on past the node along axis i
-    __shared__ TabEntry s_zero[8];
+    ZeroLds<MODE == 3>& lds = zero_lds<MODE == 3>();
+    auto& s_g = lds.g;
+    auto& s_f = lds.f;
+    auto& s_dr = lds.dr;
+    auto& s_inv = lds.inv;
+    auto& s_item = lds.item;
+    auto& s_up = lds.up;
+    auto& s_zero = lds.zero;
     const uint32_t M = a.sc->n_masked;
     if (vb * SEARCH_THREADS >= M) {   // grids are sized for every grid node; M is on the device
         return;
@@ -1940,6 +1960,24 @@ struct TqCounts {
     uint32_t pass, border, cells, maxg2, long_rows;
 };
 
+// LDS of the walk, one block of it for every form of a kernel.
+template <bool FP64>
+struct TqLds {
+    TabEntry tab[TQ_TAB];
+    TqNode node[TQ_GROUPS];
+    uint2 queue[SEARCH_THREADS / WAVE][TQ_RING];        // row | group of the wave << 28, bound
+    uint2 head[TQ_TAB];                                 // key^2, offset in nodes
+    unsigned long long f64[FP64 ? TQ_GROUPS : 1];       // FP64: F and 1 / dD of a group's node
+    double inv64[FP64 ? TQ_GROUPS : 1];
+    uint2 claim[SEARCH_THREADS / WAVE];
+    TqCounts counts[TQ_GROUPS];
+};
+template <bool FP64>
+__device__ __forceinline__ TqLds<FP64>& tq_lds() {
+    __shared__ TqLds<FP64> s;
+    return s;
+}
+
 template <int DIM, int MODE>
 __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEntry* __restrict__ tab,
                                                 const uint32_t* __restrict__ order, uint32_t M, int first,
@@ -1947,14 +1985,15 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
     constexpr int NV = DIM == 3 ? 8 : 4;
     constexpr bool FP64 = MODE == 3;
     using T = typename std::conditional<FP64, double, float>::type;
-    __shared__ TqNode s_node[TQ_GROUPS];
-    __shared__ TqCounts s_counts[TQ_GROUPS];
-    __shared__ uint2 s_claim[SEARCH_THREADS / WAVE];
-    __shared__ unsigned long long s_f64[FP64 ? TQ_GROUPS : 1];   // FP64: F and 1 / dD of a group's node
-    __shared__ double s_inv64[FP64 ? TQ_GROUPS : 1];
-    __shared__ uint2 s_queue[SEARCH_THREADS / WAVE][TQ_RING];   // row | group of the wave << 28, bound
-    __shared__ TabEntry s_tab[TQ_TAB];
-    __shared__ uint2 s_head[TQ_TAB];                            // key^2, offset in nodes
+    TqLds<FP64>& lds = tq_lds<FP64>();
+    auto& s_node = lds.node;
+    auto& s_counts = lds.counts;
+    auto& s_claim = lds.claim;
+    auto& s_f64 = lds.f64;
+    auto& s_inv64 = lds.inv64;
+    auto& s_queue = lds.queue;
+    auto& s_tab = lds.tab;
+    auto& s_head = lds.head;
     const int lane = threadIdx.x & (WAVE - 1), gl = lane & (TQ_LANES - 1), gsh = lane & ~(TQ_LANES - 1);
     uint2* queue = s_queue[threadIdx.x / WAVE];
     TqNode* wnode = s_node + (threadIdx.x / WAVE) * (WAVE / TQ_LANES);
@@ -2594,15 +2633,16 @@ unsigned tail_pass(const SearchArgs& a, const SearchPlan& p, const uint32_t* ord
 // The key-0 pass of every pair of a batch: block b takes item b = (pair, block of 256 nodes)
 // and runs that pair's pass over those nodes, as the pair's own kernel would (a block past
 // the pair's M returns at once).
-__global__ __launch_bounds__(SEARCH_THREADS) void k_batch_key0(const BatchPair* __restrict__ pairs,
+__global__ __launch_bounds__(SEARCH_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void k_batch_key0(const BatchPair* __restrict__ pairs,
                                                                const uint2* __restrict__ items) {
     const uint2 w = items[blockIdx.x];
     const BatchPair& P = pairs[w.x];
+    const SearchArgs& sa = P.sa;
     if (P.ndim == 3) {
-        if (P.guarded) zero3_body<1>(P.sa, P.zg, P.sa.sums, w.y);
-        else zero3_body<0>(P.sa, P.zg, P.sa.sums, w.y);
+        if (P.guarded) zero3_body<1>(sa, P.zg, sa.sums, w.y);
+        else zero3_body<0>(sa, P.zg, sa.sums, w.y);
     } else {
-        zero2_body(P.sa, P.zg, P.sa.sums, w.y);
+        zero2_body(sa, P.zg, sa.sums, w.y);
     }
 }
 
