@@ -42,7 +42,7 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense BF16 matrix cores
 # hash differs the traffic is reported as null.
 TRAFFIC = {
     "3d_128x128x96_2.5mm": {
-        "bytes": (16.09 + 5.48) * 1e6,
+        "bytes": (16.09 + 5.47) * 1e6,
         "source": "paper_1012_1900_amd/csrc/k_search.hip",
         "sha256": "1654df21cfba85a2b2110365af3f2dc040829957bb8875d82464e58b9fd258c4",
         "profile": "profiles/pmc_hbm_bytes_128x128x96_2.5mm_3pct3mm.md",
