@@ -492,6 +492,16 @@ bool want_ranges(const gammax_ctx* c, int64_t n) {
     return n < ((int64_t)1 << 29) && c->tail_hint >= QUEUED_TAIL && c->tail_cells >= 2 * (uint64_t)n;
 }
 
+// Whether the groups of a wave in the queued walk take list entries far apart.  Nodes with long
+// walks lie together in the list, and eight of them in one wave keep it going long after the others; entries
+// far apart share no cache lines.  So: far apart when one walk of the context's last map was
+// longer than a quarter of what a wave walks on average (4096 waves in flight), and where no
+// map tells.  Neighbours against far apart: 81 thousand nodes with walks up to 105 thousand rows
+// (51x81x81, local 3%/3mm) 4.3-4.9 and 1.2 ms (lane groups 2.6), 178 thousand up to 10 thousand
+// 516 and 259 us (701); evenly long walks 589 and 621 us (770 thousand nodes, 5 % dose error),
+// 168 and 178 us in FP64 (144 thousand, up to 1104 rows).  The result does not depend on it.
+int want_spread(const gammax_ctx* c) { return (uint64_t)c->long_rows * 1024 >= c->tail_cells ? 1 : 0; }
+
 // Least lanes per node of the automatic tail layout: wide enough that the longest walk of
 // the context's last map (if it was long) takes about 32 dependent steps.
 int tail_min_lanes(const gammax_ctx* c) {
@@ -671,6 +681,7 @@ SearchArgs make_search_args(const gammax_problem_t* p, const gammax_options_t& o
     sa.ill_span2 = (sa.den_guard * 0.999f - 1.0f) / ((sa.inv_s2[0] + sa.inv_s2[1]) + sa.inv_s2[2]);
     sa.k1 = k1;
     sa.r2_cap = r2_cap;
+    sa.spread = 1;   // (as a context without an earlier map)
     const bool learned = uses_model(p, &opt);
     sa.tail_key = opt.sort_mode == GAMMAX_SORT_BOUND
                       ? 1
@@ -730,6 +741,7 @@ gammax_status_t enqueue_search(gammax_ctx* c, const CallSetup& cs, uint32_t m_bo
                                            r2_cap, c->work, c->work_cap, c->sums, c->yhat);
     sa.range = want_ranges(c, cs.n) && c->range_cap >= cs.n ? c->range : nullptr;
     sa.range_min = (uint32_t)(cs.n / 64);
+    sa.spread = want_spread(c);
     const bool learned = uses_model(p, &opt);
     SearchPlan plan{};
     plan.ndim = p->ndim;
@@ -1762,6 +1774,7 @@ void stage_batch(BatchState* b, const BatchPlan& P) {
         d[i].sa = make_search_args(p, P.opt[i], P.cs[i].ref, P.cs[i].ev, P.cs[i].gamma, c->d_sc, c->tab,
                                    c->tab_valid ? (int)c->tab_len : 0, c->tab_valid ? c->tab_k1 : INFINITY,
                                    r2_cap, c->work, c->work_cap, c->sums, c->yhat);
+        d[i].sa.spread = want_spread(c);
         d[i].zg = make_zero_geo(p);
         d[i].pa = make_prep_args(c, P.cs[i]);
         d[i].ndim = p->ndim;
@@ -1849,6 +1862,8 @@ std::vector<unsigned char> batch_key(BatchState* b, const BatchPlan& P) {
     for (int i = 0; i < P.n; ++i) {
         const GraphKey g = key_of(b->subs[i], P.cs[i]);
         put(&g, sizeof(g));
+        const int spread = want_spread(b->subs[i]);
+        put(&spread, sizeof(spread));
     }
     const void* bufs[2] = {b->d_pairs, b->d_done};
     put(bufs, sizeof(bufs));

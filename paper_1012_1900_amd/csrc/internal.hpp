@@ -237,6 +237,7 @@ struct SearchArgs {
                              // key-0 cells, 2 = predicted gamma (learned ordering)
     float2* range;           // range of every cell's corner doses (workspace), or null
     uint32_t range_min;      // tails of at least this many nodes fill and use it
+    int spread;              // queued walk: a wave's groups take entries far apart in the list
     const float* yhat;       // learned radius: log(gamma_hat + 0.01) per tail item, or null
     float spec_factor;       // the speculative walk stops at key >= spec_factor * gamma_hat
     // work lists

@@ -1824,6 +1824,8 @@ __global__ __launch_bounds__(SEARCH_THREADS) __attribute__((amdgpu_waves_per_eu(
 //         bound F has passed meanwhile is dropped.
 // A group that finishes a node takes its next one without waiting for the other groups, and
 // past TQ_LONG rows a node is scanned by the whole wave (its walk would outlast the others').
+// The groups of a wave take neighbouring list entries, whose cells share cache lines, or (spread)
+// entries far apart, since long walks lie together in the list and a wave walks its own one after the other.
 //
 // Why: a projection costs about ten times a test.  A tail node visits about 30 cells (158 at a
 // 5 % dose error) of which 11 (23) can lower F, and walking 8 rows of a node at a time
@@ -2043,7 +2045,9 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
         return e;
     };
 
-    uint32_t i = vb * TQ_GROUPS + threadIdx.x / TQ_LANES;
+    const uint32_t waves = vgrid * (SEARCH_THREADS / WAVE), wave = vb * (SEARCH_THREADS / WAVE) + threadIdx.x / WAVE;
+    const uint32_t grp = (uint32_t)(lane / TQ_LANES);
+    uint32_t i = a.spread ? grp * waves + wave : wave * (WAVE / TQ_LANES) + grp;
     const uint32_t stride = vgrid * TQ_GROUPS, split = tq_split(M, stride);
     bool have = false, done = false;
     int n0 = 0;                           // the node's next row
