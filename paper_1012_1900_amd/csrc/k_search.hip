@@ -2930,8 +2930,8 @@ __global__ __launch_bounds__(256) void k_grids_list(GridsArgs a, int64_t nr, int
 // PL dose inside the cell lies between its vertex values, so when those share a sign the
 // cell is at least dist^2 + (smallest |g|)^2 away.  A cell at or above F (1 + 2^-8) is
 // skipped: the margin is far above the rounding of the projections, so it could not have
-// lowered F either.  The bound needs no projection, so this walk's guard judges only the cells
-// that are projected: a skipped cell's conditioning cannot change the result.
+// lowered F either.  The bound needs no projection, so the guard judges only the cells that
+// are projected: a skipped cell's conditioning cannot change the result.
 __device__ __forceinline__ bool grids_need(const float* g, float ax, float ay, float az, const float* f, float sx2,
                                            float sy2, float sz2, float F) {
     float gmin = g[0], gmax = g[0];
@@ -2987,7 +2987,8 @@ struct alignas(16) GridsNode {
     float fz, fy, fx, dr;    // position in that cell, reference dose
     float inv_dd;
     uint32_t f;              // F (non-negative float bits)
-    uint32_t pad[2];
+    float f_start;           // and what the pass began with
+    uint32_t pad;
 };
 // The evaluation grid's normalised spacings squared and their chain-block reciprocals.
 struct GridsGeo {
@@ -3010,7 +3011,7 @@ __device__ __forceinline__ GridsNode grids_node(const GridsArgs& a, int r, float
     float f[3];
     grids_cell<float>(a, u, c0, f);
     return GridsNode{c0[0], c0[1], c0[2], r, f[0], f[1], f[2], dr, node_inv_dd(dr, inv_dd_g, (float)a.dd, a.local), f2u(F),
-                     {0u, 0u}};
+                     F, 0u};
 }
 // dist^2 to the faces of the cell at offset (az, ay, ax) from the node's holding cell (a cell
 // whose lower corner lies on the grid; mask: some lane's cell is cut by the grid's faces).
@@ -3040,6 +3041,48 @@ __device__ __forceinline__ bool grids_ill(const GridsArgs& a, const GridsGeo& q,
     return tets_ill(g, q.is, a.den_guard);
 }
 
+// The queued passes below project a node's cells in another order than one lane per node (or a
+// group of lanes, batch by batch) would, and more or fewer of them, depending on which nodes share the wave; so
+// a node that met an ill-conditioned tetrahedron in any whole cell (rare) is judged by that order again.
+// The cell at offset (az, ay, ax) in it: dist^2 to its faces if it can still lower F (its
+// tetrahedra are judged then), else infinity.
+__device__ __forceinline__ float grids_judge(const GridsArgs& a, const GridsGeo& q, const GridsNode& n, int az, int ay,
+                                             int ax, float F, bool& ill) {
+    const int enx = a.en[2], eny = a.en[1], enz = a.en[0], esxy = enx * eny;
+    const int cz = n.cz + az, cy = n.cy + ay, cx = n.cx + ax;
+    if ((unsigned)cx >= (unsigned)enx || (unsigned)cy >= (unsigned)eny || (unsigned)cz >= (unsigned)enz)
+        return Num<float>::inf();
+    const bool okx = cx + 1 < enx, oky = cy + 1 < eny, okz = cz + 1 < enz;
+    float g[8];
+    cell_corners<3>(a.ev, (int64_t)cz * esxy + (int64_t)cy * enx + cx, okx, oky ? enx : 0, okz ? esxy : 0, g);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) g[k] = dose_norm<float>(g[k], n.dr, n.inv_dd);
+    const float f[3] = {n.fz, n.fy, n.fx};
+    if (!grids_need(g, (float)ax, (float)ay, (float)az, f, q.sx2, q.sy2, q.sz2, F)) return Num<float>::inf();
+    const Geo<float> G = geo_frac<float>((float)ax - n.fx, (float)ay - n.fy, (float)az - n.fz, q.sx2, q.sy2, q.sz2, q.is);
+    GuardCtx gc{};
+    uint32_t n_fp64 = 0;
+    return cell3<float, true, 1>(g, G, q.is, okx, oky, okz, a.den_guard, gc, n_fp64, ill);
+}
+// The walk past the key-0 cells by batches of 16 rows (the 8 lanes of a group, two rows each).
+__device__ __forceinline__ bool grids_judge_walk(const GridsArgs& a, const GridsGeo& q, const GridsNode& n, float F,
+                                                 int first, int gl) {
+    bool ill = false;
+#pragma unroll 1
+    for (int n0 = first; n0 < a.tab_len && a.tab[n0].key2 < F; n0 += 16) {
+        float c = Num<float>::inf();
+#pragma unroll 1
+        for (int r = n0 + gl; r < n0 + 16 && r < a.tab_len; r += 8) {
+            const int4 e = *reinterpret_cast<const int4*>(&a.tab[r]);   // key^2 and offset
+            if (__builtin_bit_cast(float, e.x) < F) c = vmin<float>(c, grids_judge(a, q, n, e.w, e.z, e.y, F, ill));
+        }
+        for (int o = 4; o > 0; o >>= 1) c = vmin<float>(c, __shfl_xor(c, o));
+        F = vmin<float>(F, c);
+    }
+    for (int o = 4; o > 0; o >>= 1) ill = (__shfl_xor((int)ill, o) != 0) || ill;
+    return ill;
+}
+
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // The 27 key-0 cells (offsets a in {-1,0,1}^3 from the holding cell) of every listed node, one
@@ -3053,8 +3096,8 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 // 66-72 (4200 instructions of a wave, half of its time; three waves per SIMD, which four with
 // 52 spilled registers do not beat: 95 against 86 us before the list was in grid order).
 //
-// The guard judges every whole cell (not only the projected ones: which those are depends on
-// the nodes that share the wave), by the range of the neighbourhood first.
+// A neighbourhood whose doses span too little for an ill-conditioned tetrahedron needs no
+// judgement, nor does one whose whole cells hold none; the others are judged cell by cell.
 template <int GMODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_grids_zero(GridsArgs a) {
     __shared__ GridsNode s_node[256];
@@ -3167,12 +3210,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         const bool suspect = live && !((all_hi - all_lo) * (all_hi - all_lo) <
                                        (a.den_guard * 0.999f - 1.0f) / ((q.is.x + q.is.y) + q.is.z));
         if (__ballot(suspect) != 0ull && suspect) {   // rare
+            bool any = false;
 #pragma unroll 1
-            for (int c = 0; c < 27; ++c) {
+            for (int c = 0; c < 27 && !any; ++c) {
                 const int cz = n.cz + c / 9 - 1, cy = n.cy + (c / 3) % 3 - 1, cx = n.cx + c % 3 - 1;
                 if (cz >= 0 && cy >= 0 && cx >= 0 && cz + 1 < enz && cy + 1 < eny && cx + 1 < enx)
-                    ill = ill || grids_ill(a, q, n, cz, cy, cx);
+                    any = grids_ill(a, q, n, cz, cy, cx);
             }
+            float f = a.f0[i];
+#pragma unroll 1
+            for (int c = 0; c < 27 && any; ++c) f = vmin<float>(f, grids_judge(a, q, n, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1, f, ill));
         }
     }
     const bool to_guard = GMODE == 1 && ill;
@@ -3184,8 +3231,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // The walk of the tail list in the automatic layout: the scan, pooled projections and finish of
 // tail_queue_body, for nodes between the evaluation grid's nodes.  A row's test takes the exact
 // distance of its cell (the key is its least over the holding cell) and the range of its
-// corner doses; visited cells and ill-conditioned tetrahedra are those of the rows below the
-// final F.  68 us of the 16-lane walk at 36 thousand nodes, 40 here (46 with the table in memory
+// corner doses; visited cells are those of the rows below the final F.  68 us of the 16-lane walk at 36 thousand nodes, 40 here (46 with the table in memory
 // and the finished counts in registers).
 template <int GMODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_grids_tail(GridsArgs a) {
@@ -3224,7 +3270,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     bool have = false, done = false;
     int n0 = FIRST;
     uint32_t q_head = 0, q_tail = 0, q_last = 0, lane_cells = 0, whole = 0;
-    float ill_key = Num<float>::inf();
+    bool steep = false;   // a whole cell of this lane's rows holds an ill-conditioned tetrahedron
 
     for (;;) {
         if (!have && i < M) {
@@ -3234,7 +3280,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             n0 = FIRST;
             q_last = q_head;
             lane_cells = whole = 0u;
-            ill_key = Num<float>::inf();
+            steep = false;
             have = true;
             done = false;
             i += stride;
@@ -3309,8 +3355,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 for (int k = 0; k < TQ_ROWS; ++k) {
                     if (!((whole >> k) & 1u)) continue;
                     const int4 e = row_head(n0 + k * TQ_LANES + gl);
-                    if (grids_ill(a, q, nd, nd.cz + e.w, nd.cy + e.z, nd.cx + e.y))
-                        ill_key = vmin<float>(ill_key, __builtin_bit_cast(float, e.x));
+                    steep = steep || grids_ill(a, q, nd, nd.cz + e.w, nd.cy + e.z, nd.cx + e.y);
                 }
             }
             const unsigned long long pb = __ballot(past);
@@ -3361,7 +3406,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 }
             }
             const uint32_t sum = sum8(lane_cells);
-            const bool to_guard = GMODE == 1 && ((__ballot(fin && ill_key < F) >> gsh) & gmask) != 0ull;
+            bool to_guard = false;
+            if (GMODE == 1) {
+                const unsigned long long sb = __ballot(fin && steep);
+                if (sb != 0ull && ((sb >> gsh) & gmask) != 0ull)   // rare
+                    to_guard = grids_judge_walk(a, q, nd, nd.f_start, FIRST, gl);
+            }
             const bool put = fin && to_guard && gl == 0;
             if (fin) {
                 if (gl == 0 && !to_guard) {
