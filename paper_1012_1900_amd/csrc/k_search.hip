@@ -3210,16 +3210,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         const bool suspect = live && !((all_hi - all_lo) * (all_hi - all_lo) <
                                        (a.den_guard * 0.999f - 1.0f) / ((q.is.x + q.is.y) + q.is.z));
         if (__ballot(suspect) != 0ull && suspect) {   // rare
+            const GridsNode o = wnode[lane];   // (read again: the node's registers are free by now)
             bool any = false;
 #pragma unroll 1
             for (int c = 0; c < 27 && !any; ++c) {
-                const int cz = n.cz + c / 9 - 1, cy = n.cy + (c / 3) % 3 - 1, cx = n.cx + c % 3 - 1;
+                const int cz = o.cz + c / 9 - 1, cy = o.cy + (c / 3) % 3 - 1, cx = o.cx + c % 3 - 1;
                 if (cz >= 0 && cy >= 0 && cx >= 0 && cz + 1 < enz && cy + 1 < eny && cx + 1 < enx)
-                    any = grids_ill(a, q, n, cz, cy, cx);
+                    any = grids_ill(a, q, o, cz, cy, cx);
             }
-            float f = a.f0[i];
+            float f = o.f_start;
 #pragma unroll 1
-            for (int c = 0; c < 27 && any; ++c) f = vmin<float>(f, grids_judge(a, q, n, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1, f, ill));
+            for (int c = 0; c < 27 && any; ++c) f = vmin<float>(f, grids_judge(a, q, o, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1, f, ill));
         }
     }
     const bool to_guard = GMODE == 1 && ill;
