@@ -123,6 +123,8 @@ struct gammax_ctx {
     TableGeom g_geom{};
     bool g_tab_valid = false;
     float g_k1 = INFINITY;             // key^2 of its first row past the 27 key-0 cells
+    uint64_t g_tail = 0;               // tail length of the last map and its longest walk, if long,
+    uint32_t g_long_rows = 0;          // or 3/4 of the ones before (which walk the next map takes)
     float* g_2d = nullptr;             // 2D two-grid maps: the pair and gamma extruded to two layers
     int64_t g_2d_cap = 0;
     struct BatchState* batch = nullptr;   // gammax_batch state (created on first use)
@@ -501,6 +503,19 @@ bool want_ranges(const gammax_ctx* c, int64_t n) {
 // 516 and 259 us (701); evenly long walks 589 and 621 us (770 thousand nodes, 5 % dose error),
 // 168 and 178 us in FP64 (144 thousand, up to 1104 rows).  The result does not depend on it.
 int want_spread(const gammax_ctx* c) { return (uint64_t)c->long_rows * 1024 >= c->tail_cells ? 1 : 0; }
+
+// Whether the tail walk of a two-grid map is the queued one, by the context's last two-grid maps.  It
+// takes 10 ns per thousand visited cells where 16 lanes per node take 17, but 90 ns per row of
+// the longest walk against 65, so it pays from some nodes per row of that walk on.  16 lanes
+// against queued, us, by nodes and longest walk: 2.9 thousand, 248 rows 22 and 28; 10 thousand, 248
+// rows 33 and 31; 37 thousand, 152 rows 68 and 38; 25 thousand, 586 rows 80 and 63; 8 thousand,
+// 586 rows 44 and 53; 51 thousand, 964 rows 88-106 and 115; 146 thousand, 1518 rows 232 and 217;
+// 130 thousand, 4088 rows 270 and 370; 657 thousand, 12476 rows 1011 and 1424; 706 thousand, 892
+// rows 886 and 550.  The results do not depend on it.
+bool grids_queued(const gammax_ctx* c) {
+    const uint64_t rows = std::max(c->g_long_rows, LONG_WALK_ROWS);   // (shorter ones are not recorded)
+    return c->g_tail >= (rows <= 640 ? 36 : 60) * rows;
+}
 
 // Least lanes per node of the automatic tail layout: wide enough that the longest walk of
 // the context's last map (if it was long) takes about 32 dependent steps.
@@ -1434,7 +1449,8 @@ gammax_status_t gammax_map_grids(gammax_ctx_t* c, const gammax_problem_t* p, con
         g.shape[i] = eg->shape[i];
         g.s[i] = eg->spacing_mm[i] / p->dta_mm;
     }
-    const int lanes = opt.tail_lanes > 0 ? opt.tail_lanes : 16;
+    const int lanes = opt.tail_lanes > 0 ? opt.tail_lanes : GRIDS_LANES;
+    const bool queued = grids_queued(c);
     // the key-0 pass, the walk and the guard over the listed nodes (their count is on the
     // device); with no table (every first bound is 0) the key-0 pass finishes every node
     auto search = [&](const TabEntry* tab, int tab_len, float k1) -> hipError_t {
@@ -1447,7 +1463,7 @@ gammax_status_t gammax_map_grids(gammax_ctx_t* c, const gammax_problem_t* p, con
         } else {
             // the 27 key-0 cells one lane per node, then the walk of the nodes left
             if ((e = launch_grids_zero(a, opt.precision, s)) != hipSuccess) return e;
-            if ((e = launch_grids_tail(a, opt.precision, opt.tail_lanes, s)) != hipSuccess) return e;
+            if ((e = launch_grids_tail(a, opt.precision, opt.tail_lanes, queued, s)) != hipSuccess) return e;
         }
         if (opt.precision == GAMMAX_PREC_GUARDED)
             if ((e = launch_grids_fp64(a, true, lanes, s)) != hipSuccess) return e;
@@ -1497,6 +1513,12 @@ gammax_status_t gammax_map_grids(gammax_ctx_t* c, const gammax_problem_t* p, con
         }
     }
     const float r2 = u2f(c->h_sc->r2_bits);
+    if (opt.precision != GAMMAX_PREC_FP64) {
+        // (a few short tails among long ones change nothing: the queued walk costs them 5 us, while
+        // 16 lanes per node cost the next long one 30)
+        c->g_tail = std::max<uint64_t>(c->h_sc->n_tail, c->g_tail / 4 * 3);
+        c->g_long_rows = std::max(c->h_sc->long_rows, c->g_long_rows / 4 * 3);
+    }
     if (res) {
         const Scalars& h = *c->h_sc;
         std::memset(res, 0, sizeof(*res));

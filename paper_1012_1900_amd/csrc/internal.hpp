@@ -326,10 +326,11 @@ hipError_t launch_grids_prep(const GridsArgs& a, hipStream_t s);
 hipError_t launch_grids_fp64(const GridsArgs& a, bool guard, int lanes, hipStream_t s);
 // FP32 (precision 0, or 1 with the guard): the 27 key-0 cells of every listed node from its
 // shared 4x4x4 neighbourhood, one lane per node; nodes not finished go to the tail list, and
-// the walk of that list starts past the key-0 rows (lanes 0: the queued walk, else that many
-// lanes per node).
+// the walk of that list starts past the key-0 rows (lanes 0: the queued walk or GRIDS_LANES
+// lanes per node, with equal results; else that many lanes per node).
+constexpr int GRIDS_LANES = 16;
 hipError_t launch_grids_zero(const GridsArgs& a, int precision, hipStream_t s);
-hipError_t launch_grids_tail(const GridsArgs& a, int precision, int lanes, hipStream_t s);
+hipError_t launch_grids_tail(const GridsArgs& a, int precision, int lanes, bool queued, hipStream_t s);
 // The partial counts into the scalars, and the scalars to the pinned ring.
 hipError_t launch_grids_finish(const GridsArgs& a, uint32_t* seq, Scalars* ring, hipStream_t s);
 

@@ -3232,8 +3232,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // The walk of the tail list in the automatic layout: the scan, pooled projections and finish of
 // tail_queue_body, for nodes between the evaluation grid's nodes.  A row's test takes the exact
 // distance of its cell (the key is its least over the holding cell) and the range of its
-// corner doses; visited cells are those of the rows below the final F.  68 us of the 16-lane walk at 36 thousand nodes, 40 here (46 with the table in memory
-// and the finished counts in registers).
+// corner doses; visited cells are those of the rows below the final F.  40 us at 36 thousand
+// nodes where 16 lanes per node take 68 (46 with the table in memory and the finished counts in
+// registers).  It is taken where grids_queued says so: its steps are heavier, so a long walk outlasts 16 lanes.
 template <int GMODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_grids_tail(GridsArgs a) {
     constexpr int FIRST = 27;   // rows of the key-0 cells
@@ -3440,15 +3441,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
     TqCounts c{};
     if (gl == 0) c = counts;
+    // the longest walk of the wave, where long: the context's next map chooses its layout by it
+    if (FIRST + (int)LONG_WALK_ROWS < a.tab_len) {
+        uint32_t f = c.maxg2;
+        for (int o = WAVE / 2; o > 0; o >>= 1) f = max(f, (uint32_t)__shfl_xor((int)f, o));
+        if (lane == 0 && a.tab[FIRST + LONG_WALK_ROWS].key2 < u2f(f))
+            atomicMax(&a.sc->long_rows, (uint32_t)(resume_row(a.tab, a.tab_len, FIRST, u2f(f)) - FIRST));
+    }
     block_sums(a.sums, blockIdx.x, c.pass, c.border, 0u, c.cells, c.maxg2);
 }
 
 // G lanes per node walk the lower-key table of the evaluation grid.  LIST 0: the listed nodes
 // from row 0 (FP64 maps); 1: the guard list (FP64) from row 0; 2: the tail list of the key-0
-// pass from the first row past the key-0 cells (an explicit number of lanes).
+// pass from the first row past the key-0 cells.  below: count the visited cells below the final F (as the
+// queued walk does: the automatic layout's count does not depend on which of the two it takes),
+// not those that the node's last batch visited past it.
 template <typename T, int GMODE, int LIST>
-__global__ __launch_bounds__(256) void k_grids_walk(GridsArgs a, int G) {
-    constexpr bool GUARD = LIST == 1;
+__global__ __launch_bounds__(256) void k_grids_walk(GridsArgs a, int G, bool below) {
+    static_assert((LIST == 2) == (sizeof(T) == 4), "FP32 walks the tail list, FP64 the others");
     const uint32_t M = LIST == 1 ? a.sc->n_guard : (LIST == 2 ? a.sc->n_tail : a.sc->n_masked);
     if (M == 0u) return;   // (the guard list, as a rule)
     const uint32_t* list = LIST == 1 ? a.guard_list : (LIST == 2 ? a.tail_list : a.list);
@@ -3484,14 +3494,15 @@ __global__ __launch_bounds__(256) void k_grids_walk(GridsArgs a, int G) {
         T F = T(0);
         if (live) {
             if constexpr (LIST == 2) F = (T)a.tail_f[i];
-            else if (GUARD || sizeof(T) == 8) F = grids_f0<T>(a, c0, f, dr, inv_dd);
-            else F = (T)a.f0[i];
+            else F = grids_f0<T>(a, c0, f, dr, inv_dd);
         }
-        uint32_t lane_cells = 0;
+        uint32_t lane_cells = 0, rows = 0;
+        T last_key = T(0);   // of this lane's last whole cell: its only one that may lie past the final F
         bool ill = false;
         for (int n0 = first; n0 < a.tab_len; n0 += G) {
             const bool grp_act = live && (T)a.tab[n0].key2 < F;
             if (__ballot(grp_act) == 0ull) break;
+            if constexpr (LIST == 2) rows += grp_act ? (uint32_t)G : 0u;
             const int n = n0 + gl;
             TabEntry e;
             bool act = false;
@@ -3515,6 +3526,7 @@ __global__ __launch_bounds__(256) void k_grids_walk(GridsArgs a, int G) {
             bool need = false;
             if (work) {
                 lane_cells += edge ? 0u : 1u;
+                if constexpr (LIST == 2) last_key = edge ? last_key : (T)e.key2;
                 const int64_t b = (int64_t)cz * esxy + (int64_t)cy * enx + cx;
                 const int ox = okx ? 1 : 0, oy = oky ? enx : 0, oz = okz ? esxy : 0;
                 g[0] = dose_norm<T>((T)a.ev[b], dr, inv_dd);
@@ -3537,6 +3549,14 @@ __global__ __launch_bounds__(256) void k_grids_walk(GridsArgs a, int G) {
             }
             for (int o = G / 2; o > 0; o >>= 1) c = vmin<T>(c, __shfl_xor(c, o));
             F = vmin<T>(F, c);
+        }
+        if constexpr (LIST == 2) {
+            lane_cells -= below && lane_cells != 0u && !(last_key < F) ? 1u : 0u;
+            // the longest walk: the context's next map chooses its layout by it
+            if (__ballot(rows > LONG_WALK_ROWS) != 0ull) {
+                for (int o = WAVE / 2; o > 0; o >>= 1) rows = max(rows, (uint32_t)__shfl_xor((int)rows, o));
+                if ((threadIdx.x & (WAVE - 1)) == 0) atomicMax(&a.sc->long_rows, rows);
+            }
         }
         for (int o = G / 2; o > 0; o >>= 1) {
             lane_cells += (uint32_t)__shfl_xor((int)lane_cells, o);
@@ -3695,8 +3715,8 @@ hipError_t launch_grids_prep(const GridsArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_grids_fp64(const GridsArgs& a, bool guard, int lanes, hipStream_t s) {
-    if (guard) hipLaunchKernelGGL((k_grids_walk<double, 0, 1>), dim3(512), dim3(256), 0, s, a, lanes);
-    else hipLaunchKernelGGL((k_grids_walk<double, 0, 0>), dim3(2048), dim3(256), 0, s, a, lanes);
+    if (guard) hipLaunchKernelGGL((k_grids_walk<double, 0, 1>), dim3(512), dim3(256), 0, s, a, lanes, false);
+    else hipLaunchKernelGGL((k_grids_walk<double, 0, 0>), dim3(2048), dim3(256), 0, s, a, lanes, false);
     return hipGetLastError();
 }
 
@@ -3713,8 +3733,8 @@ hipError_t launch_grids_zero(const GridsArgs& a, int precision, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_grids_tail(const GridsArgs& a, int precision, int lanes, hipStream_t s) {
-    if (lanes == 0) {
+hipError_t launch_grids_tail(const GridsArgs& a, int precision, int lanes, bool queued, hipStream_t s) {
+    if (lanes == 0 && queued) {
         const int64_t nr = (int64_t)a.rn[0] * a.rn[1] * a.rn[2];
         const int64_t nb = (nr + TQ_GROUPS - 1) / TQ_GROUPS;
         const dim3 g((unsigned)(nb < kTailBlocks ? nb : kTailBlocks)), b(SEARCH_THREADS);
@@ -3723,8 +3743,9 @@ hipError_t launch_grids_tail(const GridsArgs& a, int precision, int lanes, hipSt
         return hipGetLastError();
     }
     const dim3 grid(2048), block(256);
-    if (precision == 1) hipLaunchKernelGGL((k_grids_walk<float, 1, 2>), grid, block, 0, s, a, lanes);
-    else hipLaunchKernelGGL((k_grids_walk<float, 0, 2>), grid, block, 0, s, a, lanes);
+    const int G = lanes > 0 ? lanes : GRIDS_LANES;
+    if (precision == 1) hipLaunchKernelGGL((k_grids_walk<float, 1, 2>), grid, block, 0, s, a, G, lanes == 0);
+    else hipLaunchKernelGGL((k_grids_walk<float, 0, 2>), grid, block, 0, s, a, G, lanes == 0);
     return hipGetLastError();
 }
 
