@@ -1091,12 +1091,17 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
     }
     uint32_t n_fp64 = 0;
     GuardCtx gc{};
-    // cell c of the node of lane nl, all faces it owns
-    auto cell_of = [&](int nl, int c, bool mask, auto gmode, bool& ill) -> T {
+    bool dummy_ill = false;
+    // corner doses of cell c of the node of lane nl
+    auto cell_doses = [&](int nl, int c, T* g) {
         const float(*gn)[WAVE] = s_g[wv] + (((c >> 2) * 3 + ((c >> 1) & 1)) * 3 + (c & 1));
-        T g[8];
 #pragma unroll
         for (int b = 0; b < 8; ++b) g[b] = gn[(b >> 2) * 9 + ((b >> 1) & 1) * 3 + (b & 1)][nl];
+    };
+    // its dist^2, all faces it owns
+    auto cell_of = [&](int nl, int c, bool mask) -> T {
+        T g[8];
+        cell_doses(nl, c, g);
         Geo<T> G;
         if constexpr (MODE == 3) {
             const T dn = s_dr[wv][nl], in = s_inv[wv][nl];
@@ -1108,8 +1113,8 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
         }
         const uint32_t up = s_up[wv][nl] | ~(uint32_t)c;   // a cell at -1 reaches back to the node
         if (mask)
-            return cell3<T, true, decltype(gmode)::value>(g, G, is, up & 1u, up & 2u, up & 4u, (T)a.den_guard, gc, n_fp64, ill);
-        return cell3<T, false, decltype(gmode)::value>(g, G, is, true, true, true, (T)a.den_guard, gc, n_fp64, ill);
+            return cell3<T, true, 0>(g, G, is, up & 1u, up & 2u, up & 4u, (T)a.den_guard, gc, n_fp64, dummy_ill);
+        return cell3<T, false, 0>(g, G, is, true, true, true, (T)a.den_guard, gc, n_fp64, dummy_ill);
     };
     bool ill = false;
     if (q != 0u) {
@@ -1121,7 +1126,7 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
             const bool whole = ((s_up[wv][nl] | ~(uint32_t)c) & 7u) == 7u;
             const bool mask = __ballot(on && !whole) != 0ull;
             if (on) {
-                const T v = cell_of(nl, c, mask, std::integral_constant<int, 0>{}, ill);
+                const T v = cell_of(nl, c, mask);
                 atomicMin(&s_f[wv][nl], __builtin_bit_cast(U, v));
             }
         }
@@ -1131,8 +1136,10 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
     // the whole cells around the node: (goes on up) + (goes on down) per axis, multiplied
     const uint32_t both = on6 & (on6 >> 3), one = (on6 | (on6 >> 3)) & 7u;
     uint32_t cells = open && one == 7u ? 1u << __popc(both & 7u) : 0u;
-    // rare: the tetrahedra of a steep neighbourhood are judged, and a node whose F fell to 0
-    // counts the cells up to there, cell by cell in table order
+    // rare: the tetrahedra of a steep neighbourhood's whole cells are judged (their denominators
+    // only: projecting the cells again for it, the pass took 58 us at 96x128x128 with the threshold at 100, where
+    // every neighbourhood is steep; this takes 38, and 33 where none is), and a node whose F fell to 0 counts
+    // the cells up to there, cell by cell in table order
     const bool zero = open && F == T(0);
     if (__ballot(redo || zero) != 0ull) {
         if (q == 0u && __ballot(redo) == 0ull) {
@@ -1143,15 +1150,25 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
             s_up[wv][lane] = (uint8_t)(on6 & 7u);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-        if (redo || zero) {
+        if constexpr (GMODE == 1) {
+            if (redo) {
+#pragma unroll 1
+                for (int c = 0; c < 8 && !ill; ++c) {
+                    if (!there_of(c) || !whole_of(c)) continue;
+                    T g[8];
+                    cell_doses(lane, c, g);
+                    ill = tets_ill(g, is, a.den_guard);
+                }
+            }
+        }
+        if (zero) {
             F = F0;
             cells = 0u;
 #pragma unroll 1
             for (int c = 0; c < 8; ++c) {
                 if (!there_of(c)) continue;
-                const bool whole = whole_of(c);
-                cells += F > T(0) && whole ? 1u : 0u;
-                F = vmin<T>(F, cell_of(lane, c, true, std::integral_constant<int, GMODE>{}, ill));
+                cells += F > T(0) && whole_of(c) ? 1u : 0u;
+                F = vmin<T>(F, cell_of(lane, c, true));
             }
         }
     }
