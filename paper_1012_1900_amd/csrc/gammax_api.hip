@@ -112,6 +112,7 @@ struct gammax_ctx {
     int64_t yhat_cap = 0;
     float2* range = nullptr;        // range of every cell's corner doses (long tails)
     int64_t range_cap = 0;
+    int64_t range_refused = INT64_MAX;   // least size that could not be had
     float* ycoarse = nullptr;       // the network's output on the pooled coarse grid (cnn_pool 2)
     int64_t ycoarse_cap = 0;
     // gammax_map_grids: listed nodes, their first bounds, the guard list (each n_ref words)
@@ -493,6 +494,15 @@ bool short_tail(const gammax_ctx* c, const gammax_options_t& opt) {
 bool want_ranges(const gammax_ctx* c, int64_t n) {
     return n < ((int64_t)1 << 29) && c->tail_hint >= QUEUED_TAIL && c->tail_cells >= 2 * (uint64_t)n;
 }
+// Whether a map of its own (not in a phased batch, whose walk gathers the corners) may take that walk.
+bool reads_ranges(const gammax_problem_t* p, const gammax_options_t& o) {
+    if (o.precision == GAMMAX_PREC_FP64) return p->ndim == 3;
+    return o.tail_lanes == 0 && !(uses_model(p, &o) && o.radius_mode == GAMMAX_RADIUS_LEARNED);
+}
+// The ranges a map of n nodes writes and reads, or null.
+float2* map_ranges(const gammax_ctx* c, const gammax_problem_t* p, const gammax_options_t& o, int64_t n) {
+    return reads_ranges(p, o) && want_ranges(c, n) && c->range_cap >= n ? c->range : nullptr;
+}
 
 // Whether the groups of a wave in the queued walk take list entries far apart.  Nodes with long
 // walks lie together in the list, and eight of them in one wave keep it going long after the others; entries
@@ -754,7 +764,7 @@ gammax_status_t enqueue_search(gammax_ctx* c, const CallSetup& cs, uint32_t m_bo
     SearchArgs sa = make_search_args(p, opt, cs.ref, cs.ev, cs.gamma, c->d_sc, c->tab,
                                      c->tab_valid ? (int)c->tab_len : 0, c->tab_valid ? c->tab_k1 : INFINITY,
                                            r2_cap, c->work, c->work_cap, c->sums, c->yhat);
-    sa.range = want_ranges(c, cs.n) && c->range_cap >= cs.n ? c->range : nullptr;
+    sa.range = map_ranges(c, p, opt, cs.n);
     sa.range_min = (uint32_t)(cs.n / 64);
     sa.spread = want_spread(c);
     const bool learned = uses_model(p, &opt);
@@ -949,10 +959,11 @@ gammax_status_t model_inputs(gammax_ctx* c, const gammax_problem_t* p, const flo
 }
 
 // Checks and workspace of one map call (every step of the steady path then runs without a
-// host round trip).  *opt receives the options in effect, *n the node count.
+// host round trip).  *opt receives the options in effect, *n the node count.  ranges: whether
+// the call's walk can use cell ranges at all (reads_ranges).
 gammax_status_t map_setup(gammax_ctx* c, const gammax_problem_t* p, const gammax_options_t* opt_in,
                           const float* ref, const float* ev, const float* gamma, gammax_options_t* opt,
-                          int64_t* n, bool* learned) {
+                          int64_t* n, bool* learned, bool ranges = true) {
     if (!ref || !ev || !gamma) return fail(c, GAMMAX_E_NULL, "dose and gamma pointers are required");
     gammax_status_t st = check_problem(c, p, n);
     if (st != GAMMAX_OK) return st;
@@ -968,10 +979,21 @@ gammax_status_t map_setup(gammax_ctx* c, const gammax_problem_t* p, const gammax
     if ((st = grow(c, &c->hist, &c->hist_cap, sort_hist_words(*n))) != GAMMAX_OK) return st;
     if ((st = grow(c, &c->sums, &c->sums_cap, search_sums_needed((uint32_t)*n))) != GAMMAX_OK) return st;
     if (opt->timing && (st = ensure_events(c)) != GAMMAX_OK) return st;
-    if (want_ranges(c, *n) && (st = grow(c, &c->range, &c->range_cap, *n)) != GAMMAX_OK) return st;
     *learned = uses_model(p, opt);
     if (*learned && (st = grow(c, &c->yhat, &c->yhat_cap, *n)) != GAMMAX_OK) return st;
     if (*learned && opt->cnn_pool == 2 && (st = grow_pooled(c, p)) != GAMMAX_OK) return st;
+    // the ranges last: a map does without them where the memory cannot be had
+    if (ranges && reads_ranges(p, *opt) && want_ranges(c, *n) && *n < c->range_refused) {
+        const std::string err = c->err;
+        st = grow(c, &c->range, &c->range_cap, *n);
+        if (st == GAMMAX_E_NOMEM) {
+            (void)hipGetLastError();
+            c->err = err;
+            c->range_refused = *n;
+        } else if (st != GAMMAX_OK) {
+            return st;
+        }
+    }
     return GAMMAX_OK;
 }
 
@@ -2051,6 +2073,10 @@ gammax_status_t gammax_batch(gammax_ctx_t* c, int32_t n, const gammax_problem_t*
     P.cs.resize(n);
     P.nodes.resize(n);
     P.key0 = opt.precision != GAMMAX_PREC_FP64;
+    // the launches: one per phase over all pairs when every pair takes the default pipeline
+    // (a tuned tail layout does not change that)
+    P.phased = P.key0;
+    for (int i = 0; i < n; ++i) P.phased = P.phased && default_pipeline(&probs[i], opt);
     std::vector<uint64_t> cls(n);
     std::vector<int> learned(n, 0);
     for (int i = 0; i < n; ++i) {
@@ -2061,7 +2087,7 @@ gammax_status_t gammax_batch(gammax_ctx_t* c, int32_t n, const gammax_problem_t*
         gammax_options_t oi = opt;
         if (opt.tail_lanes == 0 && b->tune.count(cls[i])) oi.tail_lanes = b->tune[cls[i]];
         bool lr = false;
-        if ((st = map_setup(sub, &probs[i], &oi, refs[i], evals[i], gammas[i], &P.opt[i], &nn, &lr)) != GAMMAX_OK)
+        if ((st = map_setup(sub, &probs[i], &oi, refs[i], evals[i], gammas[i], &P.opt[i], &nn, &lr, !P.phased)) != GAMMAX_OK)
             return fail(c, st, "pair " + std::to_string(i) + ": " + sub->err);
         learned[i] = lr ? 1 : 0;
         P.nodes[i] = nn;
@@ -2111,10 +2137,6 @@ gammax_status_t gammax_batch(gammax_ctx_t* c, int32_t n, const gammax_problem_t*
         for (int i = 0; i < n; ++i) P.opt[i].tail_lanes = b->tune[cls[i]];
     }
 
-
-    // the launches: one per phase over all pairs when every pair takes the default pipeline
-    P.phased = P.key0;
-    for (int i = 0; i < n; ++i) P.phased = P.phased && default_pipeline(&probs[i], P.opt[i]);
     if ((st = plan_lists(c, b, P)) != GAMMAX_OK) return st;
     if (P.desc_bytes > b->desc_cap || !b->d_pairs) {
         if (b->graph) (void)hipGraphExecDestroy(b->graph);
