@@ -1906,8 +1906,10 @@ std::vector<unsigned char> batch_key(BatchState* b, const BatchPlan& P) {
     for (int i = 0; i < P.n; ++i) {
         const GraphKey g = key_of(b->subs[i], P.cs[i]);
         put(&g, sizeof(g));
-        const int spread = want_spread(b->subs[i]);
-        put(&spread, sizeof(spread));
+        // what else the launches take from the context's last map
+        const int walk[2] = {want_spread(b->subs[i]),
+                             !P.phased && map_ranges(b->subs[i], P.cs[i].p, P.opt[i], P.nodes[i]) ? 1 : 0};
+        put(walk, sizeof(walk));
     }
     const void* bufs[2] = {b->d_pairs, b->d_done};
     put(bufs, sizeof(bufs));
