@@ -1756,7 +1756,7 @@ struct BatchPlan {
     std::vector<gammax_options_t> opt;
     std::vector<CallSetup> cs;
     std::vector<int64_t> nodes;
-    bool key0 = true;          // false for FP64 precision (its walk starts at row 0)
+    bool key0 = true;          // false for FP64 precision (every pair launches its own passes)
     bool phased = false;       // every phase one launch over all pairs (the default pipeline)
     enum { L_KEY0, L_DM, L_TILES, L_TAIL, L_FIN, kLists };
     int64_t off[kLists] = {};  // byte offset of each item list

@@ -162,9 +162,6 @@ constexpr int FTHREADS = 512;
 constexpr int FNRY = FY / (FTHREADS / 64);   // y rows per wave
 static_assert(FNRY * (FTHREADS / 64) == FY, "the waves must cover the tile's rows");
 
-// Offset in nodes of tap t = 9 dz + 3 dy + dx within a staged forward tile.
-__host__ __device__ constexpr int ftap_offset(int t) { return ((t / 9) * FLY + (t / 3) % 3) * FLX + t % 3; }
-
 // Stage the box of BX x BY x BZ nodes with corner (gx0, gy0, gz0) of a channel-last volume
 // (iz, iy, ix, CIN channels) into LDS, node-major with CIN channels per node; nodes outside
 // the volume read as 0.  Thread t owns one 16-byte (16 channels) or 4-byte (2 channels) slot

@@ -2629,8 +2629,8 @@ void cell_ranges(const SearchArgs& a, const uint32_t* count, hipStream_t s) {
 }
 
 // Pass B over `order` (count on the device): one lane per node (G == 1) or G lanes.
-unsigned tail_pass(const SearchArgs& a, const SearchPlan& p, const uint32_t* order, const uint32_t* count,
-                   int first, bool guarded, int spec, unsigned tb, BlockSums* sums, hipStream_t s) {
+void tail_pass(const SearchArgs& a, const SearchPlan& p, const uint32_t* order, const uint32_t* count,
+               int first, bool guarded, int spec, unsigned tb, BlockSums* sums, hipStream_t s) {
     // 0: chosen on the device from the list length; negative: the same with a least width
     const int G = p.tail_lanes ? p.tail_lanes : -(p.tail_min_lanes > 8 ? p.tail_min_lanes : 8);
     if (G == 1) {
@@ -2640,7 +2640,7 @@ unsigned tail_pass(const SearchArgs& a, const SearchPlan& p, const uint32_t* ord
         } else {
             walk<2, 0, true>(a, order, count, first, tb, sums, s, spec);
         }
-        return tb;
+        return;
     }
     const unsigned groups = SEARCH_THREADS / (unsigned)(G > 0 ? G : -G);
     unsigned gb = (p.M + groups - 1) / groups;
@@ -2654,10 +2654,9 @@ unsigned tail_pass(const SearchArgs& a, const SearchPlan& p, const uint32_t* ord
         } else {
             hipLaunchKernelGGL((k_tail_auto<2, 0>), dim3(gb), dim3(SEARCH_THREADS), 0, s, a, order, sorted, count, first, G, sums);
         }
-        return gb;
+        return;
     }
     tail_group(a, order, count, p.ndim, guarded ? 1 : 0, G, first, gb, spec, sums, s);
-    return gb;
 }
 
 // ---- batches ------------------------------------------------------------------------
@@ -3638,7 +3637,6 @@ hipError_t launch_search(const SearchArgs& a, const SearchPlan& p, hipStream_t s
     if (nb == 0) return hipSuccess;
     const unsigned tb = nb < kTailBlocks ? nb : kTailBlocks;
     BlockSums* sums = a.sums;
-    int used = 0;
     if (p.precision == 2) {
         // FP64 throughout.  3D: the key-0 pass and the queued walk as in FP32, whatever the
         // tail's length and layout request (391 thousand nodes at 2.5 mm: one lane per node from
@@ -3680,7 +3678,6 @@ hipError_t launch_search(const SearchArgs& a, const SearchPlan& p, hipStream_t s
         } else {
             hipLaunchKernelGGL(k_zero2<0>, dim3(nb), dim3(SEARCH_THREADS), 0, s, a, p.zero, sums);
         }
-        used += (int)nb;
         if (p.ev_shell_end) (void)hipEventRecord(p.ev_shell_end, s);
         if (p.after_zero) {
             hipError_t e = p.after_zero(p.after_zero_user, s);
@@ -3701,9 +3698,9 @@ hipError_t launch_search(const SearchArgs& a, const SearchPlan& p, hipStream_t s
         // nodes it could not certify, resumed where the speculative bound cut them off)
         if (a.tab_len > first) {
             const int spec = p.spec;
-            used += (int)tail_pass(a, p, a.tail_pos, &a.sc->n_tail, first, guarded, spec, tb, sums, s);
+            tail_pass(a, p, a.tail_pos, &a.sc->n_tail, first, guarded, spec, tb, sums, s);
             if (spec == 1)
-                used += (int)tail_pass(a, p, a.fb_list, &a.sc->n_fallback, first, guarded, 2, tb, sums, s);
+                tail_pass(a, p, a.fb_list, &a.sc->n_fallback, first, guarded, 2, tb, sums, s);
         }
         if (p.ev_tail_end) (void)hipEventRecord(p.ev_tail_end, s);
         // guard pass, count reduction and publication in one launch
