@@ -507,12 +507,14 @@ float2* map_ranges(const gammax_ctx* c, const gammax_problem_t* p, const gammax_
 // Whether the groups of a wave in the queued walk take list entries far apart.  Nodes with long
 // walks lie together in the list, and eight of them in one wave keep it going long after the others; entries
 // far apart share no cache lines.  So: far apart when one walk of the context's last map was
-// longer than a quarter of what a wave walks on average (4096 waves in flight), and where no
-// map tells.  Neighbours against far apart: 81 thousand nodes with walks up to 105 thousand rows
+// longer than a quarter of what a wave walks on average (4096 waves in flight), and in the
+// first map of a context.  Neighbours against far apart: 81 thousand nodes with walks up to 105 thousand rows
 // (51x81x81, local 3%/3mm) 4.3-4.9 and 1.2 ms (lane groups 2.6), 178 thousand up to 10 thousand
 // 516 and 259 us (701); evenly long walks 589 and 621 us (770 thousand nodes, 5 % dose error),
 // 168 and 178 us in FP64 (144 thousand, up to 1104 rows).  The result does not depend on it.
-int want_spread(const gammax_ctx* c) { return (uint64_t)c->long_rows * 1024 >= c->tail_cells ? 1 : 0; }
+int want_spread(const gammax_ctx* c) {
+    return c->seq == 0 || (c->long_rows != 0u && (uint64_t)c->long_rows * 1024 >= c->tail_cells) ? 1 : 0;
+}
 
 // Whether the tail walk of a two-grid map is the queued one, by the context's last two-grid maps.  It
 // takes 10 ns per thousand visited cells where 16 lanes per node take 17, but 90 ns per row of
