@@ -2156,7 +2156,9 @@ __device__ __forceinline__ void tail_queue_body(const SearchArgs& a, const TabEn
             // normalised range, bit for bit
             const float glo = dose_norm<float>(lo[k], nd.dr, nd.inv_dd), ghi = dose_norm<float>(hi[k], nd.dr, nd.inv_dd);
             const float m = __builtin_fmaxf(__builtin_fmaxf(glo, -ghi), 0.0f);
-            const float lb = fmadd(m, m, kk[k]);
+            float lb = fmadd(m, m, kk[k]);
+            // FP64: a bound past the float range (doses below 1e-37 under local normalisation) says nothing
+            if constexpr (FP64) lb = lb < Num<float>::inf() ? lb : 0.0f;
             const bool need = ((work >> k) & 1u) && lb < Fm;
             if constexpr (DIM == 3 && MODE == 1) suspect = suspect || !((ghi - glo) * (ghi - glo) < a.ill_span2);
             const unsigned long long mask = __ballot(need);
