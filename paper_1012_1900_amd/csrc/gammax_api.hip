@@ -1486,8 +1486,11 @@ gammax_status_t gammax_map_grids(gammax_ctx_t* c, const gammax_problem_t* p, con
             if ((e = launch_grids_fp64(a, false, lanes, s)) != hipSuccess) return e;
         } else {
             // the 27 key-0 cells one lane per node, then the walk of the nodes left
-            if ((e = launch_grids_zero(a, opt.precision, s)) != hipSuccess) return e;
-            if ((e = launch_grids_tail(a, opt.precision, opt.tail_lanes, queued, s)) != hipSuccess) return e;
+            // (a finite first bound past the table's reach runs again on a longer one, so bounds
+            // are infinite only where the table has no end of its own)
+            const bool far = tab && std::isinf(c->g_geom.r2_cap);
+            if ((e = launch_grids_zero(a, opt.precision, far, s)) != hipSuccess) return e;
+            if ((e = launch_grids_tail(a, opt.precision, opt.tail_lanes, queued && !far, s)) != hipSuccess) return e;
         }
         if (opt.precision == GAMMAX_PREC_GUARDED)
             if ((e = launch_grids_fp64(a, true, lanes, s)) != hipSuccess) return e;

@@ -329,7 +329,8 @@ hipError_t launch_grids_fp64(const GridsArgs& a, bool guard, int lanes, hipStrea
 // the walk of that list starts past the key-0 rows (lanes 0: the queued walk or GRIDS_LANES
 // lanes per node, with equal results; else that many lanes per node).
 constexpr int GRIDS_LANES = 16;
-hipError_t launch_grids_zero(const GridsArgs& a, int precision, hipStream_t s);
+// far: the table has no end of its own, so first bounds may be infinite.
+hipError_t launch_grids_zero(const GridsArgs& a, int precision, bool far, hipStream_t s);
 hipError_t launch_grids_tail(const GridsArgs& a, int precision, int lanes, bool queued, hipStream_t s);
 // The partial counts into the scalars, and the scalars to the pinned ring.
 hipError_t launch_grids_finish(const GridsArgs& a, uint32_t* seq, Scalars* ring, hipStream_t s);

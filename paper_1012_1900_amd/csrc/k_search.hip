@@ -3116,7 +3116,12 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 //
 // A neighbourhood whose doses span too little for an ill-conditioned tetrahedron needs no
 // judgement, nor does one whose whole cells hold none; the others are judged cell by cell.
-template <int GMODE>
+//
+// FAR: the first bound of some node may have overflowed (doses more than 1e19 dD apart, as tails of a
+// dose under local normalisation without a threshold).  Projections of such doses mean little, so which
+// of a node's cells are projected shows: nodes with such a bound or neighbourhood take them one
+// after the other, while they can still lower F.
+template <int GMODE, bool FAR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_grids_zero(GridsArgs a) {
     __shared__ GridsNode s_node[256];
     __shared__ uint16_t s_item[4][26 * 64];   // queued cells: node's lane | cell << 6
@@ -3134,9 +3139,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     // per axis: does the cell at -1 exist, is the cell at +1 whole
     const bool lox = n.cx > 0, loy = n.cy > 0, loz = n.cz > 0;
     const bool hix = n.cx + 2 < enx, hiy = n.cy + 2 < eny, hiz = n.cz + 2 < enz;
+    bool far = FAR && live && !(n.f_start < Num<float>::inf());
     {
         const float c = grids_project(a, q, n, 0, 0, 0, true, true, true, false);
-        n.f = f2u(live ? vmin<float>(u2f(n.f), c) : u2f(n.f));
+        n.f = f2u(live && !far ? vmin<float>(u2f(n.f), c) : u2f(n.f));
     }
     wnode[lane] = n;
     const float Fm = u2f(n.f) + u2f(n.f) * 0x1p-8f;
@@ -3185,7 +3191,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
                 if (az == 0 && ay == 0 && ax == 0) continue;
                 const float lo = dose_norm<float>(vmin<float>(plo[k], clo[k]), n.dr, n.inv_dd);
                 const float hi = dose_norm<float>(vmax<float>(phi[k], chi[k]), n.dr, n.inv_dd);
-                if (GMODE == 1) {
+                if (GMODE == 1 || FAR) {
                     all_lo = vmin<float>(all_lo, lo);
                     all_hi = vmax<float>(all_hi, hi);
                 }
@@ -3193,7 +3199,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
                 const float d = (ax < 0 ? dxl : (ax > 0 ? dxh : 0.0f)) + (ay < 0 ? dyl : (ay > 0 ? dyh : 0.0f)) +
                                 (az < 0 ? dzl : (az > 0 ? dzh : 0.0f));
                 const bool there = (ax >= 0 || lox) && (ay >= 0 || loy) && (az >= 0 || loz);
-                const bool need = live && there && fmadd(m, m, d) < Fm;
+                const bool need = live && !far && there && fmadd(m, m, d) < Fm;
                 const unsigned long long mask = __ballot(need);
                 if (need)
                     item[nq + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] =
@@ -3222,10 +3228,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    const float F = u2f(wnode[lane].f);
+    float F = u2f(wnode[lane].f);
     bool ill = false;
+    if constexpr (FAR) {
+        far = far || (live && !((all_hi - all_lo) * (all_hi - all_lo) * ((q.is.x + q.is.y) + q.is.z) < Num<float>::inf()));
+        if (far) {
+            const GridsNode o = wnode[lane];
+            F = o.f_start;
+#pragma unroll 1
+            for (int c = 0; c < 27; ++c) F = vmin<float>(F, grids_judge(a, q, o, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1, F, ill));
+        }
+    }
     if (GMODE == 1) {
-        const bool suspect = live && !((all_hi - all_lo) * (all_hi - all_lo) <
+        const bool suspect = live && !far && !((all_hi - all_lo) * (all_hi - all_lo) <
                                        (a.den_guard * 0.999f - 1.0f) / ((q.is.x + q.is.y) + q.is.z));
         if (__ballot(suspect) != 0ull && suspect) {   // rare
             const GridsNode o = wnode[lane];   // (read again: the node's registers are free by now)
@@ -3741,11 +3756,16 @@ hipError_t launch_grids_finish(const GridsArgs& a, uint32_t* seq, Scalars* ring,
     return hipGetLastError();
 }
 
-hipError_t launch_grids_zero(const GridsArgs& a, int precision, hipStream_t s) {
+hipError_t launch_grids_zero(const GridsArgs& a, int precision, bool far, hipStream_t s) {
     const int64_t nr = (int64_t)a.rn[0] * a.rn[1] * a.rn[2];   // the list holds at most nr nodes
     const unsigned nb = (unsigned)((nr + 255) / 256);
-    if (precision == 1) hipLaunchKernelGGL(k_grids_zero<1>, dim3(nb), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(k_grids_zero<0>, dim3(nb), dim3(256), 0, s, a);
+    if (precision == 1) {
+        if (far) hipLaunchKernelGGL((k_grids_zero<1, true>), dim3(nb), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_grids_zero<1, false>), dim3(nb), dim3(256), 0, s, a);
+    } else {
+        if (far) hipLaunchKernelGGL((k_grids_zero<0, true>), dim3(nb), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_grids_zero<0, false>), dim3(nb), dim3(256), 0, s, a);
+    }
     return hipGetLastError();
 }
 
