@@ -42,9 +42,9 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense BF16 matrix cores
 # hash differs the traffic is reported as null.
 TRAFFIC = {
     "3d_128x128x96_2.5mm": {
-        "bytes": (16.09 + 5.47) * 1e6,
+        "bytes": (16.11 + 5.48) * 1e6,
         "source": "paper_1012_1900_amd/csrc/k_search.hip",
-        "sha256": "1654df21cfba85a2b2110365af3f2dc040829957bb8875d82464e58b9fd258c4",
+        "sha256": "751c8a6655dca8f99dd2e897cf311113479bc51680c74037eda0e64be01b9403",
         "profile": "profiles/pmc_hbm_bytes_128x128x96_2.5mm_3pct3mm.md",
     },
 }
@@ -731,6 +731,8 @@ def main():
                                              and args.dta == 3.0 and args.precision == "guarded"),
                     "kernel": f"{kern} (key-0 cells of every node)",
                     "flop_per_cell": FLOP_PER_CELL_REFERENCE[nd],
+                    "flop_model": "priced, not executed: every face of every key-0 cell by its own normal"
+                                  " equations; the kernel projects fewer faces, by the closed forms",
                     "algorithmic_flop_per_launch": flops, "avg_launch_ms": round(ms_search, 5),
                     "closed_form": {"flop_per_cell": FLOP_PER_CELL[nd], "achieved": round(achieved_cf, 3),
                                     "frac": round(achieved_cf / PEAK_FP32_TFLOPS, 4)}}

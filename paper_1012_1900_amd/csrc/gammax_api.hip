@@ -486,11 +486,11 @@ bool short_tail(const gammax_ctx* c, const gammax_options_t& opt) {
 
 // Whether the tail walk of an n-node map should write every cell's dose range first.  That
 // costs about 12 bytes of traffic per node of the grid (36 us at 192x256x256) and saves eight
-// gathers per cell that the queued walk visits, so it pays once such a tail visits more than about twice as many
-// cells as the grid has, judged by the context's last map (1.2 visits per node: 227 us with,
-// 226 us without; 1.8: 356 against 387 us; 43 at a 5 % dose error:
-// 2.8 -> 2.2 ms for the map of a 160x200x200 pair).  The result does
-// not depend on it.  The walk forms the ranges' byte offsets in 32 bits.
+// gathers per cell that the queued walk visits, so it pays once such a tail visits more than
+// about twice as many cells as the grid has, judged by the context's last map (1.2 visits per
+// node: 227 us with, 226 us without; 1.8: 356 against 387 us; 43 at a 5 % dose error: 2.8 -> 2.2
+// ms for the map of a 160x200x200 pair).  The result does not depend on it.  The walk forms the
+// ranges' byte offsets in 32 bits.
 bool want_ranges(const gammax_ctx* c, int64_t n) {
     return n < ((int64_t)1 << 29) && c->tail_hint >= QUEUED_TAIL && c->tail_cells >= 2 * (uint64_t)n;
 }
@@ -505,25 +505,26 @@ float2* map_ranges(const gammax_ctx* c, const gammax_problem_t* p, const gammax_
 }
 
 // Whether the groups of a wave in the queued walk take list entries far apart.  Nodes with long
-// walks lie together in the list, and eight of them in one wave keep it going long after the others; entries
-// far apart share no cache lines.  So: far apart when one walk of the context's last map was
-// longer than a quarter of what a wave walks on average (4096 waves in flight), and in the
-// first map of a context.  Neighbours against far apart: 81 thousand nodes with walks up to 105 thousand rows
-// (51x81x81, local 3%/3mm) 4.3-4.9 and 1.2 ms (lane groups 2.6), 178 thousand up to 10 thousand
-// 516 and 259 us (701); evenly long walks 589 and 621 us (770 thousand nodes, 5 % dose error),
-// 168 and 178 us in FP64 (144 thousand, up to 1104 rows).  The result does not depend on it.
+// walks lie together in the list, and eight of them in one wave keep it going long after the
+// others; entries far apart share no cache lines.  So: far apart when one walk of the context's
+// last map took at least four times the rows that a wave has cells to visit on average (4096 waves
+// in flight), and in the first map of a context.  Neighbours against far apart: 81 thousand nodes
+// with walks up to 105 thousand rows (51x81x81, local 3%/3mm) 4.3-4.9 and 1.2 ms (lane groups
+// 2.6), 178 thousand up to 10 thousand 516 and 259 us (701); evenly long walks 589 and 621 us (770
+// thousand nodes, 5 % dose error), 168 and 178 us in FP64 (144 thousand, up to 1104 rows).  The
+// result does not depend on it.
 int want_spread(const gammax_ctx* c) {
     return c->seq == 0 || (c->long_rows != 0u && (uint64_t)c->long_rows * 1024 >= c->tail_cells) ? 1 : 0;
 }
 
-// Whether the tail walk of a two-grid map is the queued one, by the context's last two-grid maps.  It
-// takes 10 ns per thousand visited cells where 16 lanes per node take 17, but 90 ns per row of
-// the longest walk against 65, so it pays from some nodes per row of that walk on.  16 lanes
+// Whether the tail walk of a two-grid map is the queued one, by the context's last two-grid
+// maps.  It takes 10 ns per thousand visited cells where 16 lanes per node take 17, but 90 ns per
+// row of the longest walk against 65, so it pays from some nodes per row of that walk on.  16 lanes
 // against queued, us, by nodes and longest walk: 2.9 thousand, 248 rows 22 and 28; 10 thousand, 248
-// rows 33 and 31; 37 thousand, 152 rows 68 and 38; 25 thousand, 586 rows 80 and 63; 8 thousand,
-// 586 rows 44 and 53; 51 thousand, 964 rows 88-106 and 115; 146 thousand, 1518 rows 232 and 217;
-// 130 thousand, 4088 rows 270 and 370; 657 thousand, 12476 rows 1011 and 1424; 706 thousand, 892
-// rows 886 and 550.  The results do not depend on it.
+// rows 33 and 31; 37 thousand, 152 rows 68 and 38; 25 thousand, 586 rows 80 and 63; 8 thousand, 586
+// rows 44 and 53; 51 thousand, 964 rows 88-106 and 115; 146 thousand, 1518 rows 232 and 217; 130
+// thousand, 4088 rows 270 and 370; 657 thousand, 12476 rows 1011 and 1424; 706 thousand, 892 rows
+// 886 and 550.  The results do not depend on it.
 bool grids_queued(const gammax_ctx* c) {
     const uint64_t rows = std::max(c->g_long_rows, LONG_WALK_ROWS);   // (shorter ones are not recorded)
     return c->g_tail >= (rows <= 640 ? 36 : 60) * rows;

@@ -733,8 +733,8 @@ __device__ __forceinline__ uint32_t zero_cells(int DIM, int x, int y, int z, int
 // visits at most 27 cells), the waves' from one barrier, and only a block with tail or guard
 // nodes waits for the atomics that give it its slots.  all_cells: the cells of tail nodes are counted
 // here too (two grids).  (Two appends and a reduction of five
-// counts by shuffles, with eight barriers between them, took 34.0 and 191 us where this takes
-// 32.3 and 180: 391 thousand nodes at 2.5 mm, 3.1 million at 1.25 mm.)
+// counts by shuffles, with eight barriers between them, took 1.7 and 11 us longer in passes of 32
+// and 180 us: 391 thousand nodes at 2.5 mm, 3.1 million at 1.25 mm.)
 __device__ __forceinline__ void append_tail(const SearchArgs& a, uint32_t pos, int node, uint32_t bound, uint32_t key) {
     a.tail_node[pos] = (uint32_t)node;
     a.tail_f[pos] = bound;
@@ -829,9 +829,9 @@ __device__ __forceinline__ void zero_epilogue(const Args& a, BlockSums* bins, ui
 // minimum has the same bits as over all 208 faces.
 //
 // Bound by VALU issue (1870 instructions of a wave against 3270 over all faces at 2.5 mm) and,
-// at 391 thousand nodes, by the two rounds its 1528 blocks take: 40.0 -> 32.3 us there,
-// 3.1 million nodes at 1.25 mm 259 -> 180 us (guarded).  Capped at 128 VGPRs for four waves per
-// SIMD (140 uncapped: 34.7 and 204 us).
+// at 391 thousand nodes, by the two rounds its 1528 blocks take: 40.0 -> 31.6 us there,
+// 3.1 million nodes at 1.25 mm 259 -> 174 us (guarded).  Capped at 128 VGPRs for four waves per
+// SIMD (uncapped, at 140, 1.07 and 1.13 times as long).
 
 // Chain sums at a block stepped before the node (M = 1: mu = -1) or after it (M = 0: mu = 0).
 template <int M, typename T>
@@ -1137,9 +1137,9 @@ __device__ __forceinline__ void zero3_body(const SearchArgs& a, const ZeroGeo& z
     const uint32_t both = on6 & (on6 >> 3), one = (on6 | (on6 >> 3)) & 7u;
     uint32_t cells = open && one == 7u ? 1u << __popc(both & 7u) : 0u;
     // rare: the tetrahedra of a steep neighbourhood's whole cells are judged (their denominators
-    // only: projecting the cells again for it, the pass took 58 us at 96x128x128 with the threshold at 100, where
-    // every neighbourhood is steep; this takes 38, and 33 where none is), and a node whose F fell to 0 counts
-    // the cells up to there, cell by cell in table order
+    // only: projecting the cells again for it, the pass took 58 us at 96x128x128 with the
+    // threshold at 100, where every neighbourhood is steep; this takes 38, and 33 where none is),
+    // and a node whose F fell to 0 counts the cells up to there, cell by cell in table order
     const bool zero = open && F == T(0);
     if (__ballot(redo || zero) != 0ull) {
         if (q == 0u && __ballot(redo) == 0ull) {
@@ -1841,15 +1841,16 @@ __global__ __launch_bounds__(SEARCH_THREADS) __attribute__((amdgpu_waves_per_eu(
 //         bound F has passed meanwhile is dropped.
 // A group that finishes a node takes its next one without waiting for the other groups, and
 // past TQ_LONG rows a node is scanned by the whole wave (its walk would outlast the others').
-// The groups of a wave take neighbouring list entries, whose cells share cache lines, or (spread)
-// entries far apart, since long walks lie together in the list and a wave walks its own one after the other.
+// The groups of a wave take neighbouring list entries, whose cells share cache lines, or
+// (spread) entries far apart, since long walks lie together in the list and a wave walks its own
+// one after the other.
 //
 // Why: a projection costs about ten times a test.  A tail node visits about 30 cells (158 at a
 // 5 % dose error) of which 11 (23) can lower F, and walking 8 rows of a node at a time
 // projected all 64 of the wave's whenever one could.  Measured, walking 8 rows at a time against
-// this: 482535 nodes at 192x256x256 410 -> 227 us; 349353 nodes under local normalisation
-// (walks up to 1440 rows) 407 -> 190 us; 1.25 M nodes at 160x200x200 with a 5 % dose error
-// 4.3 -> 2.0 ms.  Bound by VALU issue (80 % of it: 191 instructions of a wave per node, of
+// this: 482535 nodes at 192x256x256 410 -> 204 us; 349353 nodes under local normalisation
+// (walks up to 1440 rows) 407 -> 168 us; 1.25 M nodes at 160x200x200 with a 5 % dose error
+// 4.3 -> 1.54 ms.  Bound by VALU issue (80 % of it: 191 instructions of a wave per node, of
 // which the 11 projections are 74).
 //
 // A projection's or test's arithmetic is that of tail_group_body, the minimum does not depend
@@ -3060,8 +3061,9 @@ __device__ __forceinline__ bool grids_ill(const GridsArgs& a, const GridsGeo& q,
 }
 
 // The queued passes below project a node's cells in another order than one lane per node (or a
-// group of lanes, batch by batch) would, and more or fewer of them, depending on which nodes share the wave; so
-// a node that met an ill-conditioned tetrahedron in any whole cell (rare) is judged by that order again.
+// group of lanes, batch by batch) would, and more or fewer of them, depending on which nodes
+// share the wave; so a node that met an ill-conditioned tetrahedron in any whole cell (rare) is
+// judged by that order again.
 // The cell at offset (az, ay, ax) in it: dist^2 to its faces if it can still lower F (its
 // tetrahedra are judged then), else infinity.
 __device__ __forceinline__ float grids_judge(const GridsArgs& a, const GridsGeo& q, const GridsNode& n, int az, int ay,
@@ -3236,7 +3238,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             const GridsNode o = wnode[lane];
             F = o.f_start;
 #pragma unroll 1
-            for (int c = 0; c < 27; ++c) F = vmin<float>(F, grids_judge(a, q, o, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1, F, ill));
+            for (int c = 0; c < 27; ++c)
+                F = vmin<float>(F, grids_judge(a, q, o, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1, F, ill));
         }
     }
     if (GMODE == 1) {
@@ -3253,7 +3256,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
             }
             float f = o.f_start;
 #pragma unroll 1
-            for (int c = 0; c < 27 && any; ++c) f = vmin<float>(f, grids_judge(a, q, o, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1, f, ill));
+            for (int c = 0; c < 27 && any; ++c)
+                f = vmin<float>(f, grids_judge(a, q, o, c / 9 - 1, (c / 3) % 3 - 1, c % 3 - 1, f, ill));
         }
     }
     const bool to_guard = GMODE == 1 && ill;
@@ -3267,7 +3271,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 // distance of its cell (the key is its least over the holding cell) and the range of its
 // corner doses; visited cells are those of the rows below the final F.  40 us at 36 thousand
 // nodes where 16 lanes per node take 68 (46 with the table in memory and the finished counts in
-// registers).  It is taken where grids_queued says so: its steps are heavier, so a long walk outlasts 16 lanes.
+// registers).  It is taken where grids_queued says so: its steps are heavier, so one long walk
+// outlasts 16 lanes.
 template <int GMODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_grids_tail(GridsArgs a) {
     constexpr int FIRST = 27;   // rows of the key-0 cells
@@ -3486,9 +3491,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 // G lanes per node walk the lower-key table of the evaluation grid.  LIST 0: the listed nodes
 // from row 0 (FP64 maps); 1: the guard list (FP64) from row 0; 2: the tail list of the key-0
-// pass from the first row past the key-0 cells.  below: count the visited cells below the final F (as the
-// queued walk does: the automatic layout's count does not depend on which of the two it takes),
-// not those that the node's last batch visited past it.
+// pass from the first row past the key-0 cells.  below: count the visited cells below the final
+// F (as the queued walk does: the automatic layout's count does not depend on which of the two it
+// takes), not those that the node's last batch visited past it.
 template <typename T, int GMODE, int LIST>
 __global__ __launch_bounds__(256) void k_grids_walk(GridsArgs a, int G, bool below) {
     static_assert((LIST == 2) == (sizeof(T) == 4), "FP32 walks the tail list, FP64 the others");
